@@ -31,19 +31,24 @@ __device__ __forceinline__ uint64_t spread21(uint64_t v) {
     return v;
 }
 
-__global__ void k_morton(int64_t n, const double *__restrict__ x, double ibox,
-                         uint64_t *__restrict__ keys, int32_t *__restrict__ idx) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+__device__ __forceinline__ uint64_t morton_key(double x, double y, double z, double ibox) {
+    const double v[3] = {x, y, z};
     uint64_t c[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        double f = x[3 * i + a] * ibox;
+        double f = v[a] * ibox;
         f = fmin(fmax(f, 0.0), 1.0);
         uint64_t q = (uint64_t)(f * 2097152.0);
         c[a] = q > 2097151ULL ? 2097151ULL : q;
     }
-    keys[i] = (spread21(c[0]) << 2) | (spread21(c[1]) << 1) | spread21(c[2]);
+    return (spread21(c[0]) << 2) | (spread21(c[1]) << 1) | spread21(c[2]);
+}
+
+__global__ void k_morton(int64_t n, const double *__restrict__ x, double ibox,
+                         uint64_t *__restrict__ keys, int32_t *__restrict__ idx) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    keys[i] = morton_key(x[3 * i], x[3 * i + 1], x[3 * i + 2], ibox);
     idx[i] = (int32_t)i;
 }
 
@@ -105,14 +110,12 @@ __global__ void k_merge_level(int64_t first, int64_t count, double *__restrict__
     hmax[v] = fmax(hmax[a], hmax[b]);
 }
 
-// Candidate-list capacity of the smoothing-length solve (entries per
-// particle) and the most device memory the lists may take.
-constexpr int kHList = 128;
-// Entries per particle of the neighbour lists the count pass keeps (same budget).
+// Entries per particle of the neighbour lists the count pass keeps, and the
+// most device memory those lists may take.
 constexpr int kNList = 128;
-constexpr int64_t kHListBytes = int64_t(16) << 30;
+constexpr int64_t kNListBytes = int64_t(16) << 30;
 // Bit of a particle's iteration count set when its candidate list overflowed
-// (later evaluations at a smaller h walked the tree again).
+// (it was gathered again at a smaller radius).
 constexpr int32_t kIterOverflow = 1 << 24;
 
 struct Tree {
@@ -123,65 +126,12 @@ struct Tree {
 // ---------------------------------------------------------------------------
 // Smoothing length: root of g(h) = h^3 sum_j W(r_j, kappa h) - eta^3
 // (eq:number-of-neighbors), i.e. (sigma/kappa^3) sum_j w(r_j / (kappa h)) = eta^3,
-// by Newton-Raphson safeguarded with bisection.  An evaluation of g and dg/dh
-// either walks the tree with radius kappa h or reads the particle's candidate
-// list: the r^2 < (kappa h_l)^2 of the last walk, at h_l >= h, in walk order
-// (entry k of particle i at list[k n + i]).  A walk at the smaller radius
-// opens a subset of the same nodes in the same order, and a particle of a node
-// it skips lies beyond kappa h, so both routes sum the same terms in the same
-// order and give the same bits.  A particle whose list would overflow walks.
-__device__ int h_eval(const Tree &T, const double *__restrict__ xs, int64_t n, double px,
-                      double py, double pz, double h, double kappa, double box, double ibox,
-                      double *__restrict__ list, int cap, double &sw, double &sdw) {
-    const double H = kappa * h, H2 = H * H, iH = 1.0 / H;
-    const double acc2 = H2 * (1.0 + 1e-12);
-    double a = 0.0, b = 0.0;
-    int cnt = 0;
-    traverse(
-        T.P,
-        [&](int64_t v) { return box_dist2(T.lo + 3 * v, T.hi + 3 * v, px, py, pz, box) < acc2; },
-        [&](int64_t l) {
-            int64_t j0 = l * kLeaf, j1 = min(n, j0 + kLeaf);
-            for (int64_t j = j0; j < j1; ++j) {
-                double sx = min_image(xs[3 * j] - px, box, ibox);
-                double sy = min_image(xs[3 * j + 1] - py, box, ibox);
-                double sz = min_image(xs[3 * j + 2] - pz, box, ibox);
-                double r2 = sx * sx + sy * sy + sz * sz;
-                if (r2 < H2) {
-                    if (cnt < cap) list[(int64_t)cnt * n] = r2;
-                    ++cnt;
-                    double q = sqrt(r2) * iH;
-                    a += kern_w(q);
-                    b += kern_dw(q) * q;
-                }
-            }
-        });
-    sw = a;
-    sdw = b;
-    return cnt;
-}
-
-__device__ void h_eval_list(const double *__restrict__ list, int64_t n, int cnt, double h,
-                            double kappa, double &sw, double &sdw) {
-    const double H = kappa * h, H2 = H * H, iH = 1.0 / H;
-    double a = 0.0, b = 0.0;
-    for (int k = 0; k < cnt; ++k) {
-        const double r2 = list[(int64_t)k * n];
-        if (r2 < H2) {
-            double q = sqrt(r2) * iH;
-            a += kern_w(q);
-            b += kern_dw(q) * q;
-        }
-    }
-    sw = a;
-    sdw = b;
-}
-
+// by Newton-Raphson safeguarded with bisection.  h_solve_point walks the tree
+// with one thread for every evaluation: the fallback of h_solve_wave.
 __device__ double h_solve_point(const Tree &T, const double *__restrict__ xs, int64_t n,
                                 double px, double py, double pz, double h0, double eta,
-                                double kappa, double box, double hcap, double *__restrict__ list,
-                                int cap, int32_t max_iter, int32_t &iters, int32_t &flags,
-                                bool &overflow) {
+                                double kappa, double box, double hcap, int32_t max_iter,
+                                int32_t &iters, int32_t &flags) {
     const double pref = kSigma3 / (kappa * kappa * kappa);
     const double eta3 = eta * eta * eta;
     const double eps4 = 4.0 * 2.220446049250313e-16;
@@ -189,21 +139,30 @@ __device__ double h_solve_point(const Tree &T, const double *__restrict__ xs, in
     // iterates stay at or below hcap (compact support at most half the box);
     // a root beyond it is an error
     double lo = 0.0, hi = INFINITY, h = fmin(h0, hcap);
-    double hl = 0.0;     // the list holds the walk at hl (0: no list)
-    int lcnt = 0;
     int32_t it = 0;
     bool ok = false, big = false;
     for (it = 0; it < max_iter; ++it) {
-        double sw, sdw;
-        if (h <= hl) {
-            h_eval_list(list, n, lcnt, h, kappa, sw, sdw);
-        } else {
-            lcnt = h_eval(T, xs, n, px, py, pz, h, kappa, box, ibox, list, cap, sw, sdw);
-            hl = lcnt <= cap ? h : 0.0;
-            if (list && lcnt > cap) overflow = true;
-        }
-        double g = pref * sw - eta3;
-        double dg = -pref * sdw / h;
+        const double H = kappa * h, H2 = H * H, iH = 1.0 / H, acc2 = H2 * (1.0 + 1e-12);
+        double sw = 0.0, sdw = 0.0;
+        traverse(
+            T.P,
+            [&](int64_t v) { return box_dist2(T.lo + 3 * v, T.hi + 3 * v, px, py, pz, box) < acc2; },
+            [&](int64_t l) {
+                const int64_t j0 = l * kLeaf, j1 = min(n, j0 + kLeaf);
+                for (int64_t j = j0; j < j1; ++j) {
+                    const double sx = min_image(xs[3 * j] - px, box, ibox);
+                    const double sy = min_image(xs[3 * j + 1] - py, box, ibox);
+                    const double sz = min_image(xs[3 * j + 2] - pz, box, ibox);
+                    const double r2 = sx * sx + sy * sy + sz * sz;
+                    if (r2 < H2) {
+                        const double q = sqrt(r2) * iH;
+                        sw += kern_w(q);
+                        sdw += kern_dw(q) * q;
+                    }
+                }
+            });
+        const double g = pref * sw - eta3;
+        const double dg = -pref * sdw / h;
         if (g == 0.0) {
             ok = true;
             break;
@@ -217,7 +176,7 @@ __device__ double h_solve_point(const Tree &T, const double *__restrict__ xs, in
             }
             hn = 2.0 * h;                        // expand until bracketed
             if (dg > 0.0) {
-                double nt = h - g / dg;
+                const double nt = h - g / dg;
                 if (nt > h && nt < 4.0 * h) hn = nt;
             }
             hn = fmin(hn, hcap);
@@ -291,21 +250,334 @@ __global__ void k_h_guess(int64_t n, int64_t P, const double *__restrict__ lo,
     h[i] = fmin(fmin(g, 0.8 * gm), 0.25 * box);
 }
 
-__global__ void k_h_solve(int64_t n, Tree T, const double *__restrict__ xs, double eta,
-                          double kappa, double box, double *__restrict__ h,
-                          double *__restrict__ list, int cap, int32_t max_iter,
-                          int32_t *__restrict__ iters, int32_t *__restrict__ status) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// ---------------------------------------------------------------------------
+// Neighbour search of one wave for up to kPts points (8 lanes each: lane =
+// 8 p + c), a point p within R_p of the particles it wants (R_p < 0: none;
+// HM: within max(R_p, H_j), nodes opened by their largest H).  One thread per
+// particle walked a chain of some 700 dependent node and particle reads with
+// every lane on lines of its own, so the search ran at the memory's latency
+// (12.4 + 8.6 ms for the solve and the count of the 128^3 lattice, and 3.4 +
+// 3.7 ms for 22 thousand clustered particles, which fill a third of the CUs).
+// Here the wave opens the tree 6 levels at a time, one node a lane, against
+// the points' bounding box; the leaves that pass are tested against each
+// point (8 leaves x 8 points); the particles of the leaves left are read two
+// leaves at a time, kept if they lie near the box, and collected in LDS, in
+// index order, until there are 64.  emit(m) is then called with m <= 64
+// candidates in B for the exact test of every point against every candidate.
+constexpr int kPts = 8;
+template <bool HM> struct Candidates {
+    double x[128], y[128], z[128], H[HM ? 128 : 1];
+    int32_t j[128];
+    int32_t leaf[64];
+};
+
+__device__ __forceinline__ double wave_min(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+    return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+}
+// Squared distance of the intervals' product [al, ah] to [bl, bh], periodic.
+__device__ __forceinline__ double boxes_dist2(const double (&al)[3], const double (&ah)[3],
+                                              const double *bl, const double *bh, double box) {
+    double d2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double up = bl[a] - ah[a], dn = al[a] - bh[a];   // b above a, b below a
+        const double d = fmin(fmax(0.0, fmax(up, dn)),
+                              fmin(fmax(0.0, up + box), fmax(0.0, dn + box)));
+        d2 += d * d;
+    }
+    return d2;
+}
+
+template <bool HM, class Emit>
+__device__ void wave_gather(const Tree &T, int depth, const double *__restrict__ xs,
+                            const double *__restrict__ H, int64_t n, double box, double px,
+                            double py, double pz, double R, Candidates<HM> &B, Emit &&emit) {
+    const int lane = threadIdx.x & 63;
+    const bool on = R >= 0.0;
+    if (__ballot(on) == 0) return;
+    const double gl[3] = {wave_min(on ? px : INFINITY), wave_min(on ? py : INFINITY),
+                          wave_min(on ? pz : INFINITY)};
+    const double gh[3] = {wave_max(on ? px : -INFINITY), wave_max(on ? py : -INFINITY),
+                          wave_max(on ? pz : -INFINITY)};
+    const double Rg = wave_max(R);
+    constexpr double kSlack = 1.0 + 1e-12;      // the exact test is emit's
+    int nb = 0;                                 // candidates collected
+    // the accepted ones of 64 leaves v0 + lane of the tree
+    auto leaves = [&](uint64_t hit, int64_t v0) {
+        // hits in order, then 8 leaves x 8 points at a time
+        if ((hit >> lane) & 1) B.leaf[__popcll(hit & ((uint64_t(1) << lane) - 1))] = lane;
+        wave_lds_sync();
+        const int nh = __popcll(hit);
+        uint64_t take = 0;
+        for (int t = 0; t < nh; t += 8) {
+            // lane = 8 leaf + point: the point's data from lane 8 point
+            const int src = 8 * (lane & 7);
+            const double qx = __shfl(px, src, 64), qy = __shfl(py, src, 64),
+                         qz = __shfl(pz, src, 64), qR = __shfl(R, src, 64);
+            const int e = t + (lane >> 3);
+            bool ok = false;
+            if (e < nh && qR >= 0.0) {
+                const int64_t v = v0 + B.leaf[e];
+                const double rr = HM ? fmax(qR, T.hmax[v]) : qR;
+                ok = box_dist2(T.lo + 3 * v, T.hi + 3 * v, qx, qy, qz, box) < rr * rr * kSlack;
+            }
+            const uint64_t m = __ballot(ok);
+            for (int q = 0; q < 8 && t + q < nh; ++q)
+                if ((m >> (8 * q)) & 0xff) take |= uint64_t(1) << (t + q);
+        }
+        while (take) {
+            // two accepted leaves, 32 particles each
+            const int e0 = __ffsll((unsigned long long)take) - 1;
+            take &= take - 1;
+            const int e1 = take ? __ffsll((unsigned long long)take) - 1 : -1;
+            if (take) take &= take - 1;
+            const int e = lane < 32 ? e0 : e1;
+            bool ok = false;
+            double cx = 0.0, cy = 0.0, cz = 0.0, cH = 0.0;
+            int64_t j = 0;
+            if (e >= 0) {
+                j = (v0 + B.leaf[e] - T.P) * kLeaf + (lane & 31);
+                if (j < n) {
+                    cx = xs[3 * j];
+                    cy = xs[3 * j + 1];
+                    cz = xs[3 * j + 2];
+                    double rr = Rg;
+                    if (HM) {
+                        cH = H[j];
+                        rr = fmax(rr, cH);
+                    }
+                    const double c3[3] = {cx, cy, cz};
+                    ok = boxes_dist2(gl, gh, c3, c3, box) < rr * rr * kSlack;
+                }
+            }
+            const uint64_t m = __ballot(ok);
+            if (ok) {
+                const int pos = nb + __popcll(m & ((uint64_t(1) << lane) - 1));
+                B.x[pos] = cx;
+                B.y[pos] = cy;
+                B.z[pos] = cz;
+                if (HM) B.H[pos] = cH;
+                B.j[pos] = (int32_t)j;
+            }
+            nb += __popcll(m);
+            wave_lds_sync();
+            if (nb >= 64) {
+                emit(64);
+                nb -= 64;
+                wave_lds_sync();
+                if (lane < nb) {
+                    B.x[lane] = B.x[64 + lane];
+                    B.y[lane] = B.y[64 + lane];
+                    B.z[lane] = B.z[64 + lane];
+                    if (HM) B.H[lane] = B.H[64 + lane];
+                    B.j[lane] = B.j[64 + lane];
+                }
+                wave_lds_sync();
+            }
+        }
+    };
+    // depth first over steps of 6 levels (the first takes what is left over);
+    // every node id and mask is the same in all lanes
+    auto open = [&](int64_t v) {
+        const double rr = HM ? fmax(Rg, T.hmax[v]) : Rg;
+        return boxes_dist2(gl, gh, T.lo + 3 * v, T.hi + 3 * v, box) < rr * rr * kSlack;
+    };
+    const int steps = depth > 0 ? (depth + 5) / 6 : 1;
+    int64_t v0[6];
+    uint64_t todo[6];
+    int lev = 0;
+    v0[0] = int64_t(1) << (depth - 6 * (steps - 1));
+    todo[0] = __ballot(lane < v0[0] && open(v0[0] + min((int64_t)lane, v0[0] - 1)));
+#pragma unroll 1
+    while (true) {
+        if (lev == steps - 1) {
+            leaves(todo[lev], v0[lev]);
+            todo[lev] = 0;
+        }
+        while (lev >= 0 && todo[lev] == 0) --lev;
+        if (lev < 0) break;
+        const int c = __ffsll((unsigned long long)todo[lev]) - 1;
+        todo[lev] &= todo[lev] - 1;
+        const int64_t v = (v0[lev] + c) << 6;
+        ++lev;
+        v0[lev] = v;
+        todo[lev] = __ballot(open(v + lane));
+    }
+    if (nb > 0) emit(nb);
+}
+
+// Sum over the 8 lanes of a point, the same bits on each of them.
+__device__ __forceinline__ double sum8(double v) {
+    quad_sum<4>(v);
+    return v + __shfl_xor(v, 4, 64);
+}
+
+// Smoothing lengths of the wave's points: the iteration of h_solve_point, its
+// sums over r_j < kappa h_R collected once per point in LDS (kHList entries)
+// and spread over the point's 8 lanes.  A point whose root lies beyond h_R
+// gathers again further out, one with more than kHList particles in reach
+// nearer in (overflow set); one whose two radii meet falls back to the serial
+// walk.
+constexpr int kHList = 128;
+template <class Cand>
+__device__ double h_solve_wave(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
+                               bool on, double px, double py, double pz, double h0, double eta,
+                               double kappa, double box, int32_t max_iter, Cand &B,
+                               double (&list)[kPts][kHList], int32_t &iters, int32_t &flags,
+                               bool &overflow) {
+    const int lane = threadIdx.x & 63, p = lane >> 3, c = lane & 7;
+    const double pref = kSigma3 / (kappa * kappa * kappa), eta3 = eta * eta * eta;
+    const double eps4 = 4.0 * 2.220446049250313e-16, ibox = 1.0 / box;
+    const double hcap = 0.5 * box / kappa;
+    double lo = 0.0, hi = INFINITY, h = fmin(h0, hcap);
+    double small = 0.0;                        // largest h_R known to be below the root
+    double hR = fmin(1.5 * h, hcap);           // the list's reach over kappa
+    int32_t it = 0;
+    bool busy = on, serial = false;
+#pragma unroll 1
+    for (int round = 0; round < 64 && __ballot(busy) != 0; ++round) {
+        const double R = kappa * hR, R2 = R * R;
+        int cnt = 0;
+        wave_gather<false>(T, depth, xs, nullptr, n, box, px, py, pz, busy ? R : -1.0, B,
+                           [&](int m) {
+            for (int s = 0; s < m; s += 8) {
+                const int q = s + c;
+                double r2 = INFINITY;
+                if (q < m) {
+                    const double sx = min_image(B.x[q] - px, box, ibox);
+                    const double sy = min_image(B.y[q] - py, box, ibox);
+                    const double sz = min_image(B.z[q] - pz, box, ibox);
+                    r2 = sx * sx + sy * sy + sz * sz;
+                }
+                const bool hit = busy && r2 < R2;
+                const uint32_t seg = (uint32_t)(__ballot(hit) >> (lane & 56)) & 0xff;
+                const int pos = cnt + __popc(seg & ((1u << c) - 1));
+                if (hit && pos < kHList) list[p][pos] = sqrt(r2);
+                cnt += __popc(seg);
+            }
+        });
+        wave_lds_sync();
+        if (busy && cnt > kHList) {
+            overflow = true;
+            // nearer in, but beyond what is known to be too near
+            const double t = hR * cbrt(0.6 * kHList / (double)cnt);
+            const double nr = fmax(t, 0.5 * (small + hR));
+            if (nr > small * (1.0 + 1e-6) && nr < hR && round < 48) {
+                hR = t > small ? t : nr;
+            } else {
+                serial = true;
+                busy = false;
+            }
+            h = fmin(h, hR);
+            cnt = 0;
+        } else if (busy) {
+            // Newton-Raphson on the list, while it reaches
+            while (busy) {
+                if (it >= max_iter) {
+                    flags |= ST_NOCONV;
+                    busy = false;
+                    break;
+                }
+                ++it;
+                const double iH = 1.0 / (kappa * h);
+                double sw = 0.0, sdw = 0.0;
+                for (int k = c; k < cnt; k += 8) {
+                    const double q = list[p][k] * iH;
+                    sw += kern_w(q);
+                    sdw += kern_dw(q) * q;
+                }
+                sw = sum8(sw);
+                sdw = sum8(sdw);
+                const double g = pref * sw - eta3, dg = -pref * sdw / h;
+                if (g == 0.0) {
+                    busy = false;
+                    break;
+                }
+                if (g < 0.0) lo = h; else hi = h;
+                double hn;
+                if (hi == INFINITY) {
+                    if (h >= hcap) {             // g < 0 at the cap
+                        flags |= ST_BIGH;
+                        busy = false;
+                        break;
+                    }
+                    hn = 2.0 * h;                // expand until bracketed
+                    if (dg > 0.0) {
+                        const double nt = h - g / dg;
+                        if (nt > h && nt < 4.0 * h) hn = nt;
+                    }
+                    hn = fmin(hn, hcap);
+                    if (hn > hR) {
+                        if (h < hR) {
+                            hn = hR;             // the list's end first
+                        } else {                 // the root lies beyond: gather again
+                            small = hR;
+                            hR = fmin(fmax(1.15 * hn, 1.25 * hR), hcap);
+                            h = hn;
+                            break;
+                        }
+                    }
+                } else {
+                    // the step test comes before the bracket test (see h_solve_point)
+                    hn = dg > 0.0 ? h - g / dg : -1.0;
+                    if (dg > 0.0 && fabs(hn - h) <= eps4 * h) {
+                        h = hn;
+                        busy = false;
+                        break;
+                    }
+                    if (!(hn > lo && hn < hi)) hn = 0.5 * (lo + hi);
+                    if (fabs(hn - h) <= eps4 * h || hi - lo <= eps4 * hi) {
+                        h = hn;
+                        busy = false;
+                        break;
+                    }
+                }
+                h = hn;
+            }
+        }
+        wave_lds_sync();
+    }
+    if (busy) serial = true;
+    if (serial) {
+        // (all 8 lanes of the point walk: the same reads, the same result)
+        int32_t fl = 0;
+        h = h_solve_point(T, xs, n, px, py, pz, h, eta, kappa, box, hcap, max_iter, it, fl);
+        flags |= fl;
+    }
+    iters = it;
+    return h;
+}
+
+__global__ __launch_bounds__(64) void k_h_solve(int64_t n, int64_t ng, Tree T, int depth,
+                                                const double *__restrict__ xs, double eta,
+                                                double kappa, double box, double *__restrict__ h,
+                                                int32_t max_iter, int32_t *__restrict__ iters,
+                                                int32_t *__restrict__ status) {
+    __shared__ Candidates<false> B;
+    __shared__ double list[kPts][kHList];
+    const int64_t g = xcd_block(ng);
+    if (g >= ng) return;
+    const int lane = threadIdx.x;
+    const int64_t i = g * kPts + (lane >> 3);
+    const bool on = i < n;
+    const int64_t ic = on ? i : n - 1;
     int32_t it = 0, fl = 0;
     bool ovf = false;
-    double hcap = 0.5 * box / kappa;
-    double hv = h_solve_point(T, xs, n, xs[3 * i], xs[3 * i + 1], xs[3 * i + 2],
-                              fmin(h[i], 0.5 * hcap), eta, kappa, box, hcap,
-                              cap > 0 ? list + i : nullptr, cap, max_iter, it, fl, ovf);
-    h[i] = hv;
-    iters[i] = it | (ovf ? kIterOverflow : 0);
-    if (fl) atomicOr(status, fl);
+    const double hv = h_solve_wave(T, depth, xs, n, on, xs[3 * ic], xs[3 * ic + 1], xs[3 * ic + 2],
+                                   fmin(h[ic], 0.25 * box / kappa), eta, kappa, box, max_iter, B,
+                                   list, it, fl, ovf);
+    if (on && (lane & 7) == 0) {
+        h[i] = hv;
+        iters[i] = it | (ovf ? kIterOverflow : 0);
+        if (fl) atomicOr(status, fl);
+    }
 }
 
 __global__ void k_scale(int64_t n, const double *__restrict__ a, double s, double *__restrict__ b) {
@@ -316,45 +588,93 @@ __global__ void k_scale(int64_t n, const double *__restrict__ a, double s, doubl
 // ---------------------------------------------------------------------------
 // Neighbour lists N(i) = { j != i : r_ij < max(H_i, H_j) }: a pair exchanges
 // flux whenever one of the two kernels reaches the other particle (then
-// A_ij != 0).  The tree is opened when the node is within max(H_i, Hmax_node).
-// The count pass also keeps, while they fit in cap entries, the neighbours it
-// accepts in walk order (list[k n + i], a scatter neighbour with the sign bit
-// set); the fill pass then places them from that list, gather neighbours first,
-// in the order its own walk would, and walks only for the particles whose
-// list overflowed.
-template <bool FILL>
-__global__ void k_neighbours(int64_t n, Tree T, const double *__restrict__ xs,
-                             const double *__restrict__ H, double box,
-                             int32_t *__restrict__ n_nbr, int32_t *__restrict__ n_gath,
-                             const int64_t *__restrict__ wave_base, int32_t *__restrict__ nbr,
-                             int32_t *__restrict__ list, int cap) {
+// A_ij != 0).  The count pass (one wave for 8 particles, wave_gather) keeps
+// the neighbours it accepts, in index order, in a row of cap entries per
+// particle: the gather neighbours (r < H_i) from its front, the others from
+// its back.  The fill pass copies the rows into the table's columns and walks
+// the tree itself only for the particles with more than cap neighbours.
+__global__ __launch_bounds__(64) void k_neighbours_count(int64_t n, int64_t ng, Tree T, int depth,
+                                                         const double *__restrict__ xs,
+                                                         const double *__restrict__ H, double box,
+                                                         int32_t *__restrict__ n_nbr,
+                                                         int32_t *__restrict__ n_gath,
+                                                         int32_t *__restrict__ list, int cap) {
+    __shared__ Candidates<true> B;
+    const int64_t g = xcd_block(ng);
+    if (g >= ng) return;
+    const int lane = threadIdx.x, c = lane & 7;
+    const int64_t i = g * kPts + (lane >> 3);
+    const bool on = i < n;
+    const int64_t ic = on ? i : n - 1;
+    const double ibox = 1.0 / box;
+    const double px = xs[3 * ic], py = xs[3 * ic + 1], pz = xs[3 * ic + 2];
+    const double Hi = H[ic], Hi2 = Hi * Hi;
+    int32_t *row = list + ic * cap;
+    int32_t cg = 0, cs = 0;
+    wave_gather<true>(T, depth, xs, H, n, box, px, py, pz, on ? Hi : -1.0, B, [&](int m) {
+        for (int s = 0; s < m; s += 8) {
+            const int q = s + c;
+            bool near = false, far = false;
+            int32_t j = -1;
+            if (on && q < m) {
+                j = B.j[q];
+                const double sx = min_image(B.x[q] - px, box, ibox);
+                const double sy = min_image(B.y[q] - py, box, ibox);
+                const double sz = min_image(B.z[q] - pz, box, ibox);
+                const double r2 = sx * sx + sy * sy + sz * sz;
+                const double Hj = B.H[q];
+                near = j != (int32_t)i && r2 < Hi2;
+                far = j != (int32_t)i && !near && r2 < Hj * Hj;
+            }
+            const uint32_t sg = (uint32_t)(__ballot(near) >> (lane & 56)) & 0xff;
+            const uint32_t ss = (uint32_t)(__ballot(far) >> (lane & 56)) & 0xff;
+            const int kg = cg + __popc(sg & ((1u << c) - 1));
+            const int ks = cs + __popc(ss & ((1u << c) - 1));
+            // (entries that would meet from both ends are not read: the fill
+            // pass walks for a particle with more than cap neighbours)
+            if (near && kg < cap) row[kg] = j;
+            if (far && ks < cap) row[cap - 1 - ks] = j;
+            cg += __popc(sg);
+            cs += __popc(ss);
+        }
+    });
+    if (on && c == 0) {
+        n_nbr[i] = cg + cs;
+        n_gath[i] = cg;
+    }
+}
+
+__global__ void k_neighbours_fill(int64_t n, Tree T, const double *__restrict__ xs,
+                                  const double *__restrict__ H, double box,
+                                  const int32_t *__restrict__ n_nbr,
+                                  const int32_t *__restrict__ n_gath,
+                                  const int64_t *__restrict__ wave_base, int32_t *__restrict__ nbr,
+                                  const int32_t *__restrict__ list, int cap) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    const int64_t base = wave_base[i >> 6] + (i & 63);
+    const int32_t gcount = n_gath[i], scount = n_nbr[i] - gcount;
+    if (gcount + scount <= cap) {
+        const int32_t *row = list + i * cap;
+        // full-length rows start on 16-byte boundaries
+        int32_t k = 0;
+        if (cap == kNList)
+            for (; k + 4 <= gcount; k += 4) {
+                const int4 v = *reinterpret_cast<const int4 *>(row + k);
+                nbr[base + 64 * (int64_t)k] = v.x;
+                nbr[base + 64 * (int64_t)(k + 1)] = v.y;
+                nbr[base + 64 * (int64_t)(k + 2)] = v.z;
+                nbr[base + 64 * (int64_t)(k + 3)] = v.w;
+            }
+        for (; k < gcount; ++k) nbr[base + 64 * (int64_t)k] = row[k];
+        for (int32_t k = 0; k < scount; ++k)
+            nbr[base + 64 * (int64_t)(gcount + k)] = row[cap - 1 - k];
+        return;
+    }
     const double ibox = 1.0 / box;
     const double px = xs[3 * i], py = xs[3 * i + 1], pz = xs[3 * i + 2];
     const double Hi = H[i], Hi2 = Hi * Hi;
     int32_t cg = 0, cs = 0;
-    int64_t base = 0;
-    int32_t gcount = 0, scount = 0;
-    if (FILL) {
-        base = wave_base[i >> 6] + (i & 63);
-        gcount = n_gath[i];
-        scount = n_nbr[i] - gcount;
-        if (gcount + scount <= cap) {
-            int32_t a = 0, b = 0;
-            for (int32_t k = 0; k < gcount + scount; ++k) {
-                const int32_t v = list[(int64_t)k * n + i];
-                if (v >= 0) {
-                    if (a < gcount) nbr[base + 64 * (int64_t)a] = v;
-                    ++a;
-                } else {
-                    if (b < scount) nbr[base + 64 * (int64_t)(gcount + b)] = v & 0x7fffffff;
-                    ++b;
-                }
-            }
-            return;
-        }
-    }
     traverse(
         T.P,
         [&](int64_t v) {
@@ -370,24 +690,17 @@ __global__ void k_neighbours(int64_t n, Tree T, const double *__restrict__ xs,
                 double sz = min_image(xs[3 * j + 2] - pz, box, ibox);
                 double r2 = sx * sx + sy * sy + sz * sz;
                 double Hj = H[j];
-                // the fill pass repeats the count pass exactly; the bounds only
-                // keep a lane inside its own column of the wave's slice
+                // the same pairs as the count pass; the bounds only keep a
+                // lane inside its own column of the wave's slice
                 if (r2 < Hi2) {
-                    if (FILL && cg < gcount) nbr[base + 64 * (int64_t)cg] = (int32_t)j;
-                    if (!FILL && cg + cs < cap) list[(int64_t)(cg + cs) * n + i] = (int32_t)j;
+                    if (cg < gcount) nbr[base + 64 * (int64_t)cg] = (int32_t)j;
                     ++cg;
                 } else if (r2 < Hj * Hj) {
-                    if (FILL && cs < scount) nbr[base + 64 * (int64_t)(gcount + cs)] = (int32_t)j;
-                    if (!FILL && cg + cs < cap)
-                        list[(int64_t)(cg + cs) * n + i] = (int32_t)j | INT32_MIN;
+                    if (cs < scount) nbr[base + 64 * (int64_t)(gcount + cs)] = (int32_t)j;
                     ++cs;
                 }
             }
         });
-    if (!FILL) {
-        n_nbr[i] = cg + cs;
-        n_gath[i] = cg;
-    }
 }
 
 __global__ void k_wave_width(int64_t n, int64_t nwaves, const int32_t *__restrict__ n_nbr,
@@ -526,73 +839,110 @@ __global__ void k_copy_dt(const double *__restrict__ a, double *__restrict__ b) 
 //   octant a(g) from the signs of x_g - x_s (components >= 0 count as +),
 //   w_a = sum_{g in a} psi_sg,  mu_a = sum_b w_b / (q_nz w_a),
 //   xi_sg = mu_a psi_sg   (eq:isotropy-correction-with-zero).
-__global__ void k_src_h(int32_t S, Tree T, const double *__restrict__ xs, int64_t n,
-                        const double *__restrict__ src_x, double eta, double kappa, double box,
-                        double h0, int32_t max_iter, double *__restrict__ src_h,
-                        int32_t *__restrict__ status) {
-    int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
+// One wave per source (h of the gas particle nearest in Morton order as the
+// start): with one thread per source the walks' latency made this the longest
+// kernel of a clustered build (11.3 ms for 64 sources among 58 thousand
+// particles).
+__global__ __launch_bounds__(64) void k_src_h(int32_t S, Tree T, int depth,
+                                              const double *__restrict__ xs, int64_t n,
+                                              const uint64_t *__restrict__ keys,
+                                              const double *__restrict__ geo,
+                                              const double *__restrict__ src_x, double eta,
+                                              double kappa, double box, int32_t max_iter,
+                                              double *__restrict__ src_h,
+                                              int32_t *__restrict__ status) {
+    __shared__ Candidates<false> B;
+    __shared__ double list[kPts][kHList];
+    const int32_t s = blockIdx.x;
+    const double px = src_x[3 * s], py = src_x[3 * s + 1], pz = src_x[3 * s + 2];
+    const uint64_t key = morton_key(px, py, pz, 1.0 / box);
+    int64_t lo = 0, hi = n - 1;                 // first particle with keys[i] >= key
+    while (lo < hi) {
+        const int64_t m = (lo + hi) >> 1;
+        if (keys[m] < key) lo = m + 1;
+        else hi = m;
+    }
     int32_t it = 0, fl = 0;
     bool ovf = false;
-    double hcap = 0.5 * box / kappa;
-    src_h[s] = h_solve_point(T, xs, n, src_x[3 * s], src_x[3 * s + 1], src_x[3 * s + 2], h0,
-                             eta, kappa, box, hcap, nullptr, 0, max_iter, it, fl, ovf);
-    if (fl) atomicOr(status, fl);
+    const double hv = h_solve_wave(T, depth, xs, n, threadIdx.x < 8, px, py, pz,
+                                   fmin(geo[(int64_t)kRec * lo + R_H], 0.25 * box / kappa), eta,
+                                   kappa, box, max_iter, B, list, it, fl, ovf);
+    if (threadIdx.x == 0) {
+        src_h[s] = hv;
+        if (fl) atomicOr(status, fl);
+    }
 }
 
+// Gas particles within H_s of each source (cnt), or with FILL their indices,
+// injection weights xi and coefficients xi / V; one wave per source.
 template <bool FILL>
-__global__ void k_src_gas(int32_t S, Tree T, const double *__restrict__ xs, int64_t n,
-                          const double *__restrict__ src_x, const double *__restrict__ src_h,
-                          double kappa, double box, const double *__restrict__ geo,
-                          int32_t *__restrict__ cnt, const int32_t *__restrict__ ptr,
-                          int32_t *__restrict__ gas, double *__restrict__ xi,
-                          double *__restrict__ coef) {
-    int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
+__global__ __launch_bounds__(64) void k_src_gas(int32_t S, Tree T, int depth,
+                                                const double *__restrict__ xs, int64_t n,
+                                                const double *__restrict__ src_x,
+                                                const double *__restrict__ src_h, double kappa,
+                                                double box, const double *__restrict__ geo,
+                                                int32_t *__restrict__ cnt,
+                                                const int32_t *__restrict__ ptr,
+                                                int32_t *__restrict__ gas, double *__restrict__ xi,
+                                                double *__restrict__ coef) {
+    __shared__ Candidates<false> B;
+    const int32_t s = blockIdx.x;
+    const int lane = threadIdx.x;
     const double ibox = 1.0 / box;
     const double px = src_x[3 * s], py = src_x[3 * s + 1], pz = src_x[3 * s + 2];
     const double H = kappa * src_h[s], H2 = H * H, iH = 1.0 / H;
     int32_t c = 0;
-    int32_t o = FILL ? ptr[s] : 0;
-    int32_t cap = FILL ? ptr[s + 1] - ptr[s] : 0;
+    const int32_t o = FILL ? ptr[s] : 0;
+    const int32_t cap = FILL ? ptr[s + 1] - ptr[s] : 0;
     double wa[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    traverse(
-        T.P,
-        [&](int64_t v) {
-            return box_dist2(T.lo + 3 * v, T.hi + 3 * v, px, py, pz, box) < H2 * (1.0 + 1e-12);
-        },
-        [&](int64_t l) {
-            int64_t j0 = l * kLeaf, j1 = min(n, j0 + kLeaf);
-            for (int64_t j = j0; j < j1; ++j) {
-                double sx = min_image(xs[3 * j] - px, box, ibox);
-                double sy = min_image(xs[3 * j + 1] - py, box, ibox);
-                double sz = min_image(xs[3 * j + 2] - pz, box, ibox);
-                double r2 = sx * sx + sy * sy + sz * sz;
-                if (r2 < H2) {
-                    if (FILL && c < cap) {
-                        double w = kern_w(sqrt(r2) * iH);
-                        int oc = (sx >= 0.0) | ((sy >= 0.0) << 1) | ((sz >= 0.0) << 2);
-                        gas[o + c] = (int32_t)j;
-                        xi[o + c] = w;
-                        coef[o + c] = (double)oc;   // octant, replaced below
-                        wa[oc] += w;
-                    }
-                    ++c;
-                }
+    wave_gather<false>(T, depth, xs, nullptr, n, box, px, py, pz, lane < 8 ? H : -1.0, B,
+                       [&](int m) {
+        // a candidate a lane
+        bool hit = false;
+        double sx = 0.0, sy = 0.0, sz = 0.0, r2 = 0.0;
+        if (lane < m) {
+            sx = min_image(B.x[lane] - px, box, ibox);
+            sy = min_image(B.y[lane] - py, box, ibox);
+            sz = min_image(B.z[lane] - pz, box, ibox);
+            r2 = sx * sx + sy * sy + sz * sz;
+            hit = r2 < H2;
+        }
+        const uint64_t hits = __ballot(hit);
+        if (FILL && hit) {
+            const int32_t e = c + __popcll(hits & ((uint64_t(1) << lane) - 1));
+            if (e < cap) {
+                const double w = kern_w(sqrt(r2) * iH);
+                const int oc = (sx >= 0.0) | ((sy >= 0.0) << 1) | ((sz >= 0.0) << 2);
+                gas[o + e] = B.j[lane];
+                xi[o + e] = w;
+                coef[o + e] = (double)oc;   // octant, replaced below
+#pragma unroll
+                for (int a = 0; a < 8; ++a) wa[a] += a == oc ? w : 0.0;
             }
-        });
+        }
+        c += __popcll(hits);
+    });
     if (!FILL) {
-        cnt[s] = c;
+        if (lane == 0) cnt[s] = c;
         return;
     }
     int qnz = 0;
-    for (int a = 0; a < 8; ++a) qnz += wa[a] > 0.0;
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) wa[a] += __shfl_xor(wa[a], d, 64);
+        qnz += wa[a] > 0.0;
+    }
     // xi_sg = mu_a psi_sg with psi_sg = w_sg / wsum and w_a in units of wsum:
     // mu_a psi_sg = (wsum / (q_nz wa_a)) (w_sg / wsum) = w_sg / (q_nz wa_a)
     if (c > cap) c = cap;
-    for (int32_t e = 0; e < c; ++e) {
-        int oc = (int)coef[o + e];
-        double x_ = xi[o + e] > 0.0 ? xi[o + e] / ((double)qnz * wa[oc]) : 0.0;
+    __syncthreads();                            // the entries are other lanes' writes
+    for (int32_t e = lane; e < c; e += 64) {
+        const int oc = (int)coef[o + e];
+        double wo = 0.0;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) wo = a == oc ? wa[a] : wo;
+        const double x_ = xi[o + e] > 0.0 ? xi[o + e] / ((double)qnz * wo) : 0.0;
         xi[o + e] = x_;
         coef[o + e] = x_ / geo[(int64_t)kRec * gas[o + e] + R_V];
     }
@@ -865,6 +1215,12 @@ inline unsigned nblk(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) 
 // ---------------------------------------------------------------------------
 // host side
 
+static int tree_depth(const rt_ctx *ctx) {
+    int d = 0;
+    while ((int64_t(1) << d) < ctx->P) ++d;
+    return d;
+}
+
 static void build_tree(rt_ctx *ctx, const double *H) {
     int64_t P = ctx->P;
     k_leaf_boxes<<<nblk(P), kBlock, 0, ctx->stream>>>(ctx->p.n, ctx->nleaf, P, ctx->xs, H,
@@ -1022,30 +1378,17 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
         // tree on positions; smoothing lengths
         build_tree(ctx, nullptr);
         Tree T{ctx->node_lo, ctx->node_hi, ctx->node_hmax, ctx->P};
+        const int depth = tree_depth(ctx);
+        const int64_t n8 = (n + kPts - 1) / kPts;   // waves of the searches
         RT_HIP(hipMemsetAsync(ctx->status, 0, sizeof(int32_t), st));
         RT_HIP(hipMemsetAsync(ctx->h_iters, 0, sizeof(int32_t) * n, st));
         if (!h_in) {
-            // candidate lists of kHList entries per particle while they fit in
-            // kHListBytes (else every evaluation walks the tree)
-            int cap = (int)std::min<int64_t>(kHList, kHListBytes / (8 * n));
-            double *hlist = nullptr;
-            if (cap < kHList / 2 || !rt_try_alloc(ctx, (void **)&hlist, sizeof(double) * cap * n)) {
-                hlist = nullptr;
-                cap = 0;
-            }
             k_h_guess<<<nblk(n), kBlock, 0, st>>>(n, ctx->P, ctx->node_lo, ctx->node_hi,
                                                   ctx->xs, ctx->p.eta, ctx->p.box, h);
-            k_h_solve<<<nblk(n), kBlock, 0, st>>>(n, T, ctx->xs, ctx->p.eta, ctx->p.kappa,
-                                                  ctx->p.box, h, hlist, cap, ctx->h_iter_cap,
-                                                  ctx->h_iters, ctx->status);
-            if (hlist) {
-                const hipError_t e = hipStreamSynchronize(st);
-                rt_free(ctx, hlist);
-                if (e != hipSuccess) {
-                    rs = rt_fail(ctx, RT_EHIP, std::string("smoothing-length solve: ") + hipGetErrorString(e));
-                    goto fail;
-                }
-            }
+            k_h_solve<<<(unsigned)xcd_grid(n8), 64, 0, st>>>(n, n8, T, depth, ctx->xs, ctx->p.eta,
+                                                             ctx->p.kappa, ctx->p.box, h,
+                                                             ctx->h_iter_cap, ctx->h_iters,
+                                                             ctx->status);
         }
         k_scale<<<nblk(n), kBlock, 0, st>>>(n, h, ctx->p.kappa, Htmp);
         int32_t stw = 0;
@@ -1066,14 +1409,14 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
             }
         }
         // neighbour table: counts, wave widths, offsets, fill
-        ncap = (int)std::min<int64_t>(kNList, kHListBytes / (4 * n));
+        ncap = (int)std::min<int64_t>(kNList, kNListBytes / (4 * n));
         if (ncap < kNList / 2 || !rt_try_alloc(ctx, (void **)&nlist, sizeof(int32_t) * ncap * n)) {
             nlist = nullptr;
             ncap = 0;
         }
-        k_neighbours<false><<<nblk(n), kBlock, 0, st>>>(n, T, ctx->xs, Htmp, ctx->p.box,
-                                                        ctx->n_nbr, ctx->n_gath, nullptr, nullptr,
-                                                        nlist, ncap);
+        k_neighbours_count<<<(unsigned)xcd_grid(n8), 64, 0, st>>>(n, n8, T, depth, ctx->xs, Htmp,
+                                                                  ctx->p.box, ctx->n_nbr,
+                                                                  ctx->n_gath, nlist, ncap);
         k_wave_width<<<nblk(ctx->nwaves + 1), kBlock, 0, st>>>(n, ctx->nwaves, ctx->n_nbr, width);
         size_t scan_bytes = 0;
         if (rocprim::exclusive_scan(nullptr, scan_bytes, width, ctx->wave_base,
@@ -1099,9 +1442,9 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
         RT_HIP(hipStreamSynchronize(st));
         ALLOC(ctx->nbr, sizeof(int32_t) * std::max<int64_t>(ctx->slots, 1));
         RT_HIP(hipMemsetAsync(ctx->nbr, 0xff, sizeof(int32_t) * std::max<int64_t>(ctx->slots, 1), st));
-        k_neighbours<true><<<nblk(n), kBlock, 0, st>>>(n, T, ctx->xs, Htmp, ctx->p.box,
-                                                       ctx->n_nbr, ctx->n_gath, ctx->wave_base,
-                                                       ctx->nbr, nlist, ncap);
+        k_neighbours_fill<<<nblk(n), kBlock, 0, st>>>(n, T, ctx->xs, Htmp, ctx->p.box, ctx->n_nbr,
+                                                      ctx->n_gath, ctx->wave_base, ctx->nbr, nlist,
+                                                      ncap);
         {
             // task lists of the tile transports
             ALLOC(ctx->task, sizeof(int32_t) * std::max<int64_t>(ctx->slots, 1));
@@ -1224,14 +1567,13 @@ rt_status rt_sources_impl(rt_ctx *ctx, int32_t S, const double *xs, double eta_s
     RT_HIP(hipMemcpyAsync(sx, xs, sizeof(double) * 3 * S, hipMemcpyDeviceToDevice, st));
     RT_HIP(hipMemsetAsync(ctx->status, 0, sizeof(int32_t), st));
     {
-        // start below the mean spacing; the solver doubles h until bracketed
-        double h0 = 0.05 * eta_star * ctx->p.box / cbrt((double)n);
-        k_src_h<<<nblk(S, 64), 64, 0, st>>>(S, T, ctx->xs, n, sx, eta_star, ctx->p.kappa,
-                                           ctx->p.box, h0, ctx->h_iter_cap, ctx->src_h,
-                                           ctx->status);
-        k_src_gas<false><<<nblk(S, 64), 64, 0, st>>>(S, T, ctx->xs, n, sx, ctx->src_h,
-                                                    ctx->p.kappa, ctx->p.box, ctx->geo, cnt,
-                                                    nullptr, nullptr, nullptr, nullptr);
+        const int depth = tree_depth(ctx);
+        k_src_h<<<(unsigned)S, 64, 0, st>>>(S, T, depth, ctx->xs, n, ctx->keys, ctx->geo, sx,
+                                            eta_star, ctx->p.kappa, ctx->p.box, ctx->h_iter_cap,
+                                            ctx->src_h, ctx->status);
+        k_src_gas<false><<<(unsigned)S, 64, 0, st>>>(S, T, depth, ctx->xs, n, sx, ctx->src_h,
+                                                     ctx->p.kappa, ctx->p.box, ctx->geo, cnt,
+                                                     nullptr, nullptr, nullptr, nullptr);
         int32_t stw = 0;
         RT_HIP(hipMemcpyAsync(hc.data(), cnt, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
         RT_HIP(hipMemcpyAsync(&stw, ctx->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -1250,8 +1592,8 @@ rt_status rt_sources_impl(rt_ctx *ctx, int32_t S, const double *xs, double eta_s
         if ((rs = rt_alloc(ctx, (void **)&sxi, sizeof(double) * m)) != RT_OK) goto fail;
         RT_HIP(hipMemcpyAsync(ctx->src_ptr, hptr.data(), sizeof(int32_t) * (S + 1),
                               hipMemcpyHostToDevice, st));
-        k_src_gas<true><<<nblk(S, 64), 64, 0, st>>>(S, T, ctx->xs, n, sx, ctx->src_h, ctx->p.kappa,
-                                                   ctx->p.box, ctx->geo, nullptr, ctx->src_ptr,
+        k_src_gas<true><<<(unsigned)S, 64, 0, st>>>(S, T, tree_depth(ctx), ctx->xs, n, sx,
+                                                   ctx->src_h, ctx->p.kappa, ctx->p.box, ctx->geo, nullptr, ctx->src_ptr,
                                                    ctx->src_gas, sxi, ctx->src_coef);
         // gas-major copy for the per-step injection (deterministic gather)
         std::vector<int32_t> g(m), srcv(m);

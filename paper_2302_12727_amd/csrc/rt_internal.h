@@ -310,6 +310,13 @@ __device__ __forceinline__ int64_t xcd_block(int64_t nb) {
 }
 inline int64_t xcd_grid(int64_t nb) { return 8 * ((nb + 7) / 8); }
 
+// Order LDS traffic of one wavefront: everything before is complete and
+// visible to the other lanes of the wave before anything after is issued.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Wave-level sum of a double (all 64 lanes active or inactive lanes contributing 0).
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

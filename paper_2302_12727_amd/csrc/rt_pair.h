@@ -314,13 +314,6 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NP], double *__re
 // from LDS.  Records are padded to 17 doubles in LDS against bank conflicts.
 constexpr int kStage = 17;
 
-// Order LDS traffic of one wavefront: everything before is complete and
-// visible to the other lanes of the wave before anything after is issued.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Copy one 16-double line per lane's neighbour (line base pointers src + 16 *
 // row[m]) into the wave's stage buffer: 8 loads, each lane moving 16 bytes.
 // The load and store halves are separate so that a kernel can put several

@@ -948,6 +948,16 @@ __global__ __launch_bounds__(64) void k_src_gas(int32_t S, Tree T, int depth,
     }
 }
 
+// The value of lane l (the same l in every lane), and of a 64-bit one.
+__device__ __forceinline__ int32_t lane_value(int32_t v, int l) {
+    return __builtin_amdgcn_readlane(v, l);
+}
+__device__ __forceinline__ uint64_t lane_value64(uint64_t v, int l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Second pass of the task lists: lower the tile's longest list, which sets
 // how long the tile's block runs, by augmenting paths.  A particle k with the
 // longest list (L entries) passes one of the pairs it evaluates, (k, l), to l;
@@ -958,13 +968,15 @@ __global__ __launch_bounds__(64) void k_src_gas(int32_t S, Tree T, int depth,
 // with the longest list has such a path; each move lowers the sum of the
 // squared lengths, so the loop ends.  On the lattices this reaches the lower
 // bound, the larger of the longest list of neighbours outside the tile and
-// the mean, in all but a few tiles.  One wave (lane = particle of the tile); cnt[k]:
-// particle k's list length, bit l of own[k]: k evaluates the pair (k, l).
-__device__ void level_tasks(bool active, int lane, int32_t *cnt, uint64_t *own) {
-    __shared__ int32_t prev[64];
+// the mean, in all but a few tiles.  One wave (lane = particle of the tile);
+// c: the lane's list length, bit l of own: the lane evaluates its pair with l,
+// adj: the lane's partners in the tile.  All in registers: u evaluates the
+// pair (u, lane) when adj has u and own has not, so a lane finds the particles
+// of the frontier that can pass it a pair with two bit operations.
+__device__ __forceinline__ void level_tasks(bool active, int lane, int32_t &c, uint64_t &own,
+                                            uint64_t adj) {
     for (int guard = 0; guard < 64 * 64; ++guard) {
-        const int32_t c = active ? cnt[lane] : -1;
-        int32_t top = c;
+        int32_t top = active ? c : -1;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o, 64));
         uint64_t tops = __ballot(active && c == top);
@@ -974,39 +986,25 @@ __device__ void level_tasks(bool active, int lane, int32_t *cnt, uint64_t *own) 
             tops &= tops - 1;
             uint64_t visited = uint64_t(1) << v, frontier = visited;
             int found = -1;
+            int32_t prev = -1;                  // the lane that can pass this one a pair
             while (frontier && found < 0) {
-                // each lane not yet reached finds the lowest particle of the
-                // frontier that can pass it a pair
-                int pu = -1;
-                if (!((visited >> lane) & 1)) {
-                    for (uint64_t f = frontier; f; f &= f - 1) {
-                        const int u = __ffsll((unsigned long long)f) - 1;
-                        if ((own[u] >> lane) & 1) {
-                            pu = u;
-                            break;
-                        }
-                    }
-                }
-                if (pu >= 0) prev[lane] = pu;
-                const uint64_t disc = __ballot(pu >= 0);
-                const uint64_t good = __ballot(pu >= 0 && c <= top - 2);
+                const uint64_t from = adj & ~own & frontier;
+                const bool reach = from != 0 && !((visited >> lane) & 1);
+                if (reach) prev = __ffsll((unsigned long long)from) - 1;
+                const uint64_t disc = __ballot(reach);
+                const uint64_t good = __ballot(reach && c <= top - 2);
                 if (good) found = __ffsll((unsigned long long)good) - 1;
                 visited |= disc;
                 frontier = disc;
             }
             if (found >= 0) {
-                __syncthreads();
-                if (lane == 0) {
-                    for (int w = found; w != v;) {
-                        const int u = prev[w];
-                        own[u] &= ~(uint64_t(1) << w);
-                        own[w] |= uint64_t(1) << u;
-                        w = u;
-                    }
-                    --cnt[v];
-                    ++cnt[found];
+                for (int w = found; w != v;) {
+                    const int u = lane_value(prev, w);
+                    if (lane == u) own &= ~(uint64_t(1) << w);
+                    if (lane == w) own |= uint64_t(1) << u;
+                    w = u;
                 }
-                __syncthreads();
+                c += (lane == found) - (lane == v);
                 moved = true;
             }
         }
@@ -1028,55 +1026,65 @@ __device__ void level_tasks(bool active, int lane, int32_t *cnt, uint64_t *own) 
 // the mean wave iterations of the transport to 0.75 of the two-sided
 // kernel's (a fixed rule by index parity took them to 0.82 on the 64^3
 // lattice) and the longest list of a tile, which sets its block's time, to
-// 0.81; the leveling takes them to 0.70 and 0.69.  Same slots as the neighbour table, in table order; n_task[i]
-// entries.  Launched with one wave (64 threads) per tile.
+// 0.81; the leveling takes them to 0.70 and 0.69.  Same slots as the neighbour
+// table, in table order; n_task[i] entries.  Launched with one wave (64
+// threads) per tile.  The tile's pairs are kept as bit masks in registers and
+// handed out with scalar lane reads: with the lists read by one lane at a time
+// and the counts in LDS this was a serial chain of LDS and memory reads, 5.5 ms
+// on the 128^3 lattice and 0.51 ms on 22 thousand clustered particles; now 1.21
+// and 0.13 ms, with the same lists.
 __global__ __launch_bounds__(64) void k_tasks(int64_t n, const int64_t *__restrict__ wave_base,
                                               const int32_t *__restrict__ n_nbr,
+                                              const int32_t *__restrict__ n_gath,
                                               const int32_t *__restrict__ nbr,
                                               int32_t *__restrict__ task,
                                               int32_t *__restrict__ n_task,
                                               int64_t *__restrict__ tstat) {
-    __shared__ int32_t cnt[64];
-    __shared__ uint64_t own[64];     // bit l of own[k]: particle k evaluates pair (k, l)
+    static_assert(kTile == 64, "a tile is one column block of the neighbour table");
     const int lane = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.x * 64, i = t0 + lane;
     const bool active = i < n;
     const int64_t base = wave_base[blockIdx.x] + lane;
-    const int32_t nn = active ? n_nbr[i] : 0;
-    int32_t out = 0;
-    for (int32_t k = 0; k < nn; ++k)
-        out += nbr[base + 64 * (int64_t)k] / kTile != (int32_t)(i / kTile);
-    cnt[lane] = out;
-    own[lane] = 0;
-    __syncthreads();
-    for (int src = 0; src < 64; ++src) {
-        if (lane == src && active) {
-            int32_t ci = cnt[src];
-            uint64_t mine = 0;
-            for (int32_t k = 0; k < nn; ++k) {
-                const int32_t j = nbr[base + 64 * (int64_t)k];
-                const int jl = j - (int32_t)t0;
-                // outside the tile, or already given
-                if (jl <= src || jl >= 64 || jl / kTile != src / kTile) continue;
-                const int32_t cj = cnt[jl];
-                if (cj < ci) {
-                    cnt[jl] = cj + 1;
-                    own[jl] |= uint64_t(1) << src;
+    const int32_t nn = active ? n_nbr[i] : 0, ng = active ? n_gath[i] : 0;
+    uint64_t adjg = 0, adjs = 0;                // partners in the tile: gather ones, others
+    for (int32_t k = 0; k < nn; ++k) {
+        const int32_t jl = nbr[base + 64 * (int64_t)k] - (int32_t)t0;
+        const uint64_t bit = (uint32_t)jl < 64u ? uint64_t(1) << (jl & 63) : 0;
+        if (k < ng) adjg |= bit;
+        else adjs |= bit;
+    }
+    const uint64_t adj = adjg | adjs;
+    const int32_t out = nn - __popcll(adj);
+    int32_t c = out;
+    uint64_t own = 0;                           // bit l: this particle evaluates its pair with l
+    for (int src = 0; src < 63; ++src) {
+        int32_t ci = lane_value(c, src);
+        uint64_t mine = 0;
+        const uint64_t above = ~uint64_t(0) << (src + 1);
+#pragma unroll
+        for (int part = 0; part < 2; ++part)
+            for (uint64_t m = lane_value64(part ? adjs : adjg, src) & above; m; m &= m - 1) {
+                const int l = __ffsll((unsigned long long)m) - 1;
+                if (lane_value(c, l) < ci) {
+                    if (lane == l) {
+                        ++c;
+                        own |= uint64_t(1) << src;
+                    }
                 } else {
                     ++ci;
-                    mine |= uint64_t(1) << jl;
+                    mine |= uint64_t(1) << l;
                 }
             }
-            cnt[src] = ci;
-            own[src] |= mine;
+        if (lane == src) {
+            c = ci;
+            own |= mine;
         }
-        __syncthreads();
     }
-    level_tasks(active, lane, cnt, own);
+    level_tasks(active, lane, c, own, adj);
     {
         // the tile's longest list and its lower bound: the longest list of
         // neighbours outside the tile, or the mean length rounded up
-        int32_t lm = active ? cnt[lane] : 0, om = out, sm = lm, na = active ? 1 : 0;
+        int32_t lm = active ? c : 0, om = out, sm = lm, na = active ? 1 : 0;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             lm = max(lm, __shfl_xor(lm, o, 64));
@@ -1091,19 +1099,18 @@ __global__ __launch_bounds__(64) void k_tasks(int64_t n, const int64_t *__restri
         }
     }
     if (!active) return;
-    const uint64_t mine = own[lane];
-    int32_t c = 0;
+    int32_t o = 0;
     for (int32_t k = 0; k < nn; ++k) {
         int32_t j = nbr[base + 64 * (int64_t)k];
-        const int jl = j - (int32_t)t0;
-        if (jl >= 0 && jl < 64 && jl / kTile == lane / kTile) {
-            if (!((mine >> jl) & 1)) continue;
+        const int32_t jl = j - (int32_t)t0;
+        if ((uint32_t)jl < 64u) {
+            if (!((own >> jl) & 1)) continue;
             j |= int32_t(0x80000000u);
         }
-        task[base + 64 * (int64_t)c] = j;
-        ++c;
+        task[base + 64 * (int64_t)o] = j;
+        ++o;
     }
-    n_task[i] = c;
+    n_task[i] = o;
 }
 
 // Neighbour unions of the gradient (k_gradient64u, k_gradient32u; over the
@@ -1451,8 +1458,9 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
             ALLOC(ctx->n_task, sizeof(int32_t) * n);
             ALLOC(ctx->tstat, 2 * sizeof(int64_t));
             RT_HIP(hipMemsetAsync(ctx->tstat, 0, 2 * sizeof(int64_t), st));
-            k_tasks<<<(unsigned)ctx->nwaves, 64, 0, st>>>(n, ctx->wave_base, ctx->n_nbr, ctx->nbr,
-                                                          ctx->task, ctx->n_task, ctx->tstat);
+            k_tasks<<<(unsigned)ctx->nwaves, 64, 0, st>>>(n, ctx->wave_base, ctx->n_nbr, ctx->n_gath,
+                                                          ctx->nbr, ctx->task, ctx->n_task,
+                                                          ctx->tstat);
         }
         {
             // neighbour unions of the gradient (gather lists): FP64 at the

@@ -14,36 +14,6 @@ namespace {
 
 inline unsigned nblk(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) / b); }
 
-// FP64 transport with the GLF solver: the particle's own state and gradients
-// in LDS instead of registers (OWN), which frees the registers to hold the
-// next stage's neighbour lines in flight while the current stage is computed
-// (PIPE).  The HLL instantiations keep both off: they run 3 waves per SIMD
-// at 168 registers, which the in-flight lines would not fit.
-#ifndef RT_TRANSPORT_OWN_LDS
-#define RT_TRANSPORT_OWN_LDS 1
-#endif
-#ifndef RT_TRANSPORT_PIPE
-#define RT_TRANSPORT_PIPE 1
-#endif
-constexpr bool kOwnL = RT_TRANSPORT_OWN_LDS != 0;
-constexpr bool kPipe = RT_TRANSPORT_PIPE != 0;
-// GLF with the Hopkins surfaces keeps its own state and gradients in
-// registers and loads each stage just before it (256 VGPRs, 5 spilled): since
-// the inner loop was trimmed to 731 VALU instructions per slot, this form
-// saves the 24 KB of LDS reads of the own state per wave-iteration and ran
-// 4% faster than the LDS-resident pipelined one (4.10 against 4.27-4.29 ms
-// on the 3-group 128^3 lattice, same box).  The Ivanova and HLL forms keep
-// the LDS-resident own state (their register forms spill more).
-#ifndef RT_TRANSPORT_GLF_REGS
-#define RT_TRANSPORT_GLF_REGS 1
-#endif
-constexpr bool own_lds(bool hll, bool iva, int w) {
-    return (hll || iva) ? (kOwnL && (!hll || w > 1)) : (kOwnL && RT_TRANSPORT_GLF_REGS == 0);
-}
-constexpr bool pipe_on(bool hll, bool iva, int w) {
-    return (hll || iva) ? (kPipe && (!hll || w > 1)) : (kPipe && RT_TRANSPORT_GLF_REGS == 0);
-}
-
 // ---------------------------------------------------------------------------
 // Injection: E_g += dt sum_s xi_sg L_s / V_g, one thread per receiving particle.
 template <typename T>
@@ -554,364 +524,9 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
     gradient_record_part<G>(sg, u, rec, UD + ic * (16 * G), sub, status);
 }
 
-// Transport (eq:transport-update-explicit with the GLF flux eq:riemann-GLF).
-// A wave owns 64 particles and GW of the G photon groups (G/GW waves share
-// the same particles): fewer groups per wave keep less state in registers
-// and so more waves resident, at the price of recomputing the pair geometry
-// once per group slice.
-// The compiler is held to the 256 registers of 2 waves per SIMD (at 1 wave
-// per SIMD the kernel runs 1.6x slower).
-//
-// OWNL: the particle's own state and gradients (48 doubles at 3 groups) are
-// read from the block's LDS instead of being held in registers.  PIPE: with
-// the registers this frees, each stage's neighbour lines are loaded one stage
-// ahead (the next group's lines while a group is computed; the next
-// iteration's geometry and first group lines while the last group is), so no
-// stage waits for its own loads.  Measured on the 3-group 128^3 lattice: 2%
-// faster with the Hopkins surfaces, 9% with the Ivanova ones (whose
-// register-held form spilled).
-//
-// HLL: the HLL solver (eq:riemann-HLL) with the wave-speed table hll in
-// place of GLF.
-//
-// BIN: one tick of the individual-time-step scheme (time bins in slot 12 of
-// the geometry records, the smallest bin of each particle's neighbourhood in
-// binm): only pairs whose smaller bin ends a step in this tick contribute,
-// each with dt 2^min(b_k, b_l); the sums go to the pending flux sums accm, and
-// the particles that end a step apply and clear theirs (Part III
-// eq:transport-update-explicit with min{dt_k, dt_l}).
-// With one group per wave the HLL instantiation fits 3 waves per SIMD (168
-// registers), measured 4% faster than 2 (the GLF one is slower there).
-template <int G, int GW, bool BIN = false, bool HLL = false, bool IVA = false, int Q = 1,
-          bool OWNL = false, bool PIPE = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    (HLL && GW == 1 && !OWNL) ? 3 : 2, (HLL && GW == 1 && !OWNL) ? 3 : 2))) void k_transport64(
-    int64_t n, int64_t nb, const double *__restrict__ geo, const int32_t *__restrict__ nbr,
-    const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_nbr,
-    const double *__restrict__ UD, const double *__restrict__ dtp, double c, double box,
-    double *__restrict__ Uout, double *__restrict__ partials,
-    unsigned long long *__restrict__ counts, double *__restrict__ Uung,
-    int32_t *__restrict__ status, int64_t tick = 0, double *__restrict__ accm = nullptr,
-    const double2 *__restrict__ hll = nullptr, const uint8_t *__restrict__ binm = nullptr) {
-    static_assert(G % GW == 0, "group slices must tile the groups");
-    static_assert(Q == 1 || Q == 2 || Q == 4, "lanes per particle: 1, 2 or 4");
-    constexpr int NS = G / GW, NQ = 4 * G;
-    constexpr int PW = 64 / Q, PB = kBlock / Q;   // particles per wave, per block
-    constexpr int OS = 16 * GW + 1;               // own record in LDS (padded, doubles)
-    __shared__ double stage[kBlock / 64][64 * kStage];
-    __shared__ double own[OWNL ? PB * OS : 1];
-    __shared__ double smem[(kBlock / 64) * 2 * GW];
-    __shared__ unsigned long long scnt[4];
-    const int64_t bg = xcd_block(nb * NS);
-    if (bg >= nb * NS) return;                  // whole block: no barrier is skipped
-    const int64_t blk = bg / NS;
-    const int g0 = (int)(bg - blk * NS) * GW;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // Q lanes share a particle, each taking every Q-th of its neighbour slots
-    const int sub = lane % Q;
-    const int64_t i0 = blk * PB + wv * PW;      // first particle of the wave
-    const int64_t i = i0 + lane / Q;
-    const bool active = i < n;
-    const bool owner = active && sub == 0;      // writes the particle's results
-    const int64_t ic = active ? i : n - 1;      // in-range index for inactive lanes
-    const int64_t w = i0 >> 6;                  // neighbour-table wave (PW divides 64)
-    const bool wave_live = i0 < n;              // wave-uniform
-    const double ibox = 1.0 / box, hc = 0.5 * c, c3 = 3.0 * c;
-    if (threadIdx.x < 4) scnt[threadIdx.x] = 0;
-    double *sb = stage[wv];
-
-    // own particle: geometry record, state and gradients (registers, or with
-    // OWNL the wave's LDS, each lane of the particle copying every Q-th value)
-    const double *rk = geo + (int64_t)kRec * ic;
-    double Ui[OWNL ? 1 : 4 * GW], Di[OWNL ? 1 : 12 * GW];
-    double *ow = own + (OWNL ? (threadIdx.x / Q) * OS : 0);
-    if constexpr (OWNL) {
-#pragma unroll
-        for (int e = sub; e < 16 * GW; e += Q) ow[e] = UD[(ic * G + g0 + (e >> 4)) * 16 + (e & 15)];
-        wave_lds_sync();
-    } else {
-#pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            const double *r = UD + (ic * G + g0 + g) * 16;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                Ui[4 * g + m] = r[m];
-                Di[3 * (4 * g + m) + 0] = r[4 + 3 * m];
-                Di[3 * (4 * g + m) + 1] = r[5 + 3 * m];
-                Di[3 * (4 * g + m) + 2] = r[6 + 3 * m];
-            }
-        }
-    }
-    // q = 4 g + m: the state value, and its gradient component a
-    auto ui = [&](int q) -> double {
-        if constexpr (OWNL) return ow[16 * (q >> 2) + (q & 3)];
-        else return Ui[q];
-    };
-    auto di = [&](int q, int a) -> double {
-        if constexpr (OWNL) return ow[16 * (q >> 2) + 4 + 3 * (q & 3) + a];
-        else return Di[3 * q + a];
-    };
-    double acc[4 * GW];
-#pragma unroll
-    for (int q = 0; q < 4 * GW; ++q) acc[q] = 0.0;
-    int cE = 0, cF = 0;
-    double gk[3] = {0.0, 0.0, 0.0};   // IVA: own kernel-gradient sum (record slots 13-15)
-    if (IVA) {
-        gk[0] = rk[13];
-        gk[1] = rk[14];
-        gk[2] = rk[15];
-    }
-    // time bins: this particle ends a step in this tick (ends), or some pair of
-    // its neighbourhood does (touched); binm: the smallest bin of each
-    // neighbourhood (none before rt_time_bins: every bin is 0)
-    const int64_t t1 = tick + 1;
-    const int32_t bk = BIN ? (int32_t)rk[12] : 0;
-    const bool ends = !BIN || (t1 & ((int64_t(1) << bk) - 1)) == 0;
-    const int32_t bm = (BIN && binm) ? (int32_t)binm[ic] : 0;
-    const bool touched = !BIN || (t1 & ((int64_t(1) << bm) - 1)) == 0;
-
-    if (wave_live) {
-        const int64_t base = wave_base[w] + (i & 63);
-        int32_t kmax = (int32_t)((wave_base[w + 1] - wave_base[w]) >> 6);
-        const int32_t nn = (active && touched) ? n_nbr[i] : 0;
-        if (Q > 1) {                            // the longest list of this wave's particles
-            kmax = nn;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, 64));
-        }
-        if (BIN && __ballot(nn > 0) == 0) kmax = 0;   // no due pair in this wave
-        // the neighbour index of the next iteration is loaded one iteration
-        // ahead, so its latency overlaps this iteration's record loads
-        int32_t jn = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
-        // PIPE: while a stage computes, the lines of the next group (pb), or
-        // of the next iteration's geometry (pa) and first group (pb), are in
-        // flight in registers
-        double2 pa[PIPE ? 8 : 1], pb[PIPE ? 8 : 1];
-        // pointers to this lane's pieces of the gradient-record lines of the 8
-        // neighbour rows it helps to move (PIPE: the rows of the stage in
-        // flight, replaced when the next iteration's are loaded)
-        const double *udp[8];
-        if constexpr (PIPE) {
-            if (kmax > 0) {
-                int32_t rn[8];
-                const double *gp[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) rn[m] = __shfl(jn, 8 * m + (lane >> 3), 64);
-                row_ptrs(geo, rn, 1, 0, lane, gp);
-                row_ptrs(UD, rn, G, g0, lane, udp);
-                load_at(gp, 0, *reinterpret_cast<double2(*)[8]>(pa));
-                load_at(udp, 0, *reinterpret_cast<double2(*)[8]>(pb));
-            }
-        }
-        for (int32_t kk = 0; kk < kmax; kk += Q) {
-            const int32_t k = kk + sub;
-            const bool valid = k < nn;
-            const int32_t j = jn;
-            jn = k + Q < nn ? nbr[base + 64 * (int64_t)(k + Q)] : (int32_t)ic;
-            // pair geometry from the staged geometry records
-            if constexpr (PIPE) {
-                store_lines(*reinterpret_cast<double2(*)[8]>(pa), sb, lane);
-            } else {
-                int32_t rw[8];
-                const double *gp[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) rw[m] = __shfl(j, 8 * m + (lane >> 3), 64);
-                row_ptrs(geo, rw, 1, 0, lane, gp);
-                row_ptrs(UD, rw, G, g0, lane, udp);
-                double2 v[8];
-                load_at(gp, 0, v);
-                store_lines(v, sb, lane);
-            }
-            double rl[12];
-#pragma unroll
-            for (int q = 0; q < 12; ++q) rl[q] = sb[lane * kStage + q];
-            // the neighbour's time bin (slot 12 of its record)
-            const int32_t bl = BIN ? (int32_t)sb[lane * kStage + 12] : 0;
-            PairGeo pg;
-            if (IVA) {
-                // its kernel-gradient sum: slots 13-15 of the same record
-                const double gl[3] = {sb[lane * kStage + 13], sb[lane * kStage + 14],
-                                      sb[lane * kStage + 15]};
-                pair_geometry_ivanova64(rk, rl, gk, gl, box, ibox, pg);
-            } else {
-                pair_geometry64(rk, rl, box, ibox, pg);
-            }
-            bool use = valid && pg.An > 0.0;
-            double wkl = 1.0;                   // time integration of this exchange
-            if (BIN) {
-                const int32_t bmin = bk < bl ? bk : bl;
-                use = use && (t1 & ((int64_t(1) << bmin) - 1)) == 0;
-                wkl = ldexp(dtp[0], bmin);
-            }
-            const double iAn = (HLL && pg.An > 0.0) ? rcp64(pg.An) : 0.0;
-#pragma unroll
-            for (int g = 0; g < GW; ++g) {
-                if constexpr (PIPE) {
-                    double2(&vb)[8] = *reinterpret_cast<double2(*)[8]>(pb);
-                    store_lines(vb, sb, lane);
-                    if (g + 1 < GW) {
-                        load_at(udp, g + 1, vb);
-                    } else if (kk + Q < kmax) {
-                        int32_t rn[8];
-                        const double *gp[8];
-#pragma unroll
-                        for (int m = 0; m < 8; ++m) rn[m] = __shfl(jn, 8 * m + (lane >> 3), 64);
-                        row_ptrs(geo, rn, 1, 0, lane, gp);
-                        row_ptrs(UD, rn, G, g0, lane, udp);
-                        load_at(gp, 0, *reinterpret_cast<double2(*)[8]>(pa));
-                        load_at(udp, 0, vb);
-                    }
-                } else {
-                    double2 v[8];
-                    load_at(udp, g, v);
-                    store_lines(v, sb, lane);
-                }
-                const double *Rl = sb + lane * kStage;
-                double qL[4], qR[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int q = 4 * g + m;
-                    const double dk = di(q, 0) * pg.sx + di(q, 1) * pg.sy + di(q, 2) * pg.sz;
-                    const double dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
-                    const double mm = minmod_med(dk, dl);
-                    qL[m] = ui(q) + pg.fk * mm;
-                    qR[m] = Rl[m] - pg.fl * mm;
-                }
-                // face guards and M1 fluxes: F_X.A = (FA_X, a_X A + b_X F_X)
-                double FAL, aL, bL, FAR, aR, bR;
-                const int f1 = face_m164(qL, pg.Ax, pg.Ay, pg.Az, c, c3, FAL, aL, bL);
-                const int f2 = face_m164(qR, pg.Ax, pg.Ay, pg.Az, c, c3, FAR, aR, bR);
-                double w1 = 0.5, w2 = 0.5, w3 = -hc * pg.An;   // GLF
-                if (HLL) {
-                    double loL, hiL, loR, hiR;
-                    hll_speeds64(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                 loL, hiL);
-                    hll_speeds64(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                 loR, hiR);
-                    hll_weights(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
-                }
-                if (use) {
-                    cE += (f1 & 1) + (f2 & 1);
-                    cF += (f1 >> 1) + (f2 >> 1);
-                    // Phi.A = w1 F_L.A + w2 F_R.A + w3 (U_R - U_L), the vector part
-                    // (w1 a_L + w2 a_R) A + w1 b_L F_L + w2 b_R F_R + w3 (F_R - F_L)
-                    const double al = __builtin_fma(w1, aL, w2 * aR);
-                    const double bl = w1 * bL, br = w2 * bR;
-                    acc[4 * g] += wkl * __builtin_fma(w3, qR[0] - qL[0],
-                                                      __builtin_fma(w1, FAL, w2 * FAR));
-                    const double Av[3] = {pg.Ax, pg.Ay, pg.Az};
-#pragma unroll
-                    for (int m = 1; m < 4; ++m)
-                        acc[4 * g + m] +=
-                            wkl * __builtin_fma(w3, qR[m] - qL[m],
-                                                __builtin_fma(al, Av[m - 1],
-                                                              __builtin_fma(bl, qL[m], br * qR[m])));
-                }
-            }
-        }
-    }
-    // sum of the Q partial sums of each particle (a fixed butterfly: the same
-    // bits on every lane of the particle; by LDS permutes in the time-bin
-    // instantiations, where the DPP form left more registers spilled)
-    if (Q > 1) {
-#pragma unroll
-        for (int q = 0; q < 4 * GW; ++q) {
-            if constexpr (BIN) {
-#pragma unroll
-                for (int o = 1; o < Q; o <<= 1) acc[q] += __shfl_xor(acc[q], o, 64);
-            } else {
-                quad_sum<Q>(acc[q]);
-            }
-        }
-    }
-    // update, post-update guard, ledger, photon budget
-    double red[2 * GW];
-    int gE = 0, gF = 0;
-    double chk = 0.0;   // NaN iff an updated state is NaN or infinite
-    if (BIN && owner && !ends) {
-        // no update in this tick: keep the pending sums, count the current state
-        const double V = rk[R_V];
-#pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            if (touched) {
-                double *a = accm + (i * G + g0 + g) * 4;
-#pragma unroll
-                for (int m = 0; m < 4; ++m) a[m] += acc[4 * g + m];
-            }
-            red[g] = V * ui(4 * g);
-            red[GW + g] = 0.0;
-        }
-    } else if (owner) {
-        const double V = rk[R_V];
-        // the update: U - dt/V sum (global step), or U - (pending + this tick)/V
-        const double dtV = BIN ? 1.0 / V : dtp[0] / V;
-        if (BIN) {
-#pragma unroll
-            for (int g = 0; g < GW; ++g) {
-                double *a = accm + (i * G + g0 + g) * 4;
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    acc[4 * g + m] += a[m];
-                    a[m] = 0.0;
-                }
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            double q0 = ui(4 * g + 0) - dtV * acc[4 * g + 0];
-            double q1 = ui(4 * g + 1) - dtV * acc[4 * g + 1];
-            double q2 = ui(4 * g + 2) - dtV * acc[4 * g + 2];
-            double q3 = ui(4 * g + 3) - dtV * acc[4 * g + 3];
-            const double Epre = q0;
-            chk = __builtin_fma(q0, 0.0, chk);
-            chk = __builtin_fma(q1, 0.0, chk);
-            chk = __builtin_fma(q2, 0.0, chk);
-            chk = __builtin_fma(q3, 0.0, chk);
-            if (Uung) {
-                double *u = Uung + i * NQ + 4 * (g0 + g);
-                u[0] = q0;
-                u[1] = q1;
-                u[2] = q2;
-                u[3] = q3;
-            }
-            const int f = guard64(q0, q1, q2, q3, c);
-            gE += f & 1;
-            gF += f >> 1;
-            double *o = Uout + i * NQ + 4 * (g0 + g);
-            o[0] = q0;
-            o[1] = q1;
-            o[2] = q2;
-            o[3] = q3;
-            red[g] = V * q0;
-            red[GW + g] = (f & 1) ? -Epre * V : 0.0;
-        }
-    } else {
-#pragma unroll
-        for (int p = 0; p < 2 * GW; ++p) red[p] = 0.0;
-    }
-    if (chk != chk) atomicOr(status, ST_NONFINITE);
-    // partials [nb][2G]: photon totals in columns 0..G-1, ledger in G..2G-1
-    if (partials)
-        block_reduce_store<2 * GW>(red, partials + blk * 2 * G, smem,
-                                   [&](int p) { return p < GW ? g0 + p : G + g0 + p - GW; });
-    if (counts) {
-        int64_t v0 = wave_sum_i64(cE), v1 = wave_sum_i64(cF), v2 = wave_sum_i64(gE),
-                v3 = wave_sum_i64(gF);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) {
-            atomicAdd(&scnt[0], (unsigned long long)v0);
-            atomicAdd(&scnt[1], (unsigned long long)v1);
-            atomicAdd(&scnt[2], (unsigned long long)v2);
-            atomicAdd(&scnt[3], (unsigned long long)v3);
-        }
-        __syncthreads();
-        if (threadIdx.x < 4 && scnt[threadIdx.x]) atomicAdd(&counts[threadIdx.x], scnt[threadIdx.x]);
-    }
-}
-
 // Transport with the pairs inside a tile evaluated once (FP64, GLF or HLL,
-// Hopkins or Ivanova surfaces, one global step, all G <= 3 groups in one
-// wave).  Both solvers' pair fluxes and both surfaces are antisymmetric, so
+// Hopkins or Ivanova surfaces, G <= 3 groups in one wave: all of them, or one
+// of the slices that transport_slices makes of more).  Both solvers' pair fluxes and both surfaces are antisymmetric, so
 // one evaluation serves both particles of a pair.
 //
 // A block owns one tile: the 64 consecutive Morton particles of one column
@@ -939,11 +554,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 // particle none of whose pairs is due (binm) walks no list.  The particles
 // that do not end a step add their sums to the pending sums accm, the others
 // apply theirs, as in the two-sided binned kernel.
-template <int G, bool OFF32, bool HLL, bool IVA, bool BIN>
+template <int G, bool WHOLE, bool OFF32, bool HLL, bool IVA, bool BIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
+k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ geo,
                    const int32_t *__restrict__ task, const int64_t *__restrict__ wave_base,
-                   const int32_t *__restrict__ n_task, const double *__restrict__ UD,
+                   const int32_t *__restrict__ n_task, const double *__restrict__ UDall,
                    const double *__restrict__ dtp, double c, double box,
                    double *__restrict__ Uout, double *__restrict__ partials,
                    unsigned long long *__restrict__ counts, double *__restrict__ Uung,
@@ -958,8 +573,13 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
     __shared__ double dsh[kBlock / 64][16 * DS];
     __shared__ double smem[(kBlock / 64) * 2 * G];
     __shared__ unsigned long long scnt[4];
-    const int64_t blk = xcd_block(nb);
-    if (blk >= nb) return;                      // whole block: no barrier is skipped
+    // the block's tile and its groups g0 .. g0 + G of the GT
+    const int GT = WHOLE ? G : sl.groups, nsl = WHOLE ? 1 : sl.count;
+    const int64_t bg = xcd_block(nb * nsl);
+    if (bg >= nb * nsl) return;                 // whole block: no barrier is skipped
+    const int64_t blk = WHOLE ? bg : bg / nsl;
+    const int g0 = WHOLE ? 0 : sl.first + (int)(bg - blk * nsl) * G;
+    const double *UD = UDall + 16 * g0;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int sub = lane & 3;
     const int64_t t0 = blk * kTile;             // the tile's first particle
@@ -1003,7 +623,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
             double Ui[NQ];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const double *r = UD + (ic * G + g) * 16;
+                const double *r = UD + (ic * GT + g) * 16;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) Ui[4 * g + m] = r[m];
             }
@@ -1014,7 +634,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
             for (int g = 0; g < G; ++g)
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    Dsh[3 * (4 * g + sub) + a] = UD[(ic * G + g) * 16 + 4 + 3 * sub + a];
+                    Dsh[3 * (4 * g + sub) + a] = UD[(ic * GT + g) * 16 + 4 + 3 * sub + a];
             wave_lds_sync();
             const int64_t base = wb + pl;   // the particle's column in the table
             // Lines in flight: v holds the loads of the next stage (the
@@ -1041,7 +661,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
                 const int32_t tn = k + 4 < nn ? tl : (int32_t)ic;
                 const bool mirror = t < 0;
                 const int32_t j = t & 0x7fffffff;
-                const RowLines<OFF32> ul(UD, rw, G, lane);
+                const RowLines<OFF32> ul(UD, rw, GT, lane);
                 store_lines(v, sb, lane);       // the geometry lines
                 ul.load(0, v);
                 double rl[12];
@@ -1158,11 +778,11 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (touched) {
-                double *a = accm + (i * G + g) * 4;
+                double *a = accm + (i * GT + g0 + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) a[m] += acc[4 * g + m];
             }
-            red[g] = V * UD[(i * G + g) * 16];
+            red[g] = V * UD[(i * GT + g) * 16];
             red[G + g] = 0.0;
         }
     } else if (owner) {
@@ -1176,7 +796,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
         if constexpr (BIN) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                double *a = accm + (i * G + g) * 4;
+                double *a = accm + (i * GT + g0 + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     acc[4 * g + m] += a[m];
@@ -1186,7 +806,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const double *u = UD + (i * G + g) * 16;
+            const double *u = UD + (i * GT + g) * 16;
             double q0 = u[0] - dtV * acc[4 * g + 0];
             double q1 = u[1] - dtV * acc[4 * g + 1];
             double q2 = u[2] - dtV * acc[4 * g + 2];
@@ -1197,7 +817,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
             chk = __builtin_fma(q2, 0.0, chk);
             chk = __builtin_fma(q3, 0.0, chk);
             if (Uung) {
-                double *uu = Uung + i * NQ + 4 * g;
+                double *uu = Uung + (i * GT + g0 + g) * 4;
                 uu[0] = q0;
                 uu[1] = q1;
                 uu[2] = q2;
@@ -1206,7 +826,7 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
             const int f = guard64(q0, q1, q2, q3, c);
             gE += f & 1;
             gF += f >> 1;
-            double *o = Uout + i * NQ + 4 * g;
+            double *o = Uout + (i * GT + g0 + g) * 4;
             o[0] = q0;
             o[1] = q1;
             o[2] = q2;
@@ -1220,7 +840,8 @@ k_transport64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
     }
     if (chk != chk) atomicOr(status, ST_NONFINITE);
     if (partials)
-        block_reduce_store<2 * G>(red, partials + blk * 2 * G, smem, [&](int p) { return p; });
+        block_reduce_store<2 * G>(red, partials + blk * 2 * GT, smem,
+                                  [&](int p) { return p < G ? g0 + p : GT + g0 + p - G; });
     if (counts) {
         int64_t v0 = wave_sum_i64(cE), v1 = wave_sum_i64(cF), v2 = wave_sum_i64(gE),
                 v3 = wave_sum_i64(gF);
@@ -1353,129 +974,67 @@ void launch_finalize(rt_ctx *ctx, int64_t nb, const double *part, double *Q, dou
     k_finalize<G><<<1, kBlock, 0, ctx->stream>>>(fin, Q, ledger);
 }
 
-// Groups per wave of the FP64 transport (0: the default slice below).  All
-// groups in one wave compute the pair geometry once; each group costs about
-// 40 registers, and with more than 3 groups a wave no longer fits the 256
-// registers of 2 waves per SIMD (G = 3: 254 VGPRs), so larger G is cut into
-// slices of 2 groups (or 3, or one group per wave as the last resort).
-#ifndef RT_TRANSPORT_GW
-#define RT_TRANSPORT_GW 0
-#endif
-constexpr int transport_slice(int G) {
-    return G <= 3 ? G : (G % 2 == 0 ? 2 : (G % 3 == 0 ? 3 : 1));
+// rows of block partials the FP64 transport writes (one per tile)
+inline int64_t transport64_rows(int64_t n) { return (n + kTile - 1) / kTile; }
+
+// The tile transport of G groups of all GT, or of slices of G of them; accm: one
+// tick of the individual time steps.
+template <int G, bool WHOLE>
+void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, double *Uout,
+                    double *partials, int64_t *counts, double *Uung, int64_t tick, double *accm) {
+    const int64_t n = ctx->p.n, nt = transport64_rows(n);
+    const bool hll = ctx->solver == RT_HLL, iva = ctx->surfaces == RT_IVANOVA;
+    // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
+    const bool off32 = (uint64_t)n * 128u * ctx->p.groups < (uint64_t(1) << 32);
+    const unsigned grid = (unsigned)xcd_grid(nt * (WHOLE ? 1 : sl.count));
+#define RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, BIN_)                                                 \
+    k_transport64_tile<G, WHOLE, OFF32_, HLL_, IVA_, BIN_><<<grid, kBlock, 0, ctx->stream>>>(    \
+        n, nt, sl, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, ctx->p.c_red,       \
+        ctx->p.box, Uout, partials, (unsigned long long *)counts, Uung, ctx->status,             \
+        (const double2 *)ctx->hll_table, tick, accm, ctx->bin8 ? ctx->bin8 + n : nullptr)
+#define RT_TILE_LAUNCH_B(OFF32_, HLL_, IVA_)                                                     \
+    do {                                                                                         \
+        if (accm) RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, true);                                      \
+        else RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, false);                                          \
+    } while (0)
+#define RT_TILE_LAUNCH_S(HLL_, IVA_)                                                             \
+    do {                                                                                         \
+        if (off32) RT_TILE_LAUNCH_B(true, HLL_, IVA_);                                           \
+        else RT_TILE_LAUNCH_B(false, HLL_, IVA_);                                                \
+    } while (0)
+    if (hll && iva) RT_TILE_LAUNCH_S(true, true);
+    else if (hll) RT_TILE_LAUNCH_S(true, false);
+    else if (iva) RT_TILE_LAUNCH_S(false, true);
+    else RT_TILE_LAUNCH_S(false, false);
+#undef RT_TILE_LAUNCH_S
+#undef RT_TILE_LAUNCH_B
+#undef RT_TILE_LAUNCH
 }
-// The HLL solver holds about 10 more registers per group in flight (the wave
-// speeds of both face states).  With the particle's own state in LDS (OWNL)
-// all groups fit one wave up to G = 3 (256 VGPRs, no spill), measured 15%
-// faster on the 3-group 128^3 lattice than one group per wave at 3 waves per
-// SIMD (6.2 against 7.3 ms); larger odd G runs one group per wave, held in
-// registers at 3 waves per SIMD.
-#ifndef RT_HLL_GW
-#define RT_HLL_GW 0
-#endif
-constexpr int hll_slice(int G) { return G <= 3 ? G : (G % 2 == 0 ? 2 : 1); }
 
-// Lanes per particle of the FP64 transport (1, 2 or 4): with Q > 1 a wave
-// covers 64/Q particles whose neighbour lists overlap more, so the records
-// one iteration stages repeat more often in the caches.  Q = 4 cut the
-// calibrated fetch of the 3-group 128^3 lattice 14x (35 GB to 2.5 GB per
-// launch) and the time by 11% against Q = 1.
-#ifndef RT_TRANSPORT_Q
-#define RT_TRANSPORT_Q 4
-#endif
-constexpr int kQ = RT_TRANSPORT_Q;
-// rows of block partials the FP64 transport writes (one per block)
-inline int64_t transport_rows(int64_t n) { return (n + kBlock / kQ - 1) / (kBlock / kQ); }
+void launch_transport64(rt_ctx *ctx, const double *UD, const double *dt, double *Uout,
+                        double *partials, int64_t *counts, double *Uung, int64_t tick,
+                        double *accm) {
+    const int G = ctx->p.groups, s3 = slices_of_3(G), s2 = slices_of_2(G);
+    const Slices sl{G, 0, s3};
+    if (G == 1) {
+        launch_tiles64<1, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    } else if (G == 2) {
+        launch_tiles64<2, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    } else if (G == 3) {
+        launch_tiles64<3, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    } else {
+        if (s3 > 0)
+            launch_tiles64<3, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        if (s2 > 0)
+            launch_tiles64<2, false>(ctx, Slices{G, 3 * s3, s2}, UD, dt, Uout, partials, counts,
+                                     Uung, tick, accm);
+    }
+}
 
-// The FP64 global step with GLF and the Hopkins surfaces (up to 3 groups, all
-// in one wave) evaluates in-tile pairs once (k_transport64_tile); 0 selects
-// the two-sided kernel for it too.
-#ifndef RT_TRANSPORT_TILE
-#define RT_TRANSPORT_TILE 1
-#endif
-// The HLL solver takes the tiles too (its flux is as antisymmetric as GLF's);
-// 0 keeps it two-sided.
-#ifndef RT_TRANSPORT_TILE_HLL
-#define RT_TRANSPORT_TILE_HLL 1
-#endif
-// The Ivanova surfaces too (antisymmetric as well, A_lk = -A_kl; the
-// kernel-gradient sums come with the geometry records); 0 keeps them
-// two-sided.
-#ifndef RT_TRANSPORT_TILE_IVA
-#define RT_TRANSPORT_TILE_IVA 1
-#endif
-// The ticks of the individual time steps on the tiles too (a due pair's
-// weighted flux is antisymmetric); 0 keeps them two-sided.
-#ifndef RT_TICK_TILE
-#define RT_TICK_TILE 1
-#endif
-// ... and their gradients from the neighbour unions; 0: staged.
+// The ticks' gradients from the neighbour unions; 0: staged.
 #ifndef RT_TICK_UNION
 #define RT_TICK_UNION 1
 #endif
-inline bool use_tile64(const rt_ctx *ctx) {
-    return RT_TRANSPORT_TILE != 0 && ctx->p.precision == RT_FP64 &&
-           (ctx->solver == RT_GLF || (RT_TRANSPORT_TILE_HLL != 0 && ctx->solver == RT_HLL)) &&
-           (ctx->surfaces == RT_HOPKINS ||
-            (RT_TRANSPORT_TILE_IVA != 0 && ctx->surfaces == RT_IVANOVA)) &&
-           ctx->p.groups <= 3 && ctx->task != nullptr;
-}
-// rows of block partials the FP64 transport writes (one per block)
-inline int64_t transport64_rows(const rt_ctx *ctx) {
-    return use_tile64(ctx) ? (ctx->p.n + kTile - 1) / kTile : transport_rows(ctx->p.n);
-}
-
-template <int G>
-void launch_transport64(rt_ctx *ctx, const double *UD, const double *dt, double *Uout,
-                        double *partials, int64_t *counts, double *Uung) {
-    constexpr int GW =
-        (RT_TRANSPORT_GW == 0 || G % RT_TRANSPORT_GW != 0) ? transport_slice(G) : RT_TRANSPORT_GW;
-    constexpr int HW = (RT_HLL_GW == 0 || G % RT_HLL_GW != 0) ? hll_slice(G) : RT_HLL_GW;
-    const int64_t n = ctx->p.n, nb = transport_rows(n);
-    const double2 *tab = (const double2 *)ctx->hll_table;
-    const bool iva = ctx->surfaces == RT_IVANOVA;
-    if constexpr (G <= 3) {
-        if (use_tile64(ctx)) {
-            const int64_t nt = transport64_rows(ctx);
-            // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
-#define RT_TILE_LAUNCH(OFF32_, HLL_, IVA_)                                                     \
-    k_transport64_tile<G, OFF32_, HLL_, IVA_, false><<<(unsigned)xcd_grid(nt), kBlock, 0, ctx->stream>>>( \
-        n, nt, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, ctx->p.c_red,           \
-        ctx->p.box, Uout, partials, (unsigned long long *)counts, Uung, ctx->status, tab)
-#define RT_TILE_LAUNCH_S(HLL_, IVA_)                                                           \
-    do {                                                                                       \
-        if (off32) RT_TILE_LAUNCH(true, HLL_, IVA_);                                           \
-        else RT_TILE_LAUNCH(false, HLL_, IVA_);                                                \
-    } while (0)
-            const bool off32 = (uint64_t)n * 128u * G < (uint64_t(1) << 32);
-            if (ctx->solver == RT_HLL) {
-                if (iva) RT_TILE_LAUNCH_S(true, true);
-                else RT_TILE_LAUNCH_S(true, false);
-            } else {
-                if (iva) RT_TILE_LAUNCH_S(false, true);
-                else RT_TILE_LAUNCH_S(false, false);
-            }
-#undef RT_TILE_LAUNCH_S
-#undef RT_TILE_LAUNCH
-            return;
-        }
-    }
-#define RT_TRANSPORT_LAUNCH(W, HLL_, IVA_)                                                    \
-    k_transport64<G, W, false, HLL_, IVA_, kQ, own_lds(HLL_, IVA_, W),                        \
-                  pipe_on(HLL_, IVA_, W)>                                                     \
-        <<<(unsigned)xcd_grid(nb * (G / W)), kBlock, 0, ctx->stream>>>(                       \
-        n, nb, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, dt, ctx->p.c_red,          \
-        ctx->p.box, Uout, partials, (unsigned long long *)counts, Uung, ctx->status, 0,       \
-        nullptr, tab, nullptr)
-    if (ctx->solver == RT_HLL) {
-        if (iva) RT_TRANSPORT_LAUNCH(HW, true, true);
-        else RT_TRANSPORT_LAUNCH(HW, true, false);
-    } else {
-        if (iva) RT_TRANSPORT_LAUNCH(GW, false, true);
-        else RT_TRANSPORT_LAUNCH(GW, false, false);
-    }
-#undef RT_TRANSPORT_LAUNCH
-}
 
 // Lanes per particle of the FP64 gradient (1, 2 or 4); Q = 4 measured 14%
 // faster than Q = 1 on the 3-group 128^3 lattice.
@@ -1549,55 +1108,7 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
         k_gradient64<G, true, kGQ><<<(unsigned)xcd_grid(ng), B, 0, ctx->stream>>>(
             n, ng, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U, UD, ctx->status,
             ctx->p.box, tick);
-    constexpr int GW = transport_slice(G), HW = hll_slice(G);
-    const int64_t nt = transport_rows(n);
-    const double2 *tab = (const double2 *)ctx->hll_table;
-    const bool iva = ctx->surfaces == RT_IVANOVA;
-    const uint8_t *binm = ctx->bin8 ? ctx->bin8 + n : nullptr;
-    if constexpr (G <= 3) {
-        if (RT_TICK_TILE != 0 && use_tile64(ctx)) {
-            // the tiles in their time-bin mode (one row of partials per tile,
-            // as many as the two-sided kernel's blocks)
-            static_assert(kBlock / kQ == kTile, "a tile per two-sided block");
-            const bool off32 = (uint64_t)n * 128u * G < (uint64_t(1) << 32);
-#define RT_TICK_TILE_LAUNCH(OFF32_, HLL_, IVA_)                                                 \
-    k_transport64_tile<G, OFF32_, HLL_, IVA_, true>                                             \
-        <<<(unsigned)xcd_grid(nt), kBlock, 0, ctx->stream>>>(                                   \
-            n, nt, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, ctx->p.c_red,      \
-            ctx->p.box, Uout, partials, (unsigned long long *)counts, nullptr, ctx->status,     \
-            tab, tick, accm, binm)
-#define RT_TICK_TILE_S(HLL_, IVA_)                                                              \
-    do {                                                                                        \
-        if (off32) RT_TICK_TILE_LAUNCH(true, HLL_, IVA_);                                       \
-        else RT_TICK_TILE_LAUNCH(false, HLL_, IVA_);                                            \
-    } while (0)
-            if (ctx->solver == RT_HLL) {
-                if (iva) RT_TICK_TILE_S(true, true);
-                else RT_TICK_TILE_S(true, false);
-            } else {
-                if (iva) RT_TICK_TILE_S(false, true);
-                else RT_TICK_TILE_S(false, false);
-            }
-#undef RT_TICK_TILE_S
-#undef RT_TICK_TILE_LAUNCH
-            return;
-        }
-    }
-#define RT_TICK_LAUNCH(W, HLL_, IVA_)                                                          \
-    k_transport64<G, W, true, HLL_, IVA_, kQ, own_lds(HLL_, IVA_, W),                         \
-                  pipe_on(HLL_, IVA_, W)>                                                     \
-        <<<(unsigned)xcd_grid(nt * (G / W)), kBlock, 0, ctx->stream>>>(                        \
-            n, nt, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, dt, ctx->p.c_red,       \
-            ctx->p.box, Uout, partials, (unsigned long long *)counts, nullptr, ctx->status,    \
-            tick, accm, tab, binm)
-    if (ctx->solver == RT_HLL) {
-        if (iva) RT_TICK_LAUNCH(HW, true, true);
-        else RT_TICK_LAUNCH(HW, true, false);
-    } else {
-        if (iva) RT_TICK_LAUNCH(GW, false, true);
-        else RT_TICK_LAUNCH(GW, false, false);
-    }
-#undef RT_TICK_LAUNCH
+    launch_transport64(ctx, UD, dt, Uout, partials, counts, nullptr, tick, accm);
 }
 
 #define RT_DISPATCH_G(G_, FN, ...)                                  \
@@ -1667,13 +1178,13 @@ rt_status rt_gradient_impl(rt_ctx *ctx, const void *U, void *UD) {
 rt_status rt_transport_impl(rt_ctx *ctx, const void *UD, const double *dt, void *U_out,
                             double *Q, int64_t *counts, double *ledger, void *Uung) {
     // rows of block partials: the FP64 kernel's blocks, or one per kBlock particles
-    const int64_t nb = ctx->p.precision == RT_FP64 ? transport64_rows(ctx)
+    const int64_t nb = ctx->p.precision == RT_FP64 ? transport64_rows(ctx->p.n)
                                                    : rt_transport32_rows(ctx->p.n);
     double *part = (Q || ledger) ? ctx->partials : nullptr;
     rt_timer_begin(ctx, "transport");
     if (ctx->p.precision == RT_FP64) {
-        RT_DISPATCH_G(ctx->p.groups, launch_transport64, ctx, (const double *)UD, dt,
-                      (double *)U_out, part, counts, (double *)Uung);
+        launch_transport64(ctx, (const double *)UD, dt, (double *)U_out, part, counts,
+                           (double *)Uung, 0, nullptr);
     } else {
         rt_transport32(ctx, (const float *)UD, dt, (float *)U_out, part, counts, (float *)Uung);
     }
@@ -1690,7 +1201,7 @@ rt_status rt_transport_impl(rt_ctx *ctx, const void *UD, const double *dt, void 
 // (FP64; injection and the refresh of the stored states are in rt_bins.hip).
 rt_status rt_tick_step_impl(rt_ctx *ctx, double *U, double *UD, const double *dt, int64_t tick,
                             double *accm, double *Q, int64_t *counts, double *ledger) {
-    const int64_t nb = transport_rows(ctx->p.n);
+    const int64_t nb = transport64_rows(ctx->p.n);
     double *part = (Q || ledger) ? ctx->partials : nullptr;
     rt_timer_begin(ctx, "tick");
     RT_DISPATCH_G(ctx->p.groups, launch_tick64, ctx, U, UD, dt, U, part, counts, tick, accm);

@@ -12,9 +12,8 @@
 //   A: lam''   = guard^T lam'''                             (needs U'')
 //   B: mu_kl   = dt lam''_l / V_l - dt lam''_k / V_k
 //      lam'_k  = lam''_k + sum_l (dP_kl/dU'_k)^T mu_kl,  lamD_k = sum_l (dP_kl/dD_k)^T mu_kl
-//      (each lane differentiates its own-perspective pair flux with respect to
-//      its own inputs only: the pair's other half is taken by the neighbour's
-//      lane, with P_lk = -P_kl and mu_lk = -mu_kl)
+//      (a pair across tiles is differentiated by both its particles, each with
+//      respect to its own inputs, with P_lk = -P_kl and mu_lk = -mu_kl)
 //   C: rho_i   = S_i^{-1} lamD_i;
 //      lam_p   = lam'_p - (sum_j w_pj s_pj) . rho_p + sum_i w(r_ip/H_i) s_ip . rho_i
 //   D: dLoss/dL_s += dt sum_g coef_sg lam_E,g
@@ -28,36 +27,12 @@ namespace {
 
 inline unsigned nblk(int64_t n, int b = kBlock) { return (unsigned)((n + b - 1) / b); }
 
-// Waves per SIMD the HLL pair pass is held to.  With its own state in
-// registers it spilled about 30 at 2 waves and none at 1 (in accumulation
-// registers); on the 3-group 128^3 lattice the backward of 20 steps took 496
-// ms at 2 and 577 ms at 1.  With the own state in LDS it fits 256 registers
-// at 2 waves without spills: 410 ms.
-#ifndef RT_ADJ_HLL_WAVES
-#define RT_ADJ_HLL_WAVES 2
-#endif
-constexpr int kAdjHllWaves = RT_ADJ_HLL_WAVES;
-// The HLL pair pass keeps the own state, gradients and cotangent in LDS
-// rather than in registers (21 doubles per particle, 45.5 KB per block).
-#ifndef RT_ADJ_HLL_OWN
-#define RT_ADJ_HLL_OWN 1
-#endif
-// The HLL pair pass of up to 3 groups takes the tiles of the forward (the
-// adjoint of the tile transport); 0 keeps it two-sided.
-#ifndef RT_ADJ_TILE_HLL
-#define RT_ADJ_TILE_HLL 1
-#endif
-// ... and with the Ivanova surfaces; 0 keeps those two-sided.
-#ifndef RT_ADJ_TILE_IVA
-#define RT_ADJ_TILE_IVA 1
-#endif
 // Waves per SIMD of the HLL tile pair pass: at 2 it spills 28 bytes outside
 // its inner loop; at 1 (no spill) the 20-step backward of the 3-group 128^3
 // lattice took 406 ms against 305.
 #ifndef RT_ADJ_TILE_HLL_WAVES
 #define RT_ADJ_TILE_HLL_WAVES 2
 #endif
-constexpr bool kAdjHllOwn = RT_ADJ_HLL_OWN != 0;
 
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_adj_guard64(int64_t n, const double *__restrict__ Uung,
@@ -76,293 +51,51 @@ __global__ __launch_bounds__(kBlock) void k_adj_guard64(int64_t n, const double 
     for (int m = 0; m < 4; ++m) lam2[4 * t + m] = l[m];
 }
 
-// Pass B.  R[k][g] = (lam'_k (4) | rho_k (4 x 3)), the layout of a gradient
-// record.  As in the forward transport, a wave owns 64 particles and GW of the
-// G groups.
-//
-// Q lanes share a particle, each taking every Q-th neighbour slot (as in the
-// forward transport); the partial sums are combined by a fixed butterfly.
-//
-// HLL: the pair flux of the HLL solver, P = w1 F_L.A + w2 F_R.A + w3 (U_R -
-// U_L) with weights from the face states' wave speeds (the table hll); its
-// cotangent m = 2 nu pulls back through the two M1 fluxes, the jump term, the
-// weights and, through the speeds, the table lookups (hll_weights_vjp,
-// hll_speeds64_vjp).
-//
-// IVA: the Ivanova surfaces (eq:IvanovaAij) in the recomputed pair geometry;
-// they are static, so the pull-back is otherwise the same.
-template <int G, int GW, int Q = 1, bool HLL = false, bool IVA = false, bool OWNL = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(HLL ? kAdjHllWaves : 1)))
-void k_adj_pair64(
-    int64_t n, int64_t nb, const double *__restrict__ geo, const int32_t *__restrict__ nbr,
-    const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_nbr,
-    const double *__restrict__ UD, const double *__restrict__ lam2,
-    const double *__restrict__ dtp, double c, double box, double *__restrict__ R,
-    const double2 *__restrict__ hll = nullptr, const double *__restrict__ ivan = nullptr) {
-    static_assert(G % GW == 0, "group slices must tile the groups");
-    static_assert(Q == 1 || Q == 2 || Q == 4, "lanes per particle: 1, 2 or 4");
-    constexpr int NS = G / GW, NQ = 4 * GW, PW = 64 / Q, PB = kBlock / Q;
-    constexpr int OS = 20 * GW + 1;             // OWNL: (U, D, lam'') per group in LDS
-    __shared__ double stage[kBlock / 64][64 * kStage];
-    __shared__ double own[OWNL ? PB * OS : 1];
-    const int64_t bg = xcd_block(nb * NS);
-    if (bg >= nb * NS) return;
-    const int64_t blk = bg / NS;
-    const int g0 = (int)(bg - blk * NS) * GW;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int sub = lane % Q;
-    const int64_t i0 = blk * PB + wv * PW;      // first particle of the wave
-    const int64_t i = i0 + lane / Q;
-    const bool active = i < n;
-    const bool owner = active && sub == 0;
-    const int64_t ic = active ? i : n - 1;
-    const int64_t w = i0 >> 6;                  // neighbour-table wave (PW divides 64)
-    const bool wave_live = i0 < n;
-    const double ibox = 1.0 / box;
-    const double dt = dtp[0];
-    double *sb = stage[wv];
-
-    const double *rk = geo + (int64_t)kRec * ic;
-    const double dtVk = dt / rk[R_V];
-    double gk[3] = {0.0, 0.0, 0.0};   // IVA: own kernel-gradient sum
-    if (IVA) {
-        gk[0] = ivan[4 * ic];
-        gk[1] = ivan[4 * ic + 1];
-        gk[2] = ivan[4 * ic + 2];
-    }
-    double Ui[OWNL ? 1 : NQ], Di[OWNL ? 1 : NQ * 3], Li[OWNL ? 1 : NQ];
-    double *ow = own + (OWNL ? (threadIdx.x / Q) * OS : 0);
-    if constexpr (OWNL) {
-        // per group: the 16 values of the gradient record, then lam''
-#pragma unroll
-        for (int e = sub; e < 20 * GW; e += Q) {
-            const int g = e / 20, f = e - 20 * g;
-            ow[e] = f < 16 ? UD[(ic * G + g0 + g) * 16 + f] : lam2[(ic * G + g0 + g) * 4 + f - 16];
-        }
-        wave_lds_sync();
-    } else {
-#pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            const double *r = UD + (ic * G + g0 + g) * 16;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                Ui[4 * g + m] = r[m];
-                Di[3 * (4 * g + m) + 0] = r[4 + 3 * m];
-                Di[3 * (4 * g + m) + 1] = r[5 + 3 * m];
-                Di[3 * (4 * g + m) + 2] = r[6 + 3 * m];
-                Li[4 * g + m] = lam2[(ic * G + g0 + g) * 4 + m];
-            }
-        }
-    }
-    // q = 4 g + m: own state, gradient component a, cotangent
-    auto ui = [&](int q) -> double {
-        if constexpr (OWNL) return ow[20 * (q >> 2) + (q & 3)];
-        else return Ui[q];
-    };
-    auto di = [&](int q, int a) -> double {
-        if constexpr (OWNL) return ow[20 * (q >> 2) + 4 + 3 * (q & 3) + a];
-        else return Di[3 * q + a];
-    };
-    auto li = [&](int q) -> double {
-        if constexpr (OWNL) return ow[20 * (q >> 2) + 16 + (q & 3)];
-        else return Li[q];
-    };
-    double aU[NQ], aD[NQ * 3];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) aU[q] = aD[3 * q] = aD[3 * q + 1] = aD[3 * q + 2] = 0.0;
-
-    if (wave_live) {
-        const int64_t base = wave_base[w] + (i & 63);
-        int32_t kmax = (int32_t)((wave_base[w + 1] - wave_base[w]) >> 6);
-        const int32_t nn = active ? n_nbr[i] : 0;
-        if (Q > 1) {                            // the longest list of this wave's particles
-            kmax = nn;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, 64));
-        }
-        // the next iteration's neighbour index is loaded one iteration ahead
-        int32_t jn = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
-        for (int32_t kk = 0; kk < kmax; kk += Q) {
-            const int32_t k = kk + sub;
-            const bool valid = k < nn;
-            const int32_t j = jn;
-            // (slot 0 of the wave's table exists once kmax > 0: no branch
-            // around the load, whose wait would then be a full one)
-            const int32_t jl = nbr[base + 64 * (int64_t)(k + Q < nn ? k + Q : 0)];
-            jn = k + Q < nn ? jl : (int32_t)ic;
-            int64_t row[8];
-#pragma unroll
-            for (int m = 0; m < 8; ++m) row[m] = __shfl(j, 8 * m + (lane >> 3), 64);
-            stage_lines(geo, row, sb, lane);
-            double rl[12];
-#pragma unroll
-            for (int q = 0; q < 12; ++q) rl[q] = sb[lane * kStage + q];
-            PairGeo pg;
-            if (IVA) {
-                stage_rows4(ivan, 4, j, sb, lane);
-                const double gl[3] = {sb[lane * kStage], sb[lane * kStage + 1],
-                                      sb[lane * kStage + 2]};
-                pair_geometry_ivanova64(rk, rl, gk, gl, box, ibox, pg);
-            } else {
-                pair_geometry64(rk, rl, box, ibox, pg);
-            }
-            const bool use = valid && pg.An > 0.0;
-            const double dtVl = dt / rl[R_V];
-#pragma unroll
-            for (int g = 0; g < GW; ++g) {
-                // the record lines and the cotangent rows in one round trip
-                int64_t rowg[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) rowg[m] = row[m] * G + g0 + g;
-                double2 v[8], vl[2];
-                load_lines(UD, rowg, lane, v);
-                load_rows4(lam2 + 4 * (g0 + g), 4 * G, j, lane, vl);
-                store_lines(v, sb, lane);
-                double Rl[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage + q];
-                store_rows4(vl, sb, lane);
-                double Ll[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) Ll[m] = sb[lane * kStage + m];
-                // forward recompute of this pair and group
-                double qLp[4], qRp[4], qL[4], qR[4];
-                bool own_slope[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int q = 4 * g + m;
-                    const double dk = di(q, 0) * pg.sx + di(q, 1) * pg.sy + di(q, 2) * pg.sz;
-                    const double dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
-                    const double mm = minmod(dk, dl);
-                    own_slope[m] = (dk * dl > 0.0) && (fabs(dk) <= fabs(dl));
-                    qLp[m] = qL[m] = ui(q) + pg.fk * mm;
-                    qRp[m] = qR[m] = Rl[m] - pg.fl * mm;
-                }
-                guard64(qL[0], qL[1], qL[2], qL[3], c);
-                guard64(qR[0], qR[1], qR[2], qR[3], c);
-                // cotangent of P_kl and its pull-back to the face states
-                double nu[4], tL[4], tR[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) nu[m] = 0.5 * (dtVl * Ll[m] - dtVk * li(4 * g + m));
-                double S1 = 0.0, S2 = 0.0;   // HLL: m . F_L, m . F_R
-                m1_flux64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c, nu, tL,
-                              HLL ? &S1 : nullptr);
-                m1_flux64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c, nu, tR,
-                              HLL ? &S2 : nullptr);
-                if constexpr (HLL) {
-                    const double iAn = pg.An > 0.0 ? rcp64(pg.An) : 0.0;
-                    double loL, hiL, loR, hiR, w1, w2, w3;
-                    hll_speeds64(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loL,
-                                 hiL);
-                    hll_speeds64(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loR,
-                                 hiR);
-                    hll_weights(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
-                    double S3 = 0.0;                       // m . (U_R - U_L)
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        S3 += nu[m] * (qR[m] - qL[m]);
-                        tL[m] = 2.0 * (w1 * tL[m] - w3 * nu[m]);
-                        tR[m] = 2.0 * (w2 * tR[m] + w3 * nu[m]);
-                    }
-                    double gloL, ghiL, gloR, ghiR;
-                    hll_weights_vjp(loL, hiL, loR, hiR, pg.An, 2.0 * S1, 2.0 * S2, 2.0 * S3,
-                                    gloL, ghiL, gloR, ghiR);
-                    hll_speeds64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                     gloL, ghiL, tL);
-                    hll_speeds64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                     gloR, ghiR, tR);
-                } else {
-                    const double dis = c * pg.An;   // 2 * (c/2) |A| times nu = mu/2
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        tL[m] += dis * nu[m];
-                        tR[m] -= dis * nu[m];
-                    }
-                }
-                guard64_vjp(qLp, tL, c);
-                guard64_vjp(qRp, tR, c);
-                if (use) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const int q = 4 * g + m;
-                        aU[q] += tL[m];
-                        const double lm = own_slope[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0;
-                        aD[3 * q] += lm * pg.sx;
-                        aD[3 * q + 1] += lm * pg.sy;
-                        aD[3 * q + 2] += lm * pg.sz;
-                    }
-                }
-            }
-        }
-    }
-    if (Q > 1) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            quad_sum<Q>(aU[q]);
-            quad_sum<Q>(aD[3 * q]);
-            quad_sum<Q>(aD[3 * q + 1]);
-            quad_sum<Q>(aD[3 * q + 2]);
-        }
-    }
-    if (!owner) return;
-    const double iV = 1.0 / rk[R_V];
-    const double b00 = rk[R_B] * iV, b01 = rk[R_B + 1] * iV, b02 = rk[R_B + 2] * iV;
-    const double b11 = rk[R_B + 3] * iV, b12 = rk[R_B + 4] * iV, b22 = rk[R_B + 5] * iV;
-#pragma unroll
-    for (int g = 0; g < GW; ++g) {
-        double *o = R + (i * G + g0 + g) * 16;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int q = 4 * g + m;
-            o[m] = li(q) + aU[q];
-            o[4 + 3 * m + 0] = b00 * aD[3 * q] + b01 * aD[3 * q + 1] + b02 * aD[3 * q + 2];
-            o[4 + 3 * m + 1] = b01 * aD[3 * q] + b11 * aD[3 * q + 1] + b12 * aD[3 * q + 2];
-            o[4 + 3 * m + 2] = b02 * aD[3 * q] + b12 * aD[3 * q + 1] + b22 * aD[3 * q + 2];
-        }
-    }
-}
-
-// Pass B with the pairs inside a tile evaluated once: the adjoint of the tile
-// transport (GLF or HLL, Hopkins or Ivanova surfaces).  A block owns one 64-particle tile and
-// GW of the groups; its particles walk the forward's task lists (k_tasks), in
-// which an in-tile pair (k, l) appears once, flagged, in one particle's list.
-// That lane pulls the pair back for both particles: its own cotangents as in
-// k_adj_pair64, and the partner's, added by LDS atomics to the partner's row
-// of its wave's copy of the tile's accumulator.  The forward evaluates the
-// pair's face states once and uses the flux with opposite signs at its two
-// particles, so from l's side the face states swap, s and A change sign, and
-// the pull-back gives l
+// Pass B: R[k][g] = (lam'_k (4) | rho_k (4 x 3)), the layout of a gradient
+// record, with the pairs inside a tile evaluated once: the adjoint of the tile
+// transport (GLF or HLL, Hopkins or Ivanova surfaces, any number of groups).  A
+// block owns one 64-particle tile and one group (a wave's state per group is
+// three times the forward's: 239 VGPRs, and with all three groups in a wave the
+// pass ran 1.5x slower); its particles walk the forward's task lists (k_tasks),
+// in which an in-tile pair (k, l) appears once, flagged, in one particle's
+// list.  That lane pulls the pair back for both particles: its own cotangents,
+// and the partner's, added by LDS atomics to the partner's row of its wave's
+// copy of the tile's accumulator.  The forward evaluates the pair's face states
+// once and uses the flux with opposite signs at its two particles, so from l's
+// side the face states swap, s and A change sign, and the pull-back gives l
 //   the cotangent of its state: t_R (k's right-face cotangent),
 //   that of its gradient: (f_k t_L - f_l t_R) s where l's slope was the
 //     limiter's choice (|d_l| <= |d_k|, same signs),
 // which is the exact adjoint of the forward's single evaluation.  After a
 // block barrier each particle's sums are its own plus the 4 waves' rows in a
-// fixed order, as in the forward.  HLL: the HLL solver's pull-back of
-// k_adj_pair64 (its flux is antisymmetric like GLF's, so the partner's share
-// is the same t_R and slope term); it keeps the particle's own state,
-// gradients and cotangent in LDS (OWNL), which the HLL pull-back's registers
-// need.  IVA: the Ivanova surfaces (static, so only the recomputed pair
-// geometry changes), with the kernel-gradient sums from slots 13-15 of the
-// geometry records, and the own values in LDS as for HLL.
-template <int G, int GW, bool OFF32, bool HLL, bool IVA>
+// fixed order, as in the forward.
+// HLL: the pair flux of the HLL solver, P = w1 F_L.A + w2 F_R.A + w3 (U_R -
+// U_L) with weights from the face states' wave speeds (the table hll); its
+// cotangent m = 2 nu pulls back through the two M1 fluxes, the jump term, the
+// weights and, through the speeds, the table lookups (hll_weights_vjp,
+// hll_speeds64_vjp).  It keeps the particle's own state, gradients and
+// cotangent in LDS (OWNL), which its registers need.
+// IVA: the Ivanova surfaces (static, so only the recomputed pair geometry
+// changes), with the kernel-gradient sums from slots 13-15 of the geometry
+// records, and the own values in LDS as for HLL.
+template <bool OFF32, bool HLL, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(HLL ? RT_ADJ_TILE_HLL_WAVES : 2))) void
-k_adj_pair64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
+k_adj_pair64_tile(int64_t n, int64_t nb, int G, const double *__restrict__ geo,
                   const int32_t *__restrict__ task, const int64_t *__restrict__ wave_base,
                   const int32_t *__restrict__ n_task, const double *__restrict__ UD,
                   const double *__restrict__ lam2, const double *__restrict__ dtp, double c,
                   double box, double *__restrict__ R, const double2 *__restrict__ hll) {
-    static_assert(G % GW == 0, "group slices must tile the groups");
-    constexpr int NS = G / GW, NQ = 4 * GW, MS = 16 * GW + 1;   // accumulator row, padded
+    constexpr int NQ = 4, MS = 17;              // accumulator row, padded
     static_assert(kTile == 64 && kBlock == 256, "a block of 4 waves x 16 particles per tile");
     __shared__ double stage[kBlock / 64][64 * kStage];
     __shared__ double mir[kBlock / 64][kTile * MS];
     constexpr bool OWNL = HLL || IVA;
     constexpr int OS = 5 * NQ + 1;              // own row: U (NQ), D (3 NQ), lambda (NQ), pad
     __shared__ double own[OWNL ? kTile * OS : 1];
-    const int64_t bg = xcd_block(nb * NS);
-    if (bg >= nb * NS) return;                  // whole block: no barrier is skipped
-    const int64_t blk = bg / NS;
-    const int g0 = (int)(bg - blk * NS) * GW;
+    const int64_t bg = xcd_block(nb * G);
+    if (bg >= nb * G) return;                   // whole block: no barrier is skipped
+    const int64_t blk = bg / G;
+    const int g0 = (int)(bg - blk * G);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int sub = lane & 3;
     const int64_t t0 = blk * kTile;             // the tile's first particle
@@ -386,29 +119,25 @@ k_adj_pair64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
     double *orow = own + (OWNL ? pl * OS : 0);  // (OWNL) the particle's row
     if constexpr (OWNL) {
         // lane sub copies component sub of each group
-#pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            const double *r = UD + (ic * G + g0 + g) * 16;
-            const int q = 4 * g + sub;
+        {
+            const double *r = UD + (ic * G + g0) * 16;
+            const int q = sub;
             orow[q] = r[sub];
             orow[NQ + 3 * q + 0] = r[4 + 3 * sub];
             orow[NQ + 3 * q + 1] = r[5 + 3 * sub];
             orow[NQ + 3 * q + 2] = r[6 + 3 * sub];
-            orow[4 * NQ + q] = lam2[(ic * G + g0 + g) * 4 + sub];
+            orow[4 * NQ + q] = lam2[(ic * G + g0) * 4 + sub];
         }
         wave_lds_sync();
     } else {
+        const double *r = UD + (ic * G + g0) * 16;
 #pragma unroll
-        for (int g = 0; g < GW; ++g) {
-            const double *r = UD + (ic * G + g0 + g) * 16;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                Ui[4 * g + m] = r[m];
-                Di[3 * (4 * g + m) + 0] = r[4 + 3 * m];
-                Di[3 * (4 * g + m) + 1] = r[5 + 3 * m];
-                Di[3 * (4 * g + m) + 2] = r[6 + 3 * m];
-                Li[4 * g + m] = lam2[(ic * G + g0 + g) * 4 + m];
-            }
+        for (int m = 0; m < 4; ++m) {
+            Ui[m] = r[m];
+            Di[3 * m + 0] = r[4 + 3 * m];
+            Di[3 * m + 1] = r[5 + 3 * m];
+            Di[3 * m + 2] = r[6 + 3 * m];
+            Li[m] = lam2[(ic * G + g0) * 4 + m];
         }
     }
     auto ui = [&](int q) -> double { if constexpr (OWNL) return orow[q]; else return Ui[q]; };
@@ -463,97 +192,94 @@ k_adj_pair64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
             }
             const bool use = valid && pg.An > 0.0;
             const double dtVl = dt * rcp64(rl[R_V]);   // (about 1 ulp; no IEEE division per pair)
+            // the record lines and the cotangent rows in one round trip
+            double2 v[8], vl[2];
+            ul.load(g0, v);
+            load_rows4(lam2 + 4 * (g0), 4 * G, j, lane, vl);
+            store_lines(v, sb, lane);
+            double Rl[16];
 #pragma unroll
-            for (int g = 0; g < GW; ++g) {
-                // the record lines and the cotangent rows in one round trip
-                double2 v[8], vl[2];
-                ul.load(g0 + g, v);
-                load_rows4(lam2 + 4 * (g0 + g), 4 * G, j, lane, vl);
-                store_lines(v, sb, lane);
-                double Rl[16];
+            for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage + q];
+            store_rows4(vl, sb, lane);
+            double Ll[4];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage + q];
-                store_rows4(vl, sb, lane);
-                double Ll[4];
+            for (int m = 0; m < 4; ++m) Ll[m] = sb[lane * kStage + m];
+            // forward recompute of this pair and group
+            double qLp[4], qRp[4], qL[4], qR[4];
+            bool slope_k[4], slope_l[4];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) Ll[m] = sb[lane * kStage + m];
-                // forward recompute of this pair and group
-                double qLp[4], qRp[4], qL[4], qR[4];
-                bool slope_k[4], slope_l[4];
+            for (int m = 0; m < 4; ++m) {
+                const int q = m;
+                const double dk = di(q, 0) * pg.sx + di(q, 1) * pg.sy + di(q, 2) * pg.sz;
+                const double dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
+                const double mm = minmod(dk, dl);
+                slope_k[m] = (dk * dl > 0.0) && (fabs(dk) <= fabs(dl));
+                slope_l[m] = (dk * dl > 0.0) && (fabs(dl) <= fabs(dk));
+                qLp[m] = qL[m] = ui(q) + pg.fk * mm;
+                qRp[m] = qR[m] = Rl[m] - pg.fl * mm;
+            }
+            guard64(qL[0], qL[1], qL[2], qL[3], c);
+            guard64(qR[0], qR[1], qR[2], qR[3], c);
+            // cotangent of P_kl and its pull-back to the face states
+            double nu[4], tL[4], tR[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) nu[m] = 0.5 * (dtVl * Ll[m] - dtVk * li(m));
+            double S1 = 0.0, S2 = 0.0;   // HLL: m . F_L, m . F_R
+            m1_flux64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c, nu, tL,
+                          HLL ? &S1 : nullptr);
+            m1_flux64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c, nu, tR,
+                          HLL ? &S2 : nullptr);
+            if constexpr (HLL) {
+                const double iAn = pg.An > 0.0 ? rcp64(pg.An) : 0.0;
+                double loL, hiL, loR, hiR, w1, w2, w3;
+                hll_speeds64(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loL,
+                             hiL);
+                hll_speeds64(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loR,
+                             hiR);
+                hll_weights(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
+                double S3 = 0.0;                       // m . (U_R - U_L)
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    const int q = 4 * g + m;
-                    const double dk = di(q, 0) * pg.sx + di(q, 1) * pg.sy + di(q, 2) * pg.sz;
-                    const double dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
-                    const double mm = minmod(dk, dl);
-                    slope_k[m] = (dk * dl > 0.0) && (fabs(dk) <= fabs(dl));
-                    slope_l[m] = (dk * dl > 0.0) && (fabs(dl) <= fabs(dk));
-                    qLp[m] = qL[m] = ui(q) + pg.fk * mm;
-                    qRp[m] = qR[m] = Rl[m] - pg.fl * mm;
+                    S3 += nu[m] * (qR[m] - qL[m]);
+                    tL[m] = 2.0 * (w1 * tL[m] - w3 * nu[m]);
+                    tR[m] = 2.0 * (w2 * tR[m] + w3 * nu[m]);
                 }
-                guard64(qL[0], qL[1], qL[2], qL[3], c);
-                guard64(qR[0], qR[1], qR[2], qR[3], c);
-                // cotangent of P_kl and its pull-back to the face states
-                double nu[4], tL[4], tR[4];
+                double gloL, ghiL, gloR, ghiR;
+                hll_weights_vjp(loL, hiL, loR, hiR, pg.An, 2.0 * S1, 2.0 * S2, 2.0 * S3,
+                                gloL, ghiL, gloR, ghiR);
+                hll_speeds64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
+                                 gloL, ghiL, tL);
+                hll_speeds64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
+                                 gloR, ghiR, tR);
+            } else {
+                const double dis = c * pg.An;   // 2 * (c/2) |A| times nu = mu/2
 #pragma unroll
-                for (int m = 0; m < 4; ++m) nu[m] = 0.5 * (dtVl * Ll[m] - dtVk * li(4 * g + m));
-                double S1 = 0.0, S2 = 0.0;   // HLL: m . F_L, m . F_R
-                m1_flux64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c, nu, tL,
-                              HLL ? &S1 : nullptr);
-                m1_flux64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c, nu, tR,
-                              HLL ? &S2 : nullptr);
-                if constexpr (HLL) {
-                    const double iAn = pg.An > 0.0 ? rcp64(pg.An) : 0.0;
-                    double loL, hiL, loR, hiR, w1, w2, w3;
-                    hll_speeds64(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loL,
-                                 hiL);
-                    hll_speeds64(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll, loR,
-                                 hiR);
-                    hll_weights(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
-                    double S3 = 0.0;                       // m . (U_R - U_L)
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        S3 += nu[m] * (qR[m] - qL[m]);
-                        tL[m] = 2.0 * (w1 * tL[m] - w3 * nu[m]);
-                        tR[m] = 2.0 * (w2 * tR[m] + w3 * nu[m]);
-                    }
-                    double gloL, ghiL, gloR, ghiR;
-                    hll_weights_vjp(loL, hiL, loR, hiR, pg.An, 2.0 * S1, 2.0 * S2, 2.0 * S3,
-                                    gloL, ghiL, gloR, ghiR);
-                    hll_speeds64_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                     gloL, ghiL, tL);
-                    hll_speeds64_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, c, hll,
-                                     gloR, ghiR, tR);
-                } else {
-                    const double dis = c * pg.An;   // 2 * (c/2) |A| times nu = mu/2
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        tL[m] += dis * nu[m];
-                        tR[m] -= dis * nu[m];
-                    }
+                for (int m = 0; m < 4; ++m) {
+                    tL[m] += dis * nu[m];
+                    tR[m] -= dis * nu[m];
                 }
-                guard64_vjp(qLp, tL, c);
-                guard64_vjp(qRp, tR, c);
-                if (use) {
+            }
+            guard64_vjp(qLp, tL, c);
+            guard64_vjp(qRp, tR, c);
+            if (use) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int q = m;
+                    aU[q] += tL[m];
+                    const double lm = slope_k[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0;
+                    aD[3 * q] += lm * pg.sx;
+                    aD[3 * q + 1] += lm * pg.sy;
+                    aD[3 * q + 2] += lm * pg.sz;
+                }
+                if (mirror) {
+                    double *o = mw + mr;
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
-                        const int q = 4 * g + m;
-                        aU[q] += tL[m];
-                        const double lm = slope_k[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0;
-                        aD[3 * q] += lm * pg.sx;
-                        aD[3 * q + 1] += lm * pg.sy;
-                        aD[3 * q + 2] += lm * pg.sz;
-                    }
-                    if (mirror) {
-                        double *o = mw + mr + 16 * g;
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            const double ll = slope_l[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0;
-                            atomicAdd(o + m, tR[m]);
-                            atomicAdd(o + 4 + 3 * m, ll * pg.sx);
-                            atomicAdd(o + 5 + 3 * m, ll * pg.sy);
-                            atomicAdd(o + 6 + 3 * m, ll * pg.sz);
-                        }
+                        const double ll = slope_l[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0;
+                        atomicAdd(o + m, tR[m]);
+                        atomicAdd(o + 4 + 3 * m, ll * pg.sx);
+                        atomicAdd(o + 5 + 3 * m, ll * pg.sy);
+                        atomicAdd(o + 6 + 3 * m, ll * pg.sz);
                     }
                 }
             }
@@ -571,33 +297,28 @@ k_adj_pair64_tile(int64_t n, int64_t nb, const double *__restrict__ geo,
     __syncthreads();
     if (!owner || !wave_live) return;
 #pragma unroll
-    for (int g = 0; g < GW; ++g)
+    for (int m = 0; m < 4; ++m) {
+        const int q = m;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int q = 4 * g + m;
-#pragma unroll
-            for (int v = 0; v < kBlock / 64; ++v) {
-                const double *o = mir[v] + pl * MS + 16 * g;
-                aU[q] += o[m];
-                aD[3 * q] += o[4 + 3 * m];
-                aD[3 * q + 1] += o[5 + 3 * m];
-                aD[3 * q + 2] += o[6 + 3 * m];
-            }
+        for (int v = 0; v < kBlock / 64; ++v) {
+            const double *o = mir[v] + pl * MS;
+            aU[q] += o[m];
+            aD[3 * q] += o[4 + 3 * m];
+            aD[3 * q + 1] += o[5 + 3 * m];
+            aD[3 * q + 2] += o[6 + 3 * m];
         }
+    }
     const double iV = 1.0 / rk[R_V];
     const double b00 = rk[R_B] * iV, b01 = rk[R_B + 1] * iV, b02 = rk[R_B + 2] * iV;
     const double b11 = rk[R_B + 3] * iV, b12 = rk[R_B + 4] * iV, b22 = rk[R_B + 5] * iV;
+    double *o = R + (i * G + g0) * 16;
 #pragma unroll
-    for (int g = 0; g < GW; ++g) {
-        double *o = R + (i * G + g0 + g) * 16;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int q = 4 * g + m;
-            o[m] = li(q) + aU[q];
-            o[4 + 3 * m + 0] = b00 * aD[3 * q] + b01 * aD[3 * q + 1] + b02 * aD[3 * q + 2];
-            o[4 + 3 * m + 1] = b01 * aD[3 * q] + b11 * aD[3 * q + 1] + b12 * aD[3 * q + 2];
-            o[4 + 3 * m + 2] = b02 * aD[3 * q] + b12 * aD[3 * q + 1] + b22 * aD[3 * q + 2];
-        }
+    for (int m = 0; m < 4; ++m) {
+        const int q = m;
+        o[m] = li(q) + aU[q];
+        o[4 + 3 * m + 0] = b00 * aD[3 * q] + b01 * aD[3 * q + 1] + b02 * aD[3 * q + 2];
+        o[4 + 3 * m + 1] = b01 * aD[3 * q] + b11 * aD[3 * q + 1] + b12 * aD[3 * q + 2];
+        o[4 + 3 * m + 2] = b02 * aD[3 * q] + b12 * aD[3 * q + 1] + b22 * aD[3 * q + 2];
     }
 }
 
@@ -895,75 +616,39 @@ __global__ __launch_bounds__(kBlock) void k_adj_inject(int32_t S, int G,
     }
 }
 
-// Groups per wave of the adjoint pair pass.  Its per-group state is three
-// times the forward's, so one group per wave wins here (G = 3: 239 VGPRs and
-// 2 waves per SIMD, against occupancy 1 with all groups; the pass is 1.5x
-// faster).
-#ifndef RT_ADJ_GW
-#define RT_ADJ_GW 1
-#endif
-// Lanes per particle of the adjoint pair pass and of the transposed gradient
-// (1, 2 or 4).  On the 128^3 adjoint workload 4 lanes took the transposed
-// gradient from 4.2 to about 2 ms per step (backward 337 -> 292 ms); the pair
-// pass gains little (one group per wave already keeps its records in cache).
-#ifndef RT_ADJ_Q
-#define RT_ADJ_Q 4
-#endif
+// Lanes per particle of the transposed gradient (1, 2 or 4): on the 128^3
+// adjoint workload 4 lanes took it from 4.2 to about 2 ms per step.
 #ifndef RT_ADJ_GRAD_Q
 #define RT_ADJ_GRAD_Q 4
 #endif
-constexpr int kAQ = RT_ADJ_Q, kAGQ = RT_ADJ_GRAD_Q;
+constexpr int kAGQ = RT_ADJ_GRAD_Q;
 
 template <int G>
 void launch_adjoint64(rt_ctx *ctx, const double *UD, const double *Uung, const double *lam_next,
                       double *lam2, double *R, double *lam, const double *dt) {
-    const int64_t n = ctx->p.n, nb = (n + kBlock - 1) / kBlock;
+    const int64_t n = ctx->p.n;
     hipStream_t st = ctx->stream;
     k_adj_guard64<G><<<nblk(n * G), kBlock, 0, st>>>(n, Uung, lam_next, lam2, ctx->p.c_red);
-    constexpr int GW = (RT_ADJ_GW == 0 || G % RT_ADJ_GW != 0) ? G : RT_ADJ_GW;
-    const int64_t np = (n + kBlock / kAQ - 1) / (kBlock / kAQ);
-    const double2 *tab = (const double2 *)ctx->hll_table;
-    const bool iva = ctx->surfaces == RT_IVANOVA;
-    const bool hll_tile = RT_ADJ_TILE_HLL != 0 && ctx->solver == RT_HLL && G <= 3;
-    const bool iva_tile = RT_ADJ_TILE_IVA != 0 && iva && G <= 3;
-    if ((ctx->solver == RT_GLF || hll_tile) && (!iva || iva_tile) && ctx->task) {
-        // the adjoint of the tile transport (in-tile pairs once)
+    {
+        // the adjoint of the tile transport (in-tile pairs once), a group a block
         const int64_t nt = (n + kTile - 1) / kTile;
+        const bool hll = ctx->solver == RT_HLL, iva = ctx->surfaces == RT_IVANOVA;
         const bool off32 = (uint64_t)n * 128u * G < (uint64_t(1) << 32);
 #define RT_ADJ_TILE_LAUNCH(OFF32_, HLL_, IVA_)                                                  \
-    k_adj_pair64_tile<G, GW, OFF32_, HLL_, IVA_>                                                \
-        <<<(unsigned)xcd_grid(nt * (G / GW)), kBlock, 0, st>>>(                                 \
-            n, nt, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, lam2, dt,              \
-            ctx->p.c_red, ctx->p.box, R, tab)
+    k_adj_pair64_tile<OFF32_, HLL_, IVA_><<<(unsigned)xcd_grid(nt * G), kBlock, 0, st>>>(       \
+        n, nt, G, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, lam2, dt,               \
+        ctx->p.c_red, ctx->p.box, R, (const double2 *)ctx->hll_table)
 #define RT_ADJ_TILE_LAUNCH_S(HLL_, IVA_)                                                        \
     do {                                                                                        \
         if (off32) RT_ADJ_TILE_LAUNCH(true, HLL_, IVA_);                                        \
         else RT_ADJ_TILE_LAUNCH(false, HLL_, IVA_);                                             \
     } while (0)
-        if (hll_tile || iva_tile) {
-            if constexpr (G <= 3) {
-                if (hll_tile && iva_tile) RT_ADJ_TILE_LAUNCH_S(true, true);
-                else if (hll_tile) RT_ADJ_TILE_LAUNCH_S(true, false);
-                else RT_ADJ_TILE_LAUNCH_S(false, true);
-            }
-        } else {
-            RT_ADJ_TILE_LAUNCH_S(false, false);
-        }
+        if (hll && iva) RT_ADJ_TILE_LAUNCH_S(true, true);
+        else if (hll) RT_ADJ_TILE_LAUNCH_S(true, false);
+        else if (iva) RT_ADJ_TILE_LAUNCH_S(false, true);
+        else RT_ADJ_TILE_LAUNCH_S(false, false);
 #undef RT_ADJ_TILE_LAUNCH_S
 #undef RT_ADJ_TILE_LAUNCH
-    } else {
-#define RT_ADJ_PAIR_LAUNCH(HLL_, IVA_)                                                          \
-    k_adj_pair64<G, GW, kAQ, HLL_, IVA_, (HLL_ && kAdjHllOwn)><<<(unsigned)xcd_grid(np * (G / GW)), kBlock, 0, st>>>( \
-        n, np, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, lam2, dt, ctx->p.c_red,      \
-        ctx->p.box, R, tab, ctx->ivan)
-    if (ctx->solver == RT_HLL) {
-        if (iva) RT_ADJ_PAIR_LAUNCH(true, true);
-        else RT_ADJ_PAIR_LAUNCH(true, false);
-    } else {
-        if (iva) RT_ADJ_PAIR_LAUNCH(false, true);
-        else RT_ADJ_PAIR_LAUNCH(false, false);
-    }
-#undef RT_ADJ_PAIR_LAUNCH
     }
     if constexpr (G <= 4 && kAGQ == 4) {
         if (ctx->aoff) {

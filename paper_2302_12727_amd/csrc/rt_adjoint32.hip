@@ -1,5 +1,5 @@
 // Compensated-FP32 adjoint of one RT step: the passes of the FP64 adjoint
-// (guard VJP, own-side pair VJPs, transpose of the gradient) with FP32 pair
+// (guard VJP, pair VJPs, transpose of the gradient) with FP32 pair
 // arithmetic; the state cotangent of every particle is summed with Kahan
 // compensation.
 #include "rt_pair32.h"
@@ -27,30 +27,57 @@ __global__ __launch_bounds__(kBlock) void k_adj_guard32(int64_t n, const float *
     for (int m = 0; m < 4; ++m) lam2[4 * t + m] = l[m];
 }
 
-// A wave owns 64 particles and GW of the G groups (G/GW waves per 64
-// particles), as in the FP64 pair pass.  HLL and IVA as in the FP64 pair
-// pass (the FP32 table, the FP32 Ivanova surfaces of the FP32C transport).
-template <int G, int GW, bool HLL = false, bool IVA = false>
-__global__ __launch_bounds__(kBlock) void k_adj_pair32(
-    int64_t n, int64_t nb, const float *__restrict__ geo32, const double *__restrict__ geo,
-    const int32_t *__restrict__ nbr, const int64_t *__restrict__ wave_base,
-    const int32_t *__restrict__ n_nbr, const float *__restrict__ UD,
-    const float *__restrict__ lam2, const double *__restrict__ dtp, double c, double box,
-    float *__restrict__ R, const float2 *__restrict__ hll = nullptr,
-    const double *__restrict__ ivan = nullptr) {
-    static_assert(G % GW == 0, "group slices must tile the groups");
-    constexpr int NS = G / GW, NQ = 4 * GW;
+// Exchange among the 4 lanes of a quad: v[u] of lane m becomes v[m] of lane u.
+__device__ __forceinline__ void quad_transpose(float (&v)[4], int sub) {
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const float t = quad_xor<1>((sub & 1) ? v[r] : v[r + 1]);
+        if (sub & 1) v[r] = t;
+        else v[r + 1] = t;
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const float t = quad_xor<2>((sub & 2) ? v[r] : v[r + 2]);
+        if (sub & 2) v[r] = t;
+        else v[r + 2] = t;
+    }
+}
+
+// Pass B (as in the FP64 adjoint; every pair from both its particles), one
+// group a block.  A quad of lanes shares a particle: each pulls back every
+// fourth of its pairs, then the quad exchanges the four pairs' cotangents and
+// lane m sums component m (its state cotangent compensated) over all of them in
+// list order, with the operations of one lane per particle, so with the same
+// bits.  With one lane per particle a wave reached 64 neighbourhoods, one row
+// after the other, and waited for memory: 377 us for 4 groups of 58 thousand
+// clustered particles, now 262; the 100^3 lattice, 3 groups, is bound by its
+// vector instructions (whole backward step 2.94 -> 2.82 ms, HLL 4.65 -> 4.44).
+// The geometry rows are in flight one iteration ahead, a group's rows across
+// the pair geometry.  (On the tiles, pairs inside evaluated once, the FP32 sums,
+// and with them dL, round differently, and it was no faster: 300 us.)
+// HLL and IVA as in the FP64 pass (the FP32 table, the FP32 Ivanova surfaces of
+// the FP32C transport).
+template <bool HLL, bool IVA>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void
+k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
+                  const double *__restrict__ geo, const int32_t *__restrict__ nbr,
+                  const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_nbr,
+                  const float *__restrict__ UD, const float *__restrict__ lam2,
+                  const double *__restrict__ dtp, double c, double box, float *__restrict__ R,
+                  const float2 *__restrict__ hll, const double *__restrict__ ivan) {
+    static_assert(kBlock == 256, "a block of 4 waves x 16 particles per column block");
     __shared__ float stage[kBlock / 64][64 * kStage32];
-    const int64_t bg = xcd_block(nb * NS);
-    if (bg >= nb * NS) return;
-    const int64_t blk = bg / NS;
-    const int g0 = (int)(bg - blk * NS) * GW;
+    const int64_t bg = xcd_block(nb * G);
+    if (bg >= nb * G) return;
+    const int64_t blk = bg / G;
+    const int g0 = (int)(bg - blk * G);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t i = blk * kBlock + threadIdx.x;
+    const int sub = lane & 3;
+    const int pl = 16 * wv + (lane >> 2);       // the lane's particle in the column block
+    const int64_t i = blk * 64 + pl;
     const bool active = i < n;
     const int64_t ic = active ? i : n - 1;
-    const int64_t w = i >> 6;
-    const bool wave_live = (w << 6) < n;
+    const bool wave_live = blk * 64 + 16 * wv < n;   // wave-uniform
     const double ibox = 1.0 / box;
     const float cf = (float)c, c2 = (float)(c * c), ic2 = (float)(1.0 / (c * c));
     const float dtf = (float)dtp[0];
@@ -70,40 +97,52 @@ __global__ __launch_bounds__(kBlock) void k_adj_pair32(
 #pragma unroll
     for (int a = 0; a < 6; ++a) Bk[a] = rk[F_B + a];
     const float dtVk = (float)(dtp[0] / geo[(int64_t)kRec * ic + R_V]);
-    float Ui[NQ], Di[NQ * 3], Li[NQ];
+    float Ui[4], Di[12], Li[4];
+    const float *ro = UD + (ic * G + g0) * 16;
 #pragma unroll
-    for (int g = 0; g < GW; ++g) {
-        const float *r = UD + (ic * G + g0 + g) * 16;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            Ui[4 * g + m] = r[m];
-            Di[3 * (4 * g + m) + 0] = r[4 + 3 * m];
-            Di[3 * (4 * g + m) + 1] = r[5 + 3 * m];
-            Di[3 * (4 * g + m) + 2] = r[6 + 3 * m];
-            Li[4 * g + m] = lam2[(ic * G + g0 + g) * 4 + m];
-        }
+    for (int m = 0; m < 4; ++m) {
+        Ui[m] = ro[m];
+        Di[3 * m + 0] = ro[4 + 3 * m];
+        Di[3 * m + 1] = ro[5 + 3 * m];
+        Di[3 * m + 2] = ro[6 + 3 * m];
+        Li[m] = lam2[(ic * G + g0) * 4 + m];
     }
-    Kahan aU[NQ];
-    float aD[NQ * 3];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        aU[q].s = aU[q].c = 0.0f;
-        aD[3 * q] = aD[3 * q + 1] = aD[3 * q + 2] = 0.0f;
-    }
+    // component sub's sums
+    Kahan aU{0.0f, 0.0f};
+    float aD[3] = {0.0f, 0.0f, 0.0f};
     if (wave_live) {
-        const int64_t base = wave_base[w] + lane;
-        const int32_t kmax = (int32_t)((wave_base[w + 1] - wave_base[w]) >> 6);
+        const int64_t base = wave_base[blk] + pl;   // the particle's column in the table
         const int32_t nn = active ? n_nbr[i] : 0;
-        // the next iteration's neighbour index is loaded one iteration ahead
-        int32_t jn = 0 < nn ? nbr[base] : (int32_t)ic;
-        for (int32_t k = 0; k < kmax; ++k) {
+        int32_t kmax = nn;                          // the longest list of the wave
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, 64));
+        // the next iteration's neighbour, and its geometry row, are in flight
+        // while this one is evaluated
+        int32_t jn = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
+        int64_t row[4];
+        float4 v[4];
+        {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
+            load_rows32(geo32, row, lane, v);
+        }
+        for (int32_t kk = 0; kk < kmax; kk += 4) {
+            const int32_t k = kk + sub;
             const bool valid = k < nn;
             const int32_t j = jn;
-            jn = k + 1 < nn ? nbr[base + 64 * (int64_t)(k + 1)] : (int32_t)ic;
-            int64_t row[4];
+            // (slot 0 of the block's table exists once kmax > 0: no branch
+            // around the load, whose wait would then be a full one)
+            const int32_t jl = nbr[base + 64 * (int64_t)(k + 4 < nn ? k + 4 : 0)];
+            jn = k + 4 < nn ? jl : (int32_t)ic;
+            store_rows32(v, sb, lane);          // the geometry rows
+            // the group's record rows and cotangents in one round trip
+            {
+                int64_t rowg[4];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) row[m] = __shfl(j, 16 * m + (lane >> 2), 64);
-            stage_rows32(geo32, row, sb, lane);
+                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g0;
+                load_rows32(UD, rowg, lane, v);
+            }
+            const float4 Ll = *reinterpret_cast<const float4 *>(lam2 + ((int64_t)j * G + g0) * 4);
             PairGeo32 pg;
             pair_geometry32(pkx, pky, pkz, iHk, hk, Bk, sb + lane * kStage32, box, ibox, pg);
             if (IVA) {                          // the same pair with the Ivanova surface
@@ -117,104 +156,103 @@ __global__ __launch_bounds__(kBlock) void k_adj_pair32(
             }
             const float dtVl = dtf * rcp32(sb[lane * kStage32 + F_V]);
             const bool use = valid && pg.An > 0.0f;
+            // the stages in program order (see the transport)
+            __builtin_amdgcn_sched_barrier(0);
+            store_rows32(v, sb, lane);          // the record rows
+            {                                   // the next iteration's geometry rows
 #pragma unroll
-            for (int g = 0; g < GW; ++g) {
-                int64_t rowg[4];
+                for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
+                load_rows32(geo32, row, lane, v);
+            }
+            float Rl[16];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g0 + g;
-                stage_rows32(UD, rowg, sb, lane);
-                float Rl[16];
+            for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage32 + q];
+            float qLp[4], qRp[4], qL[4], qR[4];
+            bool own_slope[4];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage32 + q];
-                const float4 Ll =
-                    *reinterpret_cast<const float4 *>(lam2 + ((int64_t)j * G + g0 + g) * 4);
-                float qLp[4], qRp[4], qL[4], qR[4];
-                bool own_slope[4];
+            for (int m = 0; m < 4; ++m) {
+                const float dk = Di[3 * m] * pg.sx + Di[3 * m + 1] * pg.sy + Di[3 * m + 2] * pg.sz;
+                const float dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
+                const float mm = minmod32(dk, dl);
+                own_slope[m] = (dk * dl > 0.0f) && (fabsf(dk) <= fabsf(dl));
+                qLp[m] = qL[m] = Ui[m] + pg.fk * mm;
+                qRp[m] = qR[m] = Rl[m] - pg.fl * mm;
+            }
+            guard32(qL[0], qL[1], qL[2], qL[3], cf);
+            guard32(qR[0], qR[1], qR[2], qR[3], cf);
+            const float Llm[4] = {Ll.x, Ll.y, Ll.z, Ll.w};
+            float nu[4], tL[4], tR[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) nu[m] = 0.5f * (dtVl * Llm[m] - dtVk * Li[m]);
+            m1_flux32_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, nu, tL);
+            m1_flux32_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, nu, tR);
+            if constexpr (HLL) {
+                const float iAn = pg.An > 0.0f ? rcp32(pg.An) : 0.0f;
+                float loL, hiL, loR, hiR, w1, w2, w3;
+                hll_speeds32(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2, hll,
+                             loL, hiL);
+                hll_speeds32(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2, hll,
+                             loR, hiR);
+                hll_weights32(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
+                float FL[4], FR[4];
+                m1_flux32(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, FL);
+                m1_flux32(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, FR);
+                float S1 = 0.0f, S2 = 0.0f, S3 = 0.0f;   // m . (F_L, F_R, U_R - U_L)
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    const int q = 4 * g + m;
-                    const float dk = Di[3 * q] * pg.sx + Di[3 * q + 1] * pg.sy + Di[3 * q + 2] * pg.sz;
-                    const float dl = Rl[4 + 3 * m] * pg.sx + Rl[5 + 3 * m] * pg.sy + Rl[6 + 3 * m] * pg.sz;
-                    const float mm = minmod32(dk, dl);
-                    own_slope[m] = (dk * dl > 0.0f) && (fabsf(dk) <= fabsf(dl));
-                    qLp[m] = qL[m] = Ui[q] + pg.fk * mm;
-                    qRp[m] = qR[m] = Rl[m] - pg.fl * mm;
+                    S1 += nu[m] * FL[m];
+                    S2 += nu[m] * FR[m];
+                    S3 += nu[m] * (qR[m] - qL[m]);
+                    tL[m] = 2.0f * (w1 * tL[m] - w3 * nu[m]);
+                    tR[m] = 2.0f * (w2 * tR[m] + w3 * nu[m]);
                 }
-                guard32(qL[0], qL[1], qL[2], qL[3], cf);
-                guard32(qR[0], qR[1], qR[2], qR[3], cf);
-                const float Llm[4] = {Ll.x, Ll.y, Ll.z, Ll.w};
-                float nu[4], tL[4], tR[4];
+                float gloL, ghiL, gloR, ghiR;
+                hll_weights32_vjp(loL, hiL, loR, hiR, pg.An, 2.0f * S1, 2.0f * S2, 2.0f * S3,
+                                  gloL, ghiL, gloR, ghiR);
+                hll_speeds32_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2,
+                                 hll, gloL, ghiL, tL);
+                hll_speeds32_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2,
+                                 hll, gloR, ghiR, tR);
+            } else {
+                const float dis = cf * pg.An;
 #pragma unroll
-                for (int m = 0; m < 4; ++m) nu[m] = 0.5f * (dtVl * Llm[m] - dtVk * Li[4 * g + m]);
-                m1_flux32_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, nu, tL);
-                m1_flux32_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, nu, tR);
-                if constexpr (HLL) {
-                    const float iAn = pg.An > 0.0f ? rcp32(pg.An) : 0.0f;
-                    float loL, hiL, loR, hiR, w1, w2, w3;
-                    hll_speeds32(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2, hll,
-                                 loL, hiL);
-                    hll_speeds32(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2, hll,
-                                 loR, hiR);
-                    hll_weights32(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
-                    float FL[4], FR[4];
-                    m1_flux32(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, FL);
-                    m1_flux32(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, c2, ic2, FR);
-                    float S1 = 0.0f, S2 = 0.0f, S3 = 0.0f;   // m . (F_L, F_R, U_R - U_L)
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        S1 += nu[m] * FL[m];
-                        S2 += nu[m] * FR[m];
-                        S3 += nu[m] * (qR[m] - qL[m]);
-                        tL[m] = 2.0f * (w1 * tL[m] - w3 * nu[m]);
-                        tR[m] = 2.0f * (w2 * tR[m] + w3 * nu[m]);
-                    }
-                    float gloL, ghiL, gloR, ghiR;
-                    hll_weights32_vjp(loL, hiL, loR, hiR, pg.An, 2.0f * S1, 2.0f * S2, 2.0f * S3,
-                                      gloL, ghiL, gloR, ghiR);
-                    hll_speeds32_vjp(qL[0], qL[1], qL[2], qL[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2,
-                                     hll, gloL, ghiL, tL);
-                    hll_speeds32_vjp(qR[0], qR[1], qR[2], qR[3], pg.Ax, pg.Ay, pg.Az, iAn, cf, ic2,
-                                     hll, gloR, ghiR, tR);
-                } else {
-                    const float dis = cf * pg.An;
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        tL[m] += dis * nu[m];
-                        tR[m] -= dis * nu[m];
-                    }
-                }
-                guard32_vjp(qLp, tL, cf);
-                guard32_vjp(qRp, tR, cf);
-                if (use) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const int q = 4 * g + m;
-                        aU[q].add(tL[m]);
-                        const float lm = own_slope[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0f;
-                        aD[3 * q] += lm * pg.sx;
-                        aD[3 * q + 1] += lm * pg.sy;
-                        aD[3 * q + 2] += lm * pg.sz;
-                    }
+                for (int m = 0; m < 4; ++m) {
+                    tL[m] += dis * nu[m];
+                    tR[m] -= dis * nu[m];
                 }
             }
+            guard32_vjp(qLp, tL, cf);
+            guard32_vjp(qRp, tR, cf);
+            float lm[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) lm[m] = own_slope[m] ? pg.fk * tL[m] - pg.fl * tR[m] : 0.0f;
+            // the quad's four pairs in list order, component sub
+            quad_transpose(tL, sub);
+            quad_transpose(lm, sub);
+            auto add = [&](int on, float t, float l, float x, float y, float z) {
+                if (on) {
+                    aU.add(t);
+                    aD[0] += l * x;
+                    aD[1] += l * y;
+                    aD[2] += l * z;
+                }
+            };
+            add(quad_bcast<0>((int)use), tL[0], lm[0], quad_bcast<0>(pg.sx), quad_bcast<0>(pg.sy), quad_bcast<0>(pg.sz));
+            add(quad_bcast<1>((int)use), tL[1], lm[1], quad_bcast<1>(pg.sx), quad_bcast<1>(pg.sy), quad_bcast<1>(pg.sz));
+            add(quad_bcast<2>((int)use), tL[2], lm[2], quad_bcast<2>(pg.sx), quad_bcast<2>(pg.sy), quad_bcast<2>(pg.sz));
+            add(quad_bcast<3>((int)use), tL[3], lm[3], quad_bcast<3>(pg.sx), quad_bcast<3>(pg.sy), quad_bcast<3>(pg.sz));
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     if (!active) return;
     const float iV = rcp32(rk[F_V]);
     const float b00 = Bk[0] * iV, b01 = Bk[1] * iV, b02 = Bk[2] * iV;
     const float b11 = Bk[3] * iV, b12 = Bk[4] * iV, b22 = Bk[5] * iV;
-#pragma unroll
-    for (int g = 0; g < GW; ++g) {
-        float *o = R + (i * G + g0 + g) * 16;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int q = 4 * g + m;
-            o[m] = (float)((double)Li[q] + aU[q].value());
-            o[4 + 3 * m + 0] = b00 * aD[3 * q] + b01 * aD[3 * q + 1] + b02 * aD[3 * q + 2];
-            o[4 + 3 * m + 1] = b01 * aD[3 * q] + b11 * aD[3 * q + 1] + b12 * aD[3 * q + 2];
-            o[4 + 3 * m + 2] = b02 * aD[3 * q] + b12 * aD[3 * q + 1] + b22 * aD[3 * q + 2];
-        }
-    }
+    float *o = R + (i * G + g0) * 16;
+    o[sub] = (float)((double)(sub == 0 ? Li[0] : sub == 1 ? Li[1] : sub == 2 ? Li[2] : Li[3]) + aU.value());
+    o[4 + 3 * sub + 0] = b00 * aD[0] + b01 * aD[1] + b02 * aD[2];
+    o[4 + 3 * sub + 1] = b01 * aD[0] + b11 * aD[1] + b12 * aD[2];
+    o[4 + 3 * sub + 2] = b02 * aD[0] + b12 * aD[1] + b22 * aD[2];
 }
 
 // Q lanes share a particle, each taking every Q-th neighbour slot; the
@@ -346,12 +384,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad32(
     }
 }
 
-// Groups per wave of the pair pass (0: all G); one group per wave keeps the
-// pass at 135 VGPRs and 3 waves per SIMD for any G (all four groups of a
-// G = 4 set in one wave need 276 registers: 1 wave per SIMD).
-#ifndef RT_ADJ32_GW
-#define RT_ADJ32_GW 1
-#endif
 // Lanes per particle of the FP32 transposed gradient (1, 2 or 4); 4 took the
 // FP32C backward of the 128^3 adjoint workload from 188 to 166 ms.
 #ifndef RT_ADJ32_GRAD_Q
@@ -362,15 +394,14 @@ constexpr int kAGQ32 = RT_ADJ32_GRAD_Q;
 template <int G>
 void launch(rt_ctx *ctx, const float *UD, const float *Uung, const float *lam_next, float *lam2,
             float *R, float *lam, const double *dt) {
-    const int64_t n = ctx->p.n, nb = (n + kBlock - 1) / kBlock;
+    const int64_t n = ctx->p.n, nt = ctx->nwaves;
     hipStream_t st = ctx->stream;
-    constexpr int GW = (RT_ADJ32_GW == 0 || G % RT_ADJ32_GW != 0) ? G : RT_ADJ32_GW;
     k_adj_guard32<G><<<nblk(n * G), kBlock, 0, st>>>(n, Uung, lam_next, lam2, (float)ctx->p.c_red);
     const float2 *tab = (const float2 *)ctx->hll_table32;
     const bool iva = ctx->surfaces == RT_IVANOVA;
 #define RT_ADJ32_PAIR_LAUNCH(HLL_, IVA_)                                                       \
-    k_adj_pair32<G, GW, HLL_, IVA_><<<(unsigned)xcd_grid(nb * (G / GW)), kBlock, 0, st>>>(    \
-        n, nb, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, lam2, dt,       \
+    k_adj_pair32<HLL_, IVA_><<<(unsigned)xcd_grid(nt * G), kBlock, 0, st>>>(              \
+        n, nt, G, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, lam2, dt,    \
         ctx->p.c_red, ctx->p.box, R, tab, ctx->ivan)
     if (ctx->solver == RT_HLL) {
         if (iva) RT_ADJ32_PAIR_LAUNCH(true, true);

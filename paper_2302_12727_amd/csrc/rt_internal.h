@@ -216,6 +216,17 @@ __device__ __forceinline__ void quad_sum(T &v) {
     if constexpr (Q >= 4) v += quad_xor<2>(v);
 }
 
+// quad broadcast: every lane of a quad takes lane L's value (DPP quad_perm)
+template <int L>
+__device__ __forceinline__ float quad_bcast(float v) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), L * 0x55, 0xf, 0xf, false));
+}
+template <int L>
+__device__ __forceinline__ int quad_bcast(int v) {
+    return __builtin_amdgcn_mov_dpp(v, L * 0x55, 0xf, 0xf, false);
+}
+
 __device__ __forceinline__ double kern_w(double q) {
     double a = fmax(1.0 - q, 0.0);
     double b = fmax(0.5 - q, 0.0);

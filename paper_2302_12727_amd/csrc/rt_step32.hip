@@ -113,17 +113,6 @@ __global__ __launch_bounds__(kBlock) void k_gradient32(
 // four floats as one 16-byte access (a native vector: copies stay in registers)
 typedef float fvec4 __attribute__((ext_vector_type(4)));
 
-// quad broadcast: every lane of a quad takes lane L's value (DPP quad_perm)
-template <int L>
-__device__ __forceinline__ float quad_bcast(float v) {
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), L * 0x55, 0xf, 0xf, false));
-}
-template <int L>
-__device__ __forceinline__ int quad_bcast(int v) {
-    return __builtin_amdgcn_mov_dpp(v, L * 0x55, 0xf, 0xf, false);
-}
-
 // Gradient from the block's neighbour union in FP32 (compensated mode, up to
 // 4 groups; see k_gradient64u): the union's FP32 states (16G bytes a row) and
 // FP64 positions are staged in LDS once per block of 64 particles, and every

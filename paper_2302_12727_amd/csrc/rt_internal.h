@@ -59,12 +59,10 @@ enum { R_X = 0, R_IH = 3, R_H = 4, R_V = 5, R_B = 6 };
 // and rounded once), then 1/H, h, Bv (6) and V in FP32.
 enum { F_IH = 6, F_H = 7, F_B = 8, F_V = 14, F_BIN = 15, F_REC = 16 };
 
-// A launch of a tile transport over more than the 3 groups a wave's registers
-// hold: `count` slices of its G groups from group `first` on, of `groups`.  All
-// groups of a tile go in ceil(groups / 3) slices, of 3 and of 2; the pair
-// geometry is computed once per slice.  (Two-sided, every pair evaluated by
-// both its particles, the FP32C step of 150 thousand clustered particles in 4
-// groups took 561 us, in two slices 488 us.)
+// A launch of a transport over more than the 3 groups a wave's registers hold:
+// `count` slices of its G groups from group `first` on, of `groups`.  All groups
+// of a particle go in ceil(groups / 3) slices, of 3 and of 2; the pair geometry
+// is computed once per slice.
 struct Slices {
     int groups = 0, first = 0, count = 0;
 };

@@ -280,6 +280,358 @@ k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const doub
     if (chk != chk) atomicOr(status, ST_NONFINITE);
 }
 
+// FP32C transport of more than 3 groups, in slices (GLF or HLL, Hopkins or
+// Ivanova surfaces, BIN: a tick of the individual time steps, all as in
+// k_transport32_tile): every pair is evaluated by both its particles, whose
+// sums are then those of their own lists in list order.  On the tiles (pairs
+// inside once) 4 groups of 150 thousand clustered particles took 488 us a
+// step, but the states then round elsewhere, and the photon totals of a few
+// thousand particles with them (1e-9).  A slice of 2 or 3 groups fits 168
+// registers and 3 waves per SIMD, at the price of the pair geometry once per
+// slice: 557 us a step with the 4 groups in one wave, now 503, the same bits.
+template <int G, bool HLL, bool BIN, bool IVA>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void k_transport32(
+    int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32, const double *__restrict__ geo,
+    const int32_t *__restrict__ nbr, const int64_t *__restrict__ wave_base,
+    const int32_t *__restrict__ n_nbr, const float *__restrict__ UDall,
+    const double *__restrict__ dtp, double c, double box, float *__restrict__ Uout,
+    double *__restrict__ partials, unsigned long long *__restrict__ counts,
+    float *__restrict__ Uung, int32_t *__restrict__ status,
+    const float2 *__restrict__ hll, const double *__restrict__ ivan, int64_t tick,
+    double *__restrict__ accm, const uint8_t *__restrict__ binm) {
+    // PIPE: the next stage's rows in flight during each evaluation (GLF; the
+    // HLL instantiation has no registers left for them)
+    constexpr bool PIPE = !HLL;
+    constexpr int NQ = 4 * G, Q = 4, PW = 64 / Q, PB = kBlock / Q;
+    __shared__ float stage[kBlock / 64][64 * kStage32];
+    __shared__ double smem[(kBlock / 64) * 2 * G];
+    __shared__ unsigned long long scnt[4];
+    // the block's particles and groups g0 .. g0 + G
+    const int GT = sl.groups;
+    const int64_t bg = xcd_block(nb * sl.count);
+    if (bg >= nb * sl.count) return;            // whole block
+    const int64_t blk = bg / sl.count;
+    const int g0 = sl.first + (int)(bg - blk * sl.count) * G;
+    const float *UD = UDall + 16 * g0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int sub = lane % Q;
+    const int64_t i0 = blk * PB + wv * PW;      // first particle of the wave
+    const int64_t i = i0 + lane / Q;
+    const bool active = i < n;
+    const bool owner = active && sub == 0;
+    const int64_t ic = active ? i : n - 1;
+    const int64_t w = i0 >> 6;
+    const bool wave_live = i0 < n;
+    const double ibox = 1.0 / box;
+    const float cf = (float)c, c2 = (float)(c * c), ic2 = (float)(1.0 / (c * c)), hc = 0.5f * cf;
+    if (threadIdx.x < 4) scnt[threadIdx.x] = 0;
+    float *sb = stage[wv];
+
+    const float *rk = geo32 + (int64_t)F_REC * ic;
+    const double *xk = reinterpret_cast<const double *>(rk);
+    const double pkx = xk[0], pky = xk[1], pkz = xk[2];
+    const float iHk = rk[F_IH], hk = rk[F_H];
+    float gk[3] = {0.0f, 0.0f, 0.0f};   // IVA: own kernel-gradient sum
+    if (IVA) {
+        gk[0] = (float)ivan[4 * ic];
+        gk[1] = (float)ivan[4 * ic + 1];
+        gk[2] = (float)ivan[4 * ic + 2];
+    }
+    float Bk[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) Bk[a] = rk[F_B + a];
+    float Ui[NQ], Di[NQ * 3];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const float *r = UD + (ic * GT + g) * 16;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            Ui[4 * g + m] = r[m];
+            Di[3 * (4 * g + m) + 0] = r[4 + 3 * m];
+            Di[3 * (4 * g + m) + 1] = r[5 + 3 * m];
+            Di[3 * (4 * g + m) + 2] = r[6 + 3 * m];
+        }
+    }
+    Kahan acc[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q].s = acc[q].c = 0.0f;
+    int cE = 0, cF = 0;
+    // time bins: this particle ends a step in this tick (ends), or some pair of
+    // its neighbourhood does (touched)
+    const int64_t t1 = tick + 1;
+    const int32_t bk = BIN ? (int32_t)geo[(int64_t)kRec * ic + 12] : 0;
+    const bool ends = !BIN || (t1 & ((int64_t(1) << bk) - 1)) == 0;
+    const int32_t bm = (BIN && binm) ? (int32_t)binm[ic] : 0;
+    const bool touched = !BIN || (t1 & ((int64_t(1) << bm) - 1)) == 0;
+
+    if (wave_live) {
+        const int64_t base = wave_base[w] + (i & 63);
+        const int32_t nn = (active && touched) ? n_nbr[i] : 0;
+        int32_t kmax = nn;                      // the longest list of this wave's particles
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o, 64));
+        if (BIN && __ballot(nn > 0) == 0) kmax = 0;   // no due pair in this wave
+        // Rows in flight: v holds the loads of the next stage (the geometry
+        // rows, then each group's record rows) while the current stage is
+        // evaluated from the stage buffer.  The next iteration's neighbour
+        // index is loaded one iteration ahead.
+        int32_t jc = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
+        int64_t row[4];
+        float4 v[4];
+        if constexpr (PIPE) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) row[m] = __shfl(jc, 16 * m + (lane >> 2), 64);
+            load_rows32(geo32, row, lane, v);
+        }
+        for (int32_t kk = 0; kk < kmax; kk += Q) {
+            const int32_t k = kk + sub;
+            const bool valid = k < nn;
+            const int32_t j = jc;
+            // (slot 0 of the wave's table exists once kmax > 0: no branch
+            // around the load, whose wait would then be a full one)
+            const int32_t jl = nbr[base + 64 * (int64_t)(k + Q < nn ? k + Q : 0)];
+            const int32_t jn = k + Q < nn ? jl : (int32_t)ic;
+            if constexpr (!PIPE) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) row[m] = __shfl(j, 16 * m + (lane >> 2), 64);
+                load_rows32(geo32, row, lane, v);
+            }
+            store_rows32(v, sb, lane);          // the geometry rows
+            if constexpr (PIPE) {
+                int64_t rowg[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT;
+                load_rows32(UD, rowg, lane, v);
+            }
+            const float *rl = sb + lane * kStage32;
+            // separation in FP64 from FP64 positions, rounded once
+            double xl[3];
+            {
+                // the staged row holds the three doubles as six floats
+                union { float f[2]; double d; } u;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    u.f[0] = rl[2 * a];
+                    u.f[1] = rl[2 * a + 1];
+                    xl[a] = u.d;
+                }
+            }
+            const float sx = (float)min_image(xl[0] - pkx, box, ibox);
+            const float sy = (float)min_image(xl[1] - pky, box, ibox);
+            const float sz = (float)min_image(xl[2] - pkz, box, ibox);
+            const float r = sqrt32(sx * sx + sy * sy + sz * sz);
+            float Ax, Ay, Az;
+            if (IVA) {
+                const double *gd = ivan + 4 * (int64_t)j;
+                const float gl[3] = {(float)gd[0], (float)gd[1], (float)gd[2]};
+                ivanova_surface32(sx, sy, sz, r, iHk, rk[F_V], gk, rl[F_IH], rl[F_V], gl, Ax, Ay,
+                                  Az);
+            } else {
+                const float wk = kern_wf(r * iHk);
+                const float wl = kern_wf(r * rl[F_IH]);
+                const float m00 = wk * Bk[0] + wl * rl[F_B + 0];
+                const float m01 = wk * Bk[1] + wl * rl[F_B + 1];
+                const float m02 = wk * Bk[2] + wl * rl[F_B + 2];
+                const float m11 = wk * Bk[3] + wl * rl[F_B + 3];
+                const float m12 = wk * Bk[4] + wl * rl[F_B + 4];
+                const float m22 = wk * Bk[5] + wl * rl[F_B + 5];
+                Ax = m00 * sx + m01 * sy + m02 * sz;
+                Ay = m01 * sx + m11 * sy + m12 * sz;
+                Az = m02 * sx + m12 * sy + m22 * sz;
+            }
+            const float An = sqrt32(Ax * Ax + Ay * Ay + Az * Az);
+            const float hl = rl[F_H];
+            const float ih = rcp32(hk + hl);
+            const float fk = hk * ih, fl = hl * ih;
+            bool use = valid && An > 0.0f;
+            float wkl = 1.0f;                   // time integration of this exchange
+            if (BIN) {
+                const int32_t bl = (int32_t)rl[F_BIN];
+                const int32_t bmin = bk < bl ? bk : bl;
+                use = use && (t1 & ((int64_t(1) << bmin) - 1)) == 0;
+                wkl = (float)ldexp(dtp[0], bmin);
+            }
+            const float iAn = (HLL && An > 0.0f) ? rcp32(An) : 0.0f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                // the stages in program order: each one's loads stay in
+                // flight across the evaluation of the previous one
+                if constexpr (PIPE) {
+                    __builtin_amdgcn_sched_barrier(0);
+                } else {
+                    int64_t rowg[4];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g;
+                    load_rows32(UD, rowg, lane, v);
+                }
+                store_rows32(v, sb, lane);      // group g's record rows
+                if constexpr (PIPE) {
+                    if (g + 1 < G) {
+                        int64_t rowg[4];
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g + 1;
+                        load_rows32(UD, rowg, lane, v);
+                    } else {                    // the next iteration's geometry rows
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
+                        load_rows32(geo32, row, lane, v);
+                    }
+                }
+                const float *Rl = sb + lane * kStage32;
+                float qL[4], qR[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int q = 4 * g + m;
+                    const float dk = Di[3 * q] * sx + Di[3 * q + 1] * sy + Di[3 * q + 2] * sz;
+                    const float dl = Rl[4 + 3 * m] * sx + Rl[5 + 3 * m] * sy + Rl[6 + 3 * m] * sz;
+                    const float mm = minmod32(dk, dl);
+                    qL[m] = Ui[q] + fk * mm;
+                    qR[m] = Rl[m] - fl * mm;
+                }
+                const int f1 = guard32(qL[0], qL[1], qL[2], qL[3], cf);
+                const int f2 = guard32(qR[0], qR[1], qR[2], qR[3], cf);
+                float w1 = 0.5f, w2 = 0.5f, w3 = -hc * An;   // GLF
+                if (HLL) {
+                    float loL, hiL, loR, hiR;
+                    hll_speeds32(qL[0], qL[1], qL[2], qL[3], Ax, Ay, Az, iAn, cf, ic2, hll, loL,
+                                 hiL);
+                    hll_speeds32(qR[0], qR[1], qR[2], qR[3], Ax, Ay, Az, iAn, cf, ic2, hll, loR,
+                                 hiR);
+                    hll_weights32(loL, hiL, loR, hiR, An, w1, w2, w3);
+                }
+                float FL[4], FR[4];
+                m1_flux32(qL[0], qL[1], qL[2], qL[3], Ax, Ay, Az, c2, ic2, FL);
+                m1_flux32(qR[0], qR[1], qR[2], qR[3], Ax, Ay, Az, c2, ic2, FR);
+                if (use) {
+                    cE += (f1 & 1) + (f2 & 1);
+                    cF += (f1 >> 1) + (f2 >> 1);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        acc[4 * g + m].add(wkl * (w1 * FL[m] + w2 * FR[m] + w3 * (qR[m] - qL[m])));
+                }
+            }
+            jc = jn;
+            if constexpr (PIPE) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    double av[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) av[q] = acc[q].value();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) quad_sum<Q>(av[q]);
+    double red[2 * G];
+    int gE = 0, gF = 0;
+    float chk = 0.0f;   // NaN iff an updated state is NaN or infinite
+    if (BIN && owner && !ends) {
+        // no update in this tick: keep the pending sums, count the current state
+        const double V = geo[(int64_t)kRec * i + R_V];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (touched) {
+                double *a = accm + (i * GT + g0 + g) * 4;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) a[m] += av[4 * g + m];
+            }
+            red[g] = V * (double)Ui[4 * g];
+            red[G + g] = 0.0;
+        }
+    } else if (owner) {
+        const double V = geo[(int64_t)kRec * i + R_V];
+        // the update: U - dt/V sum (global step), or U - (pending + this tick)/V
+        const double dtV = BIN ? 1.0 / V : dtp[0] / V;
+        if (BIN) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                double *a = accm + (i * GT + g0 + g) * 4;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    av[4 * g + m] += a[m];
+                    a[m] = 0.0;
+                }
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            double q0 = (double)Ui[4 * g + 0] - dtV * av[4 * g + 0];
+            double q1 = (double)Ui[4 * g + 1] - dtV * av[4 * g + 1];
+            double q2 = (double)Ui[4 * g + 2] - dtV * av[4 * g + 2];
+            double q3 = (double)Ui[4 * g + 3] - dtV * av[4 * g + 3];
+            const double Epre = q0;
+            if (Uung) {
+                float *u = Uung + (i * GT + g0 + g) * 4;
+                u[0] = (float)q0;
+                u[1] = (float)q1;
+                u[2] = (float)q2;
+                u[3] = (float)q3;
+            }
+            int f = 0;
+            if (q0 < 0.0) {
+                q0 = q1 = q2 = q3 = 0.0;
+                f = 1;
+            } else if (q0 == 0.0) {
+                q1 = q2 = q3 = 0.0;
+            } else {
+                const double F2 = q1 * q1 + q2 * q2 + q3 * q3, lim = c * q0;
+                if (F2 > lim * lim) {
+                    const double sc = lim * rsq64(F2);
+                    q1 *= sc;
+                    q2 *= sc;
+                    q3 *= sc;
+                    f = 2;
+                }
+            }
+            gE += f & 1;
+            gF += f >> 1;
+            float *o = Uout + (i * GT + g0 + g) * 4;
+            const float o0 = (float)q0, o1 = (float)q1, o2 = (float)q2, o3 = (float)q3;
+            o[0] = o0;
+            o[1] = o1;
+            o[2] = o2;
+            o[3] = o3;
+            // the unguarded state in its stored precision (NaN stays NaN
+            // through the guard; a state beyond the FP32 range rounds to inf)
+            chk = __builtin_fmaf((float)Epre, 0.0f, chk);
+            chk = __builtin_fmaf(o1, 0.0f, chk);
+            chk = __builtin_fmaf(o2, 0.0f, chk);
+            chk = __builtin_fmaf(o3, 0.0f, chk);
+            red[g] = V * (double)o0;
+            red[G + g] = (f & 1) ? -Epre * V : 0.0;
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < 2 * G; ++p) red[p] = 0.0;
+    }
+    if (chk != chk) atomicOr(status, ST_NONFINITE);
+    if (partials) {
+        const int ln = threadIdx.x & 63;
+#pragma unroll
+        for (int p = 0; p < 2 * G; ++p) {
+            double x = wave_sum(red[p]);
+            if (ln == 0) smem[wv * 2 * G + p] = x;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2 * G) {
+            double s = 0.0;
+            for (int u = 0; u < kBlock / 64; ++u) s += smem[u * 2 * G + threadIdx.x];
+            const int p = threadIdx.x;
+            partials[blk * 2 * GT + (p < G ? g0 + p : GT + g0 + p - G)] = s;
+        }
+    }
+    if (counts) {
+        int64_t v0 = wave_sum_i64(cE), v1 = wave_sum_i64(cF), v2 = wave_sum_i64(gE),
+                v3 = wave_sum_i64(gF);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) {
+            atomicAdd(&scnt[0], (unsigned long long)v0);
+            atomicAdd(&scnt[1], (unsigned long long)v1);
+            atomicAdd(&scnt[2], (unsigned long long)v2);
+            atomicAdd(&scnt[3], (unsigned long long)v3);
+        }
+        __syncthreads();
+        if (threadIdx.x < 4 && scnt[threadIdx.x]) atomicAdd(&counts[threadIdx.x], scnt[threadIdx.x]);
+    }
+}
+
 // FP32C transport with the pairs inside a tile evaluated once (GLF or HLL,
 // Hopkins or Ivanova surfaces, up to 3 groups or a slice of more): the tile
 // scheme of the FP64 transport (k_transport64_tile, the same task lists) in FP32
@@ -297,12 +649,12 @@ k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const doub
 // BIN: one tick of the individual-time-step scheme on the tiles, as in the
 // FP64 tile kernel (due pairs weighted by dt 2^min(b_k, b_l) in the
 // compensated sums, pending sums accm in FP64).
-template <int G, bool WHOLE, bool HLL, bool BIN, bool IVA>
+template <int G, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void
-k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32,
+k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                    const double *__restrict__ geo, const int32_t *__restrict__ task,
                    const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_task,
-                   const float *__restrict__ UDall, const double *__restrict__ dtp, double c,
+                   const float *__restrict__ UD, const double *__restrict__ dtp, double c,
                    double box, float *__restrict__ Uout, double *__restrict__ partials,
                    unsigned long long *__restrict__ counts, float *__restrict__ Uung,
                    int32_t *__restrict__ status, const float2 *__restrict__ hll,
@@ -317,13 +669,8 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
     __shared__ float dsh[kBlock / 64][16 * DS];
     __shared__ double smem[(kBlock / 64) * 2 * G];
     __shared__ unsigned long long scnt[4];
-    // the block's tile and its groups g0 .. g0 + G of the GT
-    const int GT = WHOLE ? G : sl.groups, nsl = WHOLE ? 1 : sl.count;
-    const int64_t bg = xcd_block(nb * nsl);
-    if (bg >= nb * nsl) return;                 // whole block: no barrier is skipped
-    const int64_t blk = WHOLE ? bg : bg / nsl;
-    const int g0 = WHOLE ? 0 : sl.first + (int)(bg - blk * nsl) * G;
-    const float *UD = UDall + 16 * g0;
+    const int64_t blk = xcd_block(nb);
+    if (blk >= nb) return;                      // whole block: no barrier is skipped
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int sub = lane & 3;
     const int64_t t0 = blk * kTile;             // the tile's first particle
@@ -357,7 +704,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
     float Ui[NQ];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const float *r = UD + (ic * GT + g) * 16;
+        const float *r = UD + (ic * G + g) * 16;
 #pragma unroll
         for (int m = 0; m < 4; ++m) Ui[4 * g + m] = r[m];
     }
@@ -369,7 +716,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
     for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-            Dsh[3 * (4 * g + sub) + a] = UD[(ic * GT + g) * 16 + 4 + 3 * sub + a];
+            Dsh[3 * (4 * g + sub) + a] = UD[(ic * G + g) * 16 + 4 + 3 * sub + a];
     wave_lds_sync32();
     Kahan acc[NQ];
 #pragma unroll
@@ -418,7 +765,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
             {
                 int64_t rowg[4];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT;
+                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G;
                 load_rows32(UD, rowg, lane, v);
             }
             const float *rl = sb + lane * kStage32;
@@ -479,7 +826,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
                 if (g + 1 < G) {
                     int64_t rowg[4];
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g + 1;
+                    for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g + 1;
                     load_rows32(UD, rowg, lane, v);
                 } else {                        // the next iteration's geometry rows
                     const int32_t jn = tn & 0x7fffffff;
@@ -549,7 +896,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (touched) {
-                double *a = accm + (i * GT + g0 + g) * 4;
+                double *a = accm + (i * G + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) a[m] += av[4 * g + m];
             }
@@ -567,7 +914,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
         if constexpr (BIN) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                double *a = accm + (i * GT + g0 + g) * 4;
+                double *a = accm + (i * G + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     av[4 * g + m] += a[m];
@@ -583,7 +930,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
             double q3 = (double)Ui[4 * g + 3] - dtV * av[4 * g + 3];
             const double Epre = q0;
             if (Uung) {
-                float *u = Uung + (i * GT + g0 + g) * 4;
+                float *u = Uung + (i * G + g) * 4;
                 u[0] = (float)q0;
                 u[1] = (float)q1;
                 u[2] = (float)q2;
@@ -607,7 +954,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
             }
             gE += f & 1;
             gF += f >> 1;
-            float *o = Uout + (i * GT + g0 + g) * 4;
+            float *o = Uout + (i * G + g) * 4;
             const float o0 = (float)q0, o1 = (float)q1, o2 = (float)q2, o3 = (float)q3;
             o[0] = o0;
             o[1] = o1;
@@ -637,7 +984,7 @@ k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ g
             double s = 0.0;
             for (int u = 0; u < kBlock / 64; ++u) s += smem[u * 2 * G + threadIdx.x];
             const int p = threadIdx.x;
-            partials[blk * 2 * GT + (p < G ? g0 + p : GT + g0 + p - G)] = s;
+            partials[blk * 2 * G + (p < G ? p : p)] = s;
         }
     }
     if (counts) {
@@ -693,31 +1040,42 @@ void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
         ctx->p.box);
 }
 
-// The tile transport of G groups of all GT, or of slices of G of them; accm: one
-// tick of the individual time steps.
-template <int G, bool WHOLE>
-void launch_tiles32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, float *Uout,
-                    double *partials, int64_t *counts, float *Uung, int64_t tick, double *accm) {
+// Up to 3 groups on the tiles; more of them in slices of G from sl.first on
+// (see k_transport32).  accm: one tick of the individual time steps.
+template <int G, bool SLICES>
+void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, float *Uout,
+                     double *partials, int64_t *counts, float *Uung, int64_t tick, double *accm) {
     const int64_t n = ctx->p.n, nt = rt_transport32_rows(n);
     const bool hll = ctx->solver == RT_HLL, iva = ctx->surfaces == RT_IVANOVA;
-    const unsigned grid = (unsigned)xcd_grid(nt * (WHOLE ? 1 : sl.count));
-#define RT_TILE32_LAUNCH(HLL_, BIN_, IVA_)                                                       \
-    k_transport32_tile<G, WHOLE, HLL_, BIN_, IVA_><<<grid, kBlock, 0, ctx->stream>>>(            \
-        n, nt, sl, ctx->geo32, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt,         \
-        ctx->p.c_red, ctx->p.box, Uout, partials, (unsigned long long *)counts, Uung,            \
-        ctx->status, (const float2 *)ctx->hll_table32, tick, accm,                               \
-        ctx->bin8 ? ctx->bin8 + n : nullptr, ctx->ivan)
-#define RT_TILE32_LAUNCH_S(HLL_, IVA_)                                                           \
+    const float2 *tab = (const float2 *)ctx->hll_table32;
+    const uint8_t *binm = ctx->bin8 ? ctx->bin8 + n : nullptr;
+    unsigned long long *cnt = (unsigned long long *)counts;
+#define RT_STEP32_LAUNCH(HLL_, BIN_, IVA_)                                                       \
     do {                                                                                         \
-        if (accm) RT_TILE32_LAUNCH(HLL_, true, IVA_);                                            \
-        else RT_TILE32_LAUNCH(HLL_, false, IVA_);                                                \
+        if constexpr (SLICES)                                                                    \
+            k_transport32<G, HLL_, BIN_, IVA_>                                                   \
+                <<<(unsigned)xcd_grid(nt * sl.count), kBlock, 0, ctx->stream>>>(                 \
+                    n, nt, sl, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD,   \
+                    dt, ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab,   \
+                    ctx->ivan, tick, accm, binm);                                                \
+        else                                                                                     \
+            k_transport32_tile<G, HLL_, BIN_, IVA_>                                              \
+                <<<(unsigned)xcd_grid(nt), kBlock, 0, ctx->stream>>>(                            \
+                    n, nt, ctx->geo32, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, \
+                    ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab, tick, \
+                    accm, binm, ctx->ivan);                                                      \
     } while (0)
-    if (hll && iva) RT_TILE32_LAUNCH_S(true, true);
-    else if (hll) RT_TILE32_LAUNCH_S(true, false);
-    else if (iva) RT_TILE32_LAUNCH_S(false, true);
-    else RT_TILE32_LAUNCH_S(false, false);
-#undef RT_TILE32_LAUNCH_S
-#undef RT_TILE32_LAUNCH
+#define RT_STEP32_LAUNCH_S(HLL_, IVA_)                                                           \
+    do {                                                                                         \
+        if (accm) RT_STEP32_LAUNCH(HLL_, true, IVA_);                                            \
+        else RT_STEP32_LAUNCH(HLL_, false, IVA_);                                                \
+    } while (0)
+    if (hll && iva) RT_STEP32_LAUNCH_S(true, true);
+    else if (hll) RT_STEP32_LAUNCH_S(true, false);
+    else if (iva) RT_STEP32_LAUNCH_S(false, true);
+    else RT_STEP32_LAUNCH_S(false, false);
+#undef RT_STEP32_LAUNCH_S
+#undef RT_STEP32_LAUNCH
 }
 
 void launch_transport32(rt_ctx *ctx, const float *UD, const double *dt, float *Uout,
@@ -726,16 +1084,16 @@ void launch_transport32(rt_ctx *ctx, const float *UD, const double *dt, float *U
     const int G = ctx->p.groups, s3 = slices_of_3(G), s2 = slices_of_2(G);
     const Slices sl{G, 0, s3};
     if (G == 1) {
-        launch_tiles32<1, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        launch_groups32<1, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else if (G == 2) {
-        launch_tiles32<2, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        launch_groups32<2, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else if (G == 3) {
-        launch_tiles32<3, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        launch_groups32<3, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else {
         if (s3 > 0)
-            launch_tiles32<3, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+            launch_groups32<3, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
         if (s2 > 0)
-            launch_tiles32<2, false>(ctx, Slices{G, 3 * s3, s2}, UD, dt, Uout, partials, counts,
+            launch_groups32<2, true>(ctx, Slices{G, 3 * s3, s2}, UD, dt, Uout, partials, counts,
                                      Uung, tick, accm);
     }
 }

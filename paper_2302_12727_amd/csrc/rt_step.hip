@@ -526,35 +526,42 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
 
 // Transport with the pairs inside a tile evaluated once (FP64, GLF or HLL,
 // Hopkins or Ivanova surfaces, G <= 3 groups in one wave: all of them, or one
-// of the slices of more, see Slices: two-sided, every pair evaluated by both its
-// particles, 4 and 5 groups took 1.13 times as long).  Both solvers' pair fluxes and both surfaces are antisymmetric, so
-// one evaluation serves both particles of a pair.
+// of the slices of more, see Slices; two-sided, every pair evaluated by both
+// its particles, 4 and 5 groups took 1.13 times as long).  Both solvers' pair
+// fluxes and both surfaces are antisymmetric, so one evaluation serves both
+// particles of a pair.
 //
 // A block owns one tile: the 64 consecutive Morton particles of one column
-// block of the neighbour table, 16 per wave with 4 lanes each (the layout, and
-// so the cache footprint, of the two-sided kernel).  A particle's task list
-// (k_tasks, built with the geometry) holds its neighbours outside the tile and
-// its share of the pairs inside it: an in-tile pair (k, l) is evaluated by one
-// of its particles only (chosen to balance the lists' lengths), flagged by
-// the sign bit.  That lane adds Phi_kl to its own sum and -Phi_kl, by an LDS
-// atomic add, to the other particle's row of its own wave's copy of the
-// tile's accumulator; the pair's face states are the same from either side,
-// so its face-guard counts are taken twice.  After a block barrier each
-// particle's sum is its own partial sums plus the 4 waves' rows, added in a
-// fixed order, so runs are bitwise reproducible, and the in-tile pair flux
-// is antisymmetric bit for bit.  49.5% of the neighbour entries of the 128^3
-// lattice lie inside their tile, so a step evaluates 75% of the pair fluxes
-// of the two-sided kernel.  (With a wave owning a whole tile in 4 passes the
-// XCD's working set spanned 4 times the particles and its L2 hit rate fell
-// from 92% to 38%.)
-
+// block of the neighbour table, 16 per wave with 4 lanes each.  A particle's
+// task list (k_tasks, built with the geometry) holds its neighbours outside the
+// tile and its share of the pairs inside it: an in-tile pair (k, l) is
+// evaluated by one of its particles only (chosen to balance the lists'
+// lengths), flagged by the sign bit.  That lane adds Phi_kl to its own sum and,
+// by an LDS atomic add, to the other particle's row of its own wave's copy of
+// the tile's accumulator, which is taken off at the end; the pair's face states
+// are the same from either side, so its face-guard counts are taken twice.
+// After a block barrier each particle's sum is its own partial sums less the 4
+// waves' rows, in a fixed order, so runs are bitwise reproducible, and the
+// in-tile pair flux is antisymmetric bit for bit.  49.5% of the neighbour
+// entries of the 128^3 lattice lie inside their tile, so a step evaluates 75%
+// of the pair fluxes of a two-sided one.  (With a wave owning a whole tile in 4
+// passes the XCD's working set spanned 4 times the particles and its L2 hit
+// rate fell from 92% to 38%.)
+//
+// What bounds it: the FP64 vector instructions (half the issue slots) and the
+// waits of two waves per SIMD on the neighbours' rows.  Guard counts only where
+// they are asked for, the partners' sums without a sign change, and the
+// shorter reciprocals (rcp64, rsq64) took the 3-group 128^3 lattice from 3.04
+// to 2.93 ms.  (Rows staged once per tile in LDS, the groups one after the
+// other with the pair geometry in registers, cut the rows from L2 sixfold and
+// ran 3.33 ms: a fifth more instructions, and barriers between the stages.)
 //
 // BIN: one tick of the individual-time-step scheme on the tiles.  A pair is
 // due when its smaller bin ends a step in this tick, a symmetric condition,
 // and its flux weighted by dt 2^min(b_k, b_l) is antisymmetric as before; a
 // particle none of whose pairs is due (binm) walks no list.  The particles
 // that do not end a step add their sums to the pending sums accm, the others
-// apply theirs, as in the two-sided binned kernel.
+// apply theirs.
 template <int G, bool WHOLE, bool OFF32, bool HLL, bool IVA, bool BIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ geo,
@@ -726,8 +733,10 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                         hll_weights(loL, hiL, loR, hiR, pg.An, w1, w2, w3);
                     }
                     if (use) {
-                        cE += cnt2 * ((f1 & 1) + (f2 & 1));
-                        cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
+                        if (counts) {
+                            cE += cnt2 * ((f1 & 1) + (f2 & 1));
+                            cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
+                        }
                         const double al = __builtin_fma(w1, aL, w2 * aR);
                         const double bl = w1 * bL, br = w2 * bR;
                         double phi[4];
@@ -746,7 +755,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                         for (int m = 0; m < 4; ++m) acc[4 * g + m] += phi[m];
                         if (mirror) {
 #pragma unroll
-                            for (int m = 0; m < 4; ++m) atomicAdd(mw + mr + 4 * g + m, -phi[m]);
+                            for (int m = 0; m < 4; ++m) atomicAdd(mw + mr + 4 * g + m, phi[m]);
                         }
                     }
                 }
@@ -762,7 +771,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
     // every wave's deposits are in its copy of the accumulator
     __syncthreads();
     // update, post-update guard, ledger, photon budget: the first lane of each
-    // particle; its sum is its own partial sums plus the 4 waves' rows, in
+    // particle; its sum is its own partial sums less the 4 waves' rows, in
     // that fixed order
     const int64_t i = t0 + pl;
     const bool owner = wave_live && sub == 0 && i < n;
@@ -775,7 +784,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int v = 0; v < kBlock / 64; ++v) acc[q] += mir[v][pl * MS + q];
+            for (int v = 0; v < kBlock / 64; ++v) acc[q] -= mir[v][pl * MS + q];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (touched) {
@@ -793,7 +802,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int v = 0; v < kBlock / 64; ++v) acc[q] += mir[v][pl * MS + q];
+            for (int v = 0; v < kBlock / 64; ++v) acc[q] -= mir[v][pl * MS + q];
         if constexpr (BIN) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {

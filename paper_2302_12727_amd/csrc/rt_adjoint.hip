@@ -455,7 +455,7 @@ typedef double dvec2a __attribute__((ext_vector_type(2)));
 template <int G, int W>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W, W))) void
 k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
-              const int32_t *__restrict__ urow, const int64_t *__restrict__ uoff,
+              const int32_t *__restrict__ urow, const int32_t *__restrict__ urows,
               const uint16_t *__restrict__ gloc, const int64_t *__restrict__ goff,
               const uint16_t *__restrict__ uown, const int32_t *__restrict__ n_nbr,
               const double *__restrict__ R, double *__restrict__ lam, double box) {
@@ -466,9 +466,9 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
     __shared__ int32_t uidx[UC];
     const int64_t blk = xcd_block(nb);
     if (blk >= nb) return;                      // whole block
-    const int64_t u0 = uoff[blk];
-    const int32_t rows = (int32_t)(uoff[blk + 1] - u0);
-    if (rows == 0) return;                      // left to k_adj_grad64 (whole block)
+    const int64_t u0 = blk * adj_union_cap(2);
+    const int32_t rows = urows[blk];
+    if (rows == 0 || rows > UC) return;                      // left to k_adj_grad64 (whole block)
     for (int e = threadIdx.x; e < rows; e += kBlock) uidx[e] = urow[u0 + e];
     __syncthreads();
     {   // positions and 1/H, all loads in flight
@@ -651,21 +651,21 @@ void launch_adjoint64(rt_ctx *ctx, const double *UD, const double *Uung, const d
 #undef RT_ADJ_TILE_LAUNCH
     }
     if constexpr (G <= 4 && kAGQ == 4) {
-        if (ctx->aoff) {
+        if (ctx->arows) {
             // blocks whose union fits: from LDS; the others: by list
             const int64_t nw = ctx->nwaves;
             if (ctx->adj_union_waves == 3)
                 k_adj_grad64u<G, 3><<<(unsigned)xcd_grid(nw), kBlock, 0, st>>>(
-                    n, nw, ctx->geo, ctx->arow, ctx->aoff, ctx->agloc, ctx->goff, ctx->aown,
+                    n, nw, ctx->geo, ctx->arow, ctx->arows, ctx->agloc, ctx->goff, ctx->aown,
                     ctx->n_nbr, R, lam, ctx->p.box);
             else
                 k_adj_grad64u<G, 2><<<(unsigned)xcd_grid(nw), kBlock, 0, st>>>(
-                    n, nw, ctx->geo, ctx->arow, ctx->aoff, ctx->agloc, ctx->goff, ctx->aown,
+                    n, nw, ctx->geo, ctx->arow, ctx->arows, ctx->agloc, ctx->goff, ctx->aown,
                     ctx->n_nbr, R, lam, ctx->p.box);
             if (ctx->n_ablk > 0)
                 k_adj_grad64<G, 4><<<(unsigned)xcd_grid(ctx->n_ablk), kBlock, 0, st>>>(
                     n, ctx->n_ablk, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, R, lam,
-                    ctx->p.box, ctx->ablk);
+                    ctx->p.box, ctx->ablk + 2);
             return;
         }
     }

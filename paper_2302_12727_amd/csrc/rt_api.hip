@@ -38,6 +38,18 @@ rt_status rt_alloc(rt_ctx *ctx, void **ptr, size_t bytes) {
                                        " bytes failed");
 }
 
+bool rt_holds(const rt_ctx *ctx, void *ptr, size_t bytes) {
+    const auto it = ctx->allocs.find(ptr);
+    return ptr && it != ctx->allocs.end() && it->second >= bytes;
+}
+
+rt_status rt_reserve(rt_ctx *ctx, void **ptr, size_t bytes) {
+    if (rt_holds(ctx, *ptr, bytes)) return RT_OK;
+    rt_free(ctx, *ptr);
+    *ptr = nullptr;
+    return rt_alloc(ctx, ptr, bytes);
+}
+
 void rt_free(rt_ctx *ctx, void *ptr) {
     if (!ptr) return;
     auto it = ctx->allocs.find(ptr);
@@ -127,9 +139,9 @@ void rt_destroy(rt_ctx *ctx) {
                     ctx->inj_gas, ctx->inj_src, ctx->inj_coef, ctx->inj_xi, ctx->src_ptr,
                     ctx->src_gas, ctx->src_coef, ctx->status, ctx->partials, ctx->scan_tmp,
                     ctx->adj_buf, ctx->hll_table, ctx->hll_table32, ctx->vol, ctx->ivan,
-                    ctx->bin8, ctx->task, ctx->n_task, ctx->tstat, ctx->uoff, ctx->urow, ctx->gloc,
-                    ctx->uown, ctx->ublk, ctx->goff, ctx->aoff, ctx->arow, ctx->agloc,
-                    ctx->aown, ctx->ablk};
+                    ctx->bin8, ctx->task, ctx->n_task, ctx->tstat, ctx->urows, ctx->urow, ctx->gloc,
+                    ctx->uown, ctx->ublk, ctx->goff, ctx->arows, ctx->arow, ctx->agloc,
+                    ctx->aown, ctx->ablk, ctx->dxpart, ctx->result};
     for (void *b : bufs) rt_free(ctx, b);
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
     delete ctx;
@@ -365,11 +377,11 @@ rt_status rt_get_stats(rt_ctx *ctx, rt_stats *out) {
     out->device_bytes = ctx->device_bytes;
     out->device_bytes_peak = ctx->device_peak;
     out->h_list_overflow = ctx->h_list_overflow;
-    out->union_blocks = ctx->uoff ? ctx->nwaves - ctx->n_ublk : 0;
-    out->union_staged_blocks = ctx->uoff ? ctx->n_ublk : 0;
-    out->adj_union_blocks = ctx->aoff ? ctx->nwaves - ctx->n_ablk : 0;
-    out->adj_union_staged_blocks = ctx->aoff ? ctx->n_ablk : 0;
-    if (ctx->tstat) {
+    out->union_blocks = ctx->urows ? ctx->nwaves - ctx->n_ublk : 0;
+    out->union_staged_blocks = ctx->urows ? ctx->n_ublk : 0;
+    out->adj_union_blocks = ctx->arows ? ctx->nwaves - ctx->n_ablk : 0;
+    out->adj_union_staged_blocks = ctx->arows ? ctx->n_ablk : 0;
+    if (ctx->built && ctx->tstat) {
         int64_t t[2];
         RT_HIP(hipStreamSynchronize(ctx->stream));
         RT_HIP(hipMemcpy(t, ctx->tstat, sizeof t, hipMemcpyDeviceToHost));

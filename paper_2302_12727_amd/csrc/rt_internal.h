@@ -76,6 +76,14 @@ struct TimerRec {
 
 }  // namespace gearrt
 
+// What the host reads once a build is done: its statistics (k_stats), status
+// and the blocks of the unions (k_union_left).
+struct BuildResult {
+    unsigned long long stat[5];
+    int32_t status;
+    int32_t left[2], aleft[2];
+};
+
 struct rt_ctx {
     rt_params p{};
     hipStream_t stream = nullptr;
@@ -109,23 +117,26 @@ struct rt_ctx {
     int32_t *nbr = nullptr;      // [slots]
     int32_t *task = nullptr;     // [slots] task lists of the FP64 tile transport (same slots)
     int32_t *n_task = nullptr;   // [n]
+    double *dxpart = nullptr;    // partial minima of the time step's lengths
+    BuildResult *result = nullptr;
     int64_t *tstat = nullptr;    // [2] over the tiles: the longest task list, its lower bound
     // neighbour unions of the FP64 gradient (k_union): per block of 64
     // particles its sorted distinct gather neighbours and own particles
-    int64_t *uoff = nullptr;     // [nwaves + 1] offsets into urow (no rows: staged gradient)
-    int32_t *urow = nullptr;     // [uoff[nwaves]]
+    int32_t *urows = nullptr;    // [nwaves] rows of the union (0: staged gradient)
+    int32_t *urow = nullptr;     // [nwaves][union_cap or union_cap32]
     // a gather slot's position in its block's union, packed so that a lane's
     // entries of four consecutive iterations share 8 bytes: entry (p, k) of
     // block b at goff[b] + (k / 16) 1024 + (4 p + k % 4) 4 + (k / 4) % 4
     uint16_t *gloc = nullptr;
     int64_t *goff = nullptr;     // [nwaves + 1], 1024 ceil(rows / 16) entries per block
     uint16_t *uown = nullptr;    // [n] a particle's position in its block's union
-    int32_t *ublk = nullptr;     // [n_ublk] blocks left to the staged gradient
+    int32_t *ublk = nullptr;     // two counts (k_union_left), then the n_ublk blocks left to
+                                 // the staged gradient
     int64_t n_ublk = 0;
     int union_waves = 2;         // waves per SIMD of the union gradient (capacity by it)
     // the same over the symmetric lists, for the FP64 adjoint's transposed
     // gradient (entries packed as gloc, at the same goff)
-    int64_t *aoff = nullptr;
+    int32_t *arows = nullptr;
     int32_t *arow = nullptr;
     uint16_t *agloc = nullptr;
     uint16_t *aown = nullptr;
@@ -364,6 +375,10 @@ rt_status rt_fail(rt_ctx *ctx, rt_status st, const std::string &msg);
 rt_status rt_alloc(rt_ctx *ctx, void **ptr, size_t bytes);
 // rt_alloc for optional scratch: false (and no error message) when it fails
 bool rt_try_alloc(rt_ctx *ctx, void **ptr, size_t bytes);
+// memory of at least `bytes` in *ptr: what is there if it is large enough, else
+// new (its contents are lost)
+rt_status rt_reserve(rt_ctx *ctx, void **ptr, size_t bytes);
+bool rt_holds(const rt_ctx *ctx, void *ptr, size_t bytes);
 // free memory from rt_alloc / rt_try_alloc and take it off the context's count
 void rt_free(rt_ctx *ctx, void *ptr);
 void rt_timer_begin(rt_ctx *ctx, const char *name);

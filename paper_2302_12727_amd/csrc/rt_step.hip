@@ -383,7 +383,7 @@ __global__ __launch_bounds__(grad_block(G)) __attribute__((amdgpu_waves_per_eu(
 template <int G, int Q, int W, bool BIN = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W, W))) void
 k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const double *__restrict__ xs,
-              const int32_t *__restrict__ urow, const int64_t *__restrict__ uoff,
+              const int32_t *__restrict__ urow, const int32_t *__restrict__ urows,
               const uint16_t *__restrict__ gloc, const int64_t *__restrict__ goff,
               const uint16_t *__restrict__ uown, const int32_t *__restrict__ n_gath,
               const double *__restrict__ U, double *__restrict__ UD, int32_t *__restrict__ status,
@@ -396,9 +396,9 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
     __shared__ int32_t uidx[UC];
     const int64_t blk = xcd_block(nb);
     if (blk >= nb) return;                      // whole block
-    const int64_t u0 = uoff[blk];
-    const int32_t rows = (int32_t)(uoff[blk + 1] - u0);
-    if (rows == 0) return;                      // left to the staged gradient (whole block)
+    const int64_t u0 = blk * union_cap(G);
+    const int32_t rows = urows[blk];
+    if (rows == 0 || rows > UC) return;                      // left to the staged gradient (whole block)
     if constexpr (BIN) {
         const int64_t ib = blk * (kBlock / Q) + threadIdx.x / Q;
         const bool e = ib < n &&
@@ -1057,12 +1057,12 @@ template <int G>
 void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
     constexpr int B = grad_block(G);
     if constexpr (union_cap(G) > 0 && kGQ == 4 && B == 256) {
-        if (ctx->uoff) {
+        if (ctx->urows) {
             // blocks whose union fits: from LDS; the others: staged, by list
             const int64_t nw = ctx->nwaves;
 #define RT_UNION_LAUNCH(W_)                                                                    \
     k_gradient64u<G, kGQ, W_><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(            \
-        ctx->p.n, nw, ctx->geo, ctx->xs, ctx->urow, ctx->uoff, ctx->gloc, ctx->goff,          \
+        ctx->p.n, nw, ctx->geo, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,          \
         ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box)
             if constexpr (union_cap3(G) > 0) {
                 if (ctx->union_waves == 3) RT_UNION_LAUNCH(3);
@@ -1074,7 +1074,7 @@ void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
             if (ctx->n_ublk > 0)
                 k_gradient64<G, false, kGQ><<<(unsigned)xcd_grid(ctx->n_ublk), B, 0, ctx->stream>>>(
                     ctx->p.n, ctx->n_ublk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
-                    U, UD, ctx->status, ctx->p.box, 0, ctx->ublk);
+                    U, UD, ctx->status, ctx->p.box, 0, ctx->ublk + 2);
             return;
         }
     }
@@ -1092,13 +1092,13 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
     const int64_t ng = (n + B / kGQ - 1) / (B / kGQ);
     bool grad_done = false;
     if constexpr (union_cap(G) > 0 && kGQ == 4 && B == 256) {
-        if (RT_TICK_UNION != 0 && ctx->uoff) {
+        if (RT_TICK_UNION != 0 && ctx->urows) {
             // the neighbour unions, in their time-bin mode; the blocks whose
             // union does not fit: staged, by list
             const int64_t nw = ctx->nwaves;
 #define RT_TICK_UNION_LAUNCH(W_)                                                               \
     k_gradient64u<G, kGQ, W_, true><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(      \
-        n, nw, ctx->geo, ctx->xs, ctx->urow, ctx->uoff, ctx->gloc, ctx->goff, ctx->uown,       \
+        n, nw, ctx->geo, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff, ctx->uown,       \
         ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick)
             if constexpr (union_cap3(G) > 0) {
                 if (ctx->union_waves == 3) RT_TICK_UNION_LAUNCH(3);
@@ -1110,7 +1110,7 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
             if (ctx->n_ublk > 0)
                 k_gradient64<G, true, kGQ><<<(unsigned)xcd_grid(ctx->n_ublk), B, 0, ctx->stream>>>(
                     n, ctx->n_ublk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
-                    U, UD, ctx->status, ctx->p.box, tick, ctx->ublk);
+                    U, UD, ctx->status, ctx->p.box, tick, ctx->ublk + 2);
             grad_done = true;
         }
     }

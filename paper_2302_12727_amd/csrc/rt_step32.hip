@@ -133,7 +133,7 @@ typedef float fvec4 __attribute__((ext_vector_type(4)));
 template <int G, bool BIN = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const double *__restrict__ xs,
-              const int32_t *__restrict__ urow, const int64_t *__restrict__ uoff,
+              const int32_t *__restrict__ urow, const int32_t *__restrict__ urows,
               const uint16_t *__restrict__ gloc, const int64_t *__restrict__ goff,
               const uint16_t *__restrict__ uown, const int32_t *__restrict__ n_gath,
               const float *__restrict__ U, float *__restrict__ UD, int32_t *__restrict__ status,
@@ -145,8 +145,8 @@ k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const doub
     __shared__ int32_t uidx[UC];
     const int64_t blk = xcd_block(nb);
     if (blk >= nb) return;                      // whole block
-    const int64_t u0 = uoff[blk];
-    const int32_t rows = (int32_t)(uoff[blk + 1] - u0);
+    const int64_t u0 = blk * UC;
+    const int32_t rows = urows[blk];
     if (rows == 0) return;                      // left to k_gradient32 (whole block)
     if constexpr (BIN) {
         const int64_t ib = blk * (kBlock / Q) + threadIdx.x / Q;
@@ -1018,18 +1018,18 @@ constexpr int kGQ32 = RT_GRADIENT32_Q;
 template <int G>
 void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
     if constexpr (union_cap32(G) > 0 && kGQ32 == 1) {   // the union sums in one lane's order
-        if (ctx->uoff) {
+        if (ctx->urows) {
             // blocks whose union fits: from LDS; the others: one lane per
             // particle (the same order), by list
             const int64_t nw = ctx->nwaves;
             k_gradient32u<G><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(
-                ctx->p.n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->uoff, ctx->gloc, ctx->goff,
+                ctx->p.n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box);
             if (ctx->n_ublk > 0) {
                 const int64_t nl = (ctx->n_ublk + 3) / 4;
                 k_gradient32<G, 1><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     ctx->p.n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U,
-                    UD, ctx->status, ctx->p.box, 0, ctx->ublk, ctx->n_ublk);
+                    UD, ctx->status, ctx->p.box, 0, ctx->ublk + 2, ctx->n_ublk);
             }
             return;
         }
@@ -1105,18 +1105,18 @@ void launch_tick32(rt_ctx *ctx, float *U, float *UD, const double *dt, double *p
     const int64_t ng = (n + kBlock / kGQ32 - 1) / (kBlock / kGQ32);
     bool grad_done = false;
     if constexpr (union_cap32(G) > 0 && kGQ32 == 1) {
-        if (RT_TICK_UNION32 != 0 && ctx->uoff) {
+        if (RT_TICK_UNION32 != 0 && ctx->urows) {
             // the neighbour unions in their time-bin mode; the blocks whose
             // union does not fit: one lane per particle, by list
             const int64_t nw = ctx->nwaves;
             k_gradient32u<G, true><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(
-                n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->uoff, ctx->gloc, ctx->goff,
+                n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick);
             if (ctx->n_ublk > 0) {
                 const int64_t nl = (ctx->n_ublk + 3) / 4;
                 k_gradient32<G, 1, true><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U, UD,
-                    ctx->status, ctx->p.box, tick, ctx->ublk, ctx->n_ublk);
+                    ctx->status, ctx->p.box, tick, ctx->ublk + 2, ctx->n_ublk);
             }
             grad_done = true;
         }

@@ -37,7 +37,8 @@ def clump_set(n_side: int, m: int, seed: int) -> np.ndarray:
     workloads.jittered_lattice(13, 0.1, 2)[:2047],     # 64 leaves, one whole step
     workloads.jittered_lattice(13, 0.1, 2)[:2049],     # 65 leaves, two steps
     clump_set(10, 400, 3),
-], ids=["n125", "n2047", "n2049", "clump"])
+    clump_set(10, 100, 4),                             # reaches cut and drawn out again
+], ids=["n125", "n2047", "n2049", "clump", "small clump"])
 def test_smoothing_lengths_and_neighbours(x):
     n = x.shape[0]
     geo = oracle.build_geometry(x)

@@ -897,37 +897,53 @@ __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e
 }
 
 // part [nb][2G]: columns 0..G-1 photon totals, G..2G-1 ledger.  Q[g] = sum (written),
-// ledger[g] += sum.  Two passes in a fixed order:
-//  1. block k of kFinBlocks takes the rows [k m, (k+1) m), m = ceil(nb / kFinBlocks):
-//     thread t sums rows t, t + kBlock, ... of it (whole rows, so consecutive
-//     threads read consecutive rows), one compensated sum per column, and the
-//     block's 256 sums of each column meet in a fixed tree;
-//  2. one block combines the kFinBlocks compensated sums of each column.
+// ledger[g] += sum, in a fixed order: thread t of a block sums whole rows t,
+// t + kBlock, ... of the block's share (consecutive threads read consecutive
+// rows), one compensated sum per column; the threads' sums of all columns meet
+// in a fixed tree, over the lanes by shuffles, then over the waves.  Up to
+// kFinOneRows rows are one block's work; more are kFinBlocks blocks' and
+// their compensated sums a second launch's.  (Two launches whatever the rows,
+// and a tree through LDS per column, were 7.8 of the 32 us of a step of 16^3
+// particles.)
 constexpr int kFinBlocks = 32;
+constexpr int64_t kFinOneRows = 2048;
 
-// Fixed tree over the block of the compensated pairs (ss, sc); the result is
-// in ss[0] + sc[0].
-__device__ __forceinline__ void block_two_sum_tree(double *ss, double *sc) {
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            double t, err;
-            two_sum(ss[threadIdx.x], ss[threadIdx.x + w], t, err);
-            ss[threadIdx.x] = t;
-            sc[threadIdx.x] += sc[threadIdx.x + w] + err;
+// The compensated pairs (s, e) of the block's W waves, summed, in lane 0 of wave 0.
+template <int C, int W>
+__device__ __forceinline__ void block_two_sum(double (&s)[C], double (&e)[C],
+                                              double (&sh)[W][C][2]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    auto add = [](double &s0, double &e0, double s1, double e1) {
+        double t, err;
+        two_sum(s0, s1, t, err);
+        s0 = t;
+        e0 += e1 + err;
+    };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            add(s[c], e[c], __shfl_down(s[c], o, 64), __shfl_down(e[c], o, 64));
+    if constexpr (W > 1) {
+        if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                sh[wv][c][0] = s[c];
+                sh[wv][c][1] = e[c];
+            }
         }
         __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                for (int w = 1; w < W; ++w) add(s[c], e[c], sh[w][c][0], sh[w][c][1]);
+        }
     }
 }
 
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_finalize_rows(int64_t nb, const double *__restrict__ part,
-                                                          double *__restrict__ fin) {
-    constexpr int C = 2 * G;
-    __shared__ double ss[kBlock], sc[kBlock];
-    const int64_t m = (nb + kFinBlocks - 1) / kFinBlocks;
-    const int64_t r0 = blockIdx.x * m, r1 = min(nb, r0 + m);
-    double s[C], e[C];
+template <int C>
+__device__ __forceinline__ void sum_rows(int64_t r0, int64_t r1, const double *__restrict__ part,
+                                         double (&s)[C], double (&e)[C]) {
 #pragma unroll
     for (int c = 0; c < C; ++c) s[c] = e[c] = 0.0;
     for (int64_t b = r0 + threadIdx.x; b < r1; b += kBlock) {
@@ -940,48 +956,76 @@ __global__ __launch_bounds__(kBlock) void k_finalize_rows(int64_t nb, const doub
             e[c] += err;
         }
     }
+}
+
+template <int G>
+__device__ __forceinline__ void store_totals(const double (&s)[2 * G], const double (&e)[2 * G],
+                                             double *__restrict__ Q, double *__restrict__ ledger) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (Q) Q[g] = s[g] + e[g];
+        if (ledger) ledger[g] += s[G + g] + e[G + g];
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_finalize_one(int64_t nb, const double *__restrict__ part,
+                                                         double *__restrict__ Q,
+                                                         double *__restrict__ ledger) {
+    __shared__ double sh[kBlock / 64][2 * G][2];
+    double s[2 * G], e[2 * G];
+    sum_rows<2 * G>(0, nb, part, s, e);
+    block_two_sum<2 * G, kBlock / 64>(s, e, sh);
+    if (threadIdx.x == 0) store_totals<G>(s, e, Q, ledger);
+}
+
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_finalize_rows(int64_t nb, const double *__restrict__ part,
+                                                          double *__restrict__ fin) {
+    constexpr int C = 2 * G;
+    __shared__ double sh[kBlock / 64][C][2];
+    const int64_t m = (nb + kFinBlocks - 1) / kFinBlocks;
+    const int64_t r0 = blockIdx.x * m;
+    double s[C], e[C];
+    sum_rows<C>(r0, min(nb, r0 + m), part, s, e);
+    block_two_sum<C, kBlock / 64>(s, e, sh);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            fin[(blockIdx.x * C + c) * 2] = s[c];
+            fin[(blockIdx.x * C + c) * 2 + 1] = e[c];
+        }
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(64) void k_finalize(const double *__restrict__ fin,
+                                                 double *__restrict__ Q,
+                                                 double *__restrict__ ledger) {
+    constexpr int C = 2 * G;
+    __shared__ double sh[1][C][2];
+    double s[C], e[C];
+    const bool in = threadIdx.x < kFinBlocks;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        ss[threadIdx.x] = s[c];
-        sc[threadIdx.x] = e[c];
-        block_two_sum_tree(ss, sc);
-        if (threadIdx.x == 0) {
-            fin[(blockIdx.x * C + c) * 2] = ss[0];
-            fin[(blockIdx.x * C + c) * 2 + 1] = sc[0];
-        }
-        __syncthreads();
+        s[c] = in ? fin[(threadIdx.x * C + c) * 2] : 0.0;
+        e[c] = in ? fin[(threadIdx.x * C + c) * 2 + 1] : 0.0;
     }
+    block_two_sum<C, 1>(s, e, sh);
+    if (threadIdx.x == 0) store_totals<G>(s, e, Q, ledger);
 }
 
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_finalize(const double *__restrict__ fin,
-                                                     double *__restrict__ Q,
-                                                     double *__restrict__ ledger) {
-    constexpr int C = 2 * G;
-    __shared__ double ss[kBlock], sc[kBlock];
-    for (int c = 0; c < C; ++c) {
-        double *dst = c < G ? Q : ledger;
-        if (!dst) continue;
-        const bool in = threadIdx.x < kFinBlocks;
-        ss[threadIdx.x] = in ? fin[(threadIdx.x * C + c) * 2] : 0.0;
-        sc[threadIdx.x] = in ? fin[(threadIdx.x * C + c) * 2 + 1] : 0.0;
-        block_two_sum_tree(ss, sc);
-        if (threadIdx.x == 0) {
-            double v = ss[0] + sc[0];
-            if (c < G) Q[c] = v;
-            else ledger[c - G] += v;
-        }
-        __syncthreads();
-    }
-}
-
-// part is ctx->partials; the kFinBlocks x 2G compensated pairs of the first
-// pass go to the slack the buffer keeps after its rows.
+// part is ctx->partials; the kFinBlocks x 2G compensated pairs of a first pass
+// go to the slack the buffer keeps after its rows.
 template <int G>
 void launch_finalize(rt_ctx *ctx, int64_t nb, const double *part, double *Q, double *ledger) {
+    if (nb <= kFinOneRows) {
+        k_finalize_one<G><<<1, kBlock, 0, ctx->stream>>>(nb, part, Q, ledger);
+        return;
+    }
     double *fin = ctx->partials + 2 * G * ctx->nblocks;
     k_finalize_rows<G><<<kFinBlocks, kBlock, 0, ctx->stream>>>(nb, part, fin);
-    k_finalize<G><<<1, kBlock, 0, ctx->stream>>>(fin, Q, ledger);
+    k_finalize<G><<<1, 64, 0, ctx->stream>>>(fin, Q, ledger);
 }
 
 // rows of block partials the FP64 transport writes (one per tile)

@@ -287,11 +287,11 @@ __device__ __forceinline__ void pair_geometry_ivanova64(const double *__restrict
     pg.fl = rl[R_H] * ih;
 }
 
-// Block sum of NP per-lane values; value p goes to out[col(p)].
-template <int NP, class Col>
+// Block sum (W waves) of NP per-lane values; value p goes to out[col(p)].
+template <int NP, int W = kBlock / 64, class Col>
 __device__ __forceinline__ void block_reduce_store(double (&v)[NP], double *__restrict__ out,
                                                    double *smem, Col col) {
-    // smem: [kBlock/64][NP]
+    // smem: [W][NP]
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -301,7 +301,7 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NP], double *__re
     __syncthreads();
     if (threadIdx.x < NP) {
         double s = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) s += smem[w * NP + threadIdx.x];
+        for (int w = 0; w < W; ++w) s += smem[w * NP + threadIdx.x];
         out[col((int)threadIdx.x)] = s;
     }
 }

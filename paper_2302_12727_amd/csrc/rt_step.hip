@@ -532,21 +532,29 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
 // particles of a pair.
 //
 // A block owns one tile: the 64 consecutive Morton particles of one column
-// block of the neighbour table, 16 per wave with 4 lanes each.  A particle's
-// task list (k_tasks, built with the geometry) holds its neighbours outside the
+// block of the neighbour table, 16 per wave with 4 lanes each (see below for
+// 8).  A particle's task list (k_tasks, built with the geometry) holds its neighbours outside the
 // tile and its share of the pairs inside it: an in-tile pair (k, l) is
 // evaluated by one of its particles only (chosen to balance the lists'
 // lengths), flagged by the sign bit.  That lane adds Phi_kl to its own sum and,
 // by an LDS atomic add, to the other particle's row of its own wave's copy of
 // the tile's accumulator, which is taken off at the end; the pair's face states
 // are the same from either side, so its face-guard counts are taken twice.
-// After a block barrier each particle's sum is its own partial sums less the 4
+// After a block barrier each particle's sum is its own partial sums less the
 // waves' rows, in a fixed order, so runs are bitwise reproducible, and the
 // in-tile pair flux is antisymmetric bit for bit.  49.5% of the neighbour
 // entries of the 128^3 lattice lie inside their tile, so a step evaluates 75%
 // of the pair fluxes of a two-sided one.  (With a wave owning a whole tile in 4
 // passes the XCD's working set spanned 4 times the particles and its L2 hit
 // rate fell from 92% to 38%.)
+//
+// Q lanes a particle, a tile by Q waves, W waves per SIMD.  Up to 256 tiles
+// (one a CU) Q = 8 halves the chain of a particle's pairs: 16^3 particles, 3
+// groups, 38.7 -> 33.0 us, 25^3 45.9 -> 36.9; with two tiles a CU it costs
+// (32^3 55.2 -> 62.9).  One group of the GLF solver fits W = 3 without much
+// spilled (the 32-bit offsets; HLL and more groups do not, the latter for their
+// LDS too): from 513 tiles, two a CU, on 48^3 88.5 -> 85.0 us, 100^3 742 ->
+// 667; 32^3, where no third one comes, 28.3 -> 30.2.
 //
 // What bounds it: the FP64 vector instructions (half the issue slots) and the
 // waits of two waves per SIMD on the neighbours' rows.  Guard counts only where
@@ -562,8 +570,8 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
 // particle none of whose pairs is due (binm) walks no list.  The particles
 // that do not end a step add their sums to the pending sums accm, the others
 // apply theirs.
-template <int G, bool WHOLE, bool OFF32, bool HLL, bool IVA, bool BIN>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+template <int G, bool WHOLE, bool OFF32, bool HLL, bool IVA, bool BIN, int Q, int W>
+__global__ __launch_bounds__(64 * Q) __attribute__((amdgpu_waves_per_eu(W, W))) void
 k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ geo,
                    const int32_t *__restrict__ task, const int64_t *__restrict__ wave_base,
                    const int32_t *__restrict__ n_task, const double *__restrict__ UDall,
@@ -574,12 +582,13 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                    int64_t tick = 0, double *__restrict__ accm = nullptr,
                    const uint8_t *__restrict__ binm = nullptr) {
     constexpr int NQ = 4 * G, MS = NQ + 1;     // accumulator row, padded against bank conflicts
-    __shared__ double stage[kBlock / 64][64 * kStage];
-    static_assert(kTile == 64 && kBlock == 256, "a block of 4 waves x 16 particles per tile");
-    __shared__ double mir[kBlock / 64][kTile * MS];
+    static_assert(kTile == 64 && (Q == 4 || Q == 8), "a tile is Q waves of 64 / Q particles");
+    constexpr int PW = 64 / Q;                  // particles per wave
+    __shared__ double stage[Q][64 * kStage];
+    __shared__ double mir[Q][kTile * MS];
     constexpr int DS = 3 * NQ + 1;              // own-gradient row, padded
-    __shared__ double dsh[kBlock / 64][16 * DS];
-    __shared__ double smem[(kBlock / 64) * 2 * G];
+    __shared__ double dsh[Q][PW * DS];
+    __shared__ double smem[Q * 2 * G];
     __shared__ unsigned long long scnt[4];
     // the block's tile and its groups g0 .. g0 + G of the GT
     const int GT = WHOLE ? G : sl.groups, nsl = WHOLE ? 1 : sl.count;
@@ -589,9 +598,9 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
     const int g0 = WHOLE ? 0 : sl.first + (int)(bg - blk * nsl) * G;
     const double *UD = UDall + 16 * g0;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int sub = lane & 3;
+    const int sub = lane & (Q - 1);
     const int64_t t0 = blk * kTile;             // the tile's first particle
-    const bool wave_live = t0 + 16 * wv < n;    // wave-uniform
+    const bool wave_live = t0 + PW * wv < n;    // wave-uniform
     const double ibox = 1.0 / box, hc = 0.5 * c, c3 = 3.0 * c;
     if (threadIdx.x < 4) scnt[threadIdx.x] = 0;
     double *sb = stage[wv];
@@ -599,7 +608,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
     for (int e = lane; e < kTile * MS; e += 64) mw[e] = 0.0;
     wave_lds_sync();
     int cE = 0, cF = 0;
-    const int pl = 16 * wv + (lane >> 2);       // the lane's particle in the tile
+    const int pl = PW * wv + lane / Q;       // the lane's particle in the tile
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
@@ -635,14 +644,16 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
 #pragma unroll
                 for (int m = 0; m < 4; ++m) Ui[4 * g + m] = r[m];
             }
-            // the own gradients live in LDS (4 lanes read one address); lane
-            // sub copies component sub's
-            double *Dsh = dsh[wv] + (lane >> 2) * DS;
+            // the own gradients live in LDS (Q lanes read one address); lane
+            // sub < 4 copies component sub's
+            double *Dsh = dsh[wv] + lane / Q * DS;
+            if (Q == 4 || sub < 4) {
 #pragma unroll
-            for (int g = 0; g < G; ++g)
+                for (int g = 0; g < G; ++g)
 #pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    Dsh[3 * (4 * g + sub) + a] = UD[(ic * GT + g) * 16 + 4 + 3 * sub + a];
+                    for (int a = 0; a < 3; ++a)
+                        Dsh[3 * (4 * g + sub) + a] = UD[(ic * GT + g) * 16 + 4 + 3 * sub + a];
+            }
             wave_lds_sync();
             const int64_t base = wb + pl;   // the particle's column in the table
             // Lines in flight: v holds the loads of the next stage (the
@@ -659,14 +670,14 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                 const RowLines<OFF32> gl(geo, rw, 1, lane);
                 gl.load(0, v);
             }
-            for (int32_t kk = 0; kk < kmax; kk += 4) {
+            for (int32_t kk = 0; kk < kmax; kk += Q) {
                 const int32_t k = kk + sub;
                 const bool valid = k < nn;
                 const int32_t t = tc;
                 // (slot 0 of the tile's table exists once kmax > 0: no branch
                 // around the load, whose wait would then be a full one)
-                const int32_t tl = task[base + 64 * (int64_t)(k + 4 < nn ? k + 4 : 0)];
-                const int32_t tn = k + 4 < nn ? tl : (int32_t)ic;
+                const int32_t tl = task[base + 64 * (int64_t)(k + Q < nn ? k + Q : 0)];
+                const int32_t tn = k + Q < nn ? tl : (int32_t)ic;
                 const bool mirror = t < 0;
                 const int32_t j = t & 0x7fffffff;
                 const RowLines<OFF32> ul(UD, rw, GT, lane);
@@ -762,16 +773,18 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                 tc = tn;
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // the 4 lanes' partial sums, combined by a fixed butterfly
+            // the Q lanes' partial sums, combined by a fixed butterfly
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q) {
                 quad_sum<4>(acc[q]);
+                if constexpr (Q == 8) acc[q] += __shfl_xor(acc[q], 4, 64);
+            }
         }
     }
     // every wave's deposits are in its copy of the accumulator
     __syncthreads();
     // update, post-update guard, ledger, photon budget: the first lane of each
-    // particle; its sum is its own partial sums less the 4 waves' rows, in
+    // particle; its sum is its own partial sums less the waves' rows, in
     // that fixed order
     const int64_t i = t0 + pl;
     const bool owner = wave_live && sub == 0 && i < n;
@@ -784,7 +797,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int v = 0; v < kBlock / 64; ++v) acc[q] -= mir[v][pl * MS + q];
+            for (int v = 0; v < Q; ++v) acc[q] -= mir[v][pl * MS + q];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (touched) {
@@ -802,7 +815,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int v = 0; v < kBlock / 64; ++v) acc[q] -= mir[v][pl * MS + q];
+            for (int v = 0; v < Q; ++v) acc[q] -= mir[v][pl * MS + q];
         if constexpr (BIN) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -850,7 +863,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
     }
     if (chk != chk) atomicOr(status, ST_NONFINITE);
     if (partials)
-        block_reduce_store<2 * G>(red, partials + blk * 2 * GT, smem,
+        block_reduce_store<2 * G, Q>(red, partials + blk * 2 * GT, smem,
                                   [&](int p) { return p < G ? g0 + p : GT + g0 + p - G; });
     if (counts) {
         int64_t v0 = wave_sum_i64(cE), v1 = wave_sum_i64(cF), v2 = wave_sum_i64(gE),
@@ -1031,6 +1044,8 @@ void launch_finalize(rt_ctx *ctx, int64_t nb, const double *part, double *Q, dou
 // rows of block partials the FP64 transport writes (one per tile)
 inline int64_t transport64_rows(int64_t n) { return (n + kTile - 1) / kTile; }
 
+constexpr int64_t kWideTiles = 256, kThreeTiles = 512;
+
 // The tile transport of G groups of all GT, or of slices of G of them; accm: one
 // tick of the individual time steps.
 template <int G, bool WHOLE>
@@ -1041,15 +1056,37 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
     // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
     const bool off32 = (uint64_t)n * 128u * ctx->p.groups < (uint64_t(1) << 32);
     const unsigned grid = (unsigned)xcd_grid(nt * (WHOLE ? 1 : sl.count));
-#define RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, BIN_)                                                 \
-    k_transport64_tile<G, WHOLE, OFF32_, HLL_, IVA_, BIN_><<<grid, kBlock, 0, ctx->stream>>>(    \
+    // lanes per particle and waves per SIMD: see k_transport64_tile
+    const bool wide = WHOLE && nt <= kWideTiles, three = nt > kThreeTiles;
+#define RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, Q_, W_)                                      \
+    k_transport64_tile<G, WHOLE, OFF32_, HLL_, IVA_, BIN_, Q_, W_>                               \
+        <<<grid, 64 * Q_, 0, ctx->stream>>>(                                                     \
         n, nt, sl, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, ctx->p.c_red,       \
         ctx->p.box, Uout, partials, (unsigned long long *)counts, Uung, ctx->status,             \
         (const double2 *)ctx->hll_table, tick, accm, ctx->bin8 ? ctx->bin8 + n : nullptr)
+#define RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, BIN_)                                                 \
+    do {                                                                                         \
+        if constexpr (WHOLE && OFF32_) {                                                         \
+            if (wide) {                                                                          \
+                RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, 8, 2);                               \
+                break;                                                                           \
+            }                                                                                    \
+        }                                                                                        \
+        if constexpr (G == 1 && OFF32_ && !HLL_) {                                               \
+            if (three) {                                                                         \
+                RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, 4, 3);                               \
+                break;                                                                           \
+            }                                                                                    \
+        }                                                                                        \
+        RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, 4, 2);                                       \
+    } while (0)
 #define RT_TILE_LAUNCH_B(OFF32_, HLL_, IVA_)                                                     \
     do {                                                                                         \
-        if (accm) RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, true);                                      \
-        else RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, false);                                          \
+        if (accm) {                                                                              \
+            RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, true);                                            \
+        } else {                                                                                 \
+            RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, false);                                           \
+        }                                                                                        \
     } while (0)
 #define RT_TILE_LAUNCH_S(HLL_, IVA_)                                                             \
     do {                                                                                         \
@@ -1063,6 +1100,7 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
 #undef RT_TILE_LAUNCH_S
 #undef RT_TILE_LAUNCH_B
 #undef RT_TILE_LAUNCH
+#undef RT_TILE_LAUNCH_QW
 }
 
 void launch_transport64(rt_ctx *ctx, const double *UD, const double *dt, double *Uout,

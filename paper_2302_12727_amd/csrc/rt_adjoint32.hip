@@ -29,17 +29,22 @@ __global__ __launch_bounds__(kBlock) void k_adj_guard32(int64_t n, const float *
 
 // Exchange among the 4 lanes of a quad: v[u] of lane m becomes v[m] of lane u.
 __device__ __forceinline__ void quad_transpose(float (&v)[4], int sub) {
+    // (values, not elements, in the conditions: a chosen element would put the
+    // array into memory)
+    const bool o1 = sub & 1, o2 = sub & 2;
 #pragma unroll
     for (int r = 0; r < 4; r += 2) {
-        const float t = quad_xor<1>((sub & 1) ? v[r] : v[r + 1]);
-        if (sub & 1) v[r] = t;
-        else v[r + 1] = t;
+        const float a = v[r], b = v[r + 1];
+        const float t = quad_xor<1>(o1 ? +a : +b);
+        v[r] = o1 ? +t : +a;
+        v[r + 1] = o1 ? +b : +t;
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const float t = quad_xor<2>((sub & 2) ? v[r] : v[r + 2]);
-        if (sub & 2) v[r] = t;
-        else v[r + 2] = t;
+        const float a = v[r], b = v[r + 2];
+        const float t = quad_xor<2>(o2 ? +a : +b);
+        v[r] = o2 ? +t : +a;
+        v[r + 2] = o2 ? +b : +t;
     }
 }
 
@@ -57,7 +62,7 @@ __device__ __forceinline__ void quad_transpose(float (&v)[4], int sub) {
 // and with them dL, round differently, and it was no faster: 300 us.)
 // HLL and IVA as in the FP64 pass (the FP32 table, the FP32 Ivanova surfaces of
 // the FP32C transport).
-template <bool HLL, bool IVA>
+template <bool OFF32, bool HLL, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void
 k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
                   const double *__restrict__ geo, const int32_t *__restrict__ nbr,
@@ -66,7 +71,7 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
                   const double *__restrict__ dtp, double c, double box, float *__restrict__ R,
                   const float2 *__restrict__ hll, const double *__restrict__ ivan) {
     static_assert(kBlock == 256, "a block of 4 waves x 16 particles per column block");
-    __shared__ float stage[kBlock / 64][64 * kStage32];
+    __shared__ __attribute__((aligned(16))) float stage[kBlock / 64][64 * kStage32];
     const int64_t bg = xcd_block(nb * G);
     if (bg >= nb * G) return;
     const int64_t blk = bg / G;
@@ -119,12 +124,12 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
         // the next iteration's neighbour, and its geometry row, are in flight
         // while this one is evaluated
         int32_t jn = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
-        int64_t row[4];
-        float4 v[4];
+        uint32_t row[4];
+        fvec4 v[4];
         {
 #pragma unroll
             for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
-            load_rows32(geo32, row, lane, v);
+            load_rows32<OFF32>(geo32, row, lane, v);
         }
         for (int32_t kk = 0; kk < kmax; kk += 4) {
             const int32_t k = kk + sub;
@@ -137,16 +142,16 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
             store_rows32(v, sb, lane);          // the geometry rows
             // the group's record rows and cotangents in one round trip
             {
-                int64_t rowg[4];
+                uint32_t rowg[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g0;
-                load_rows32(UD, rowg, lane, v);
+                load_rows32<OFF32>(UD, rowg, lane, v);
             }
-            const float4 Ll = *reinterpret_cast<const float4 *>(lam2 + ((int64_t)j * G + g0) * 4);
+            const fvec4 Ll = *reinterpret_cast<const fvec4 *>(lam2 + ((int64_t)j * G + g0) * 4);
             PairGeo32 pg;
-            pair_geometry32(pkx, pky, pkz, iHk, hk, Bk, sb + lane * kStage32, box, ibox, pg);
+            const Row32 rl(sb, lane);
+            pair_geometry32(pkx, pky, pkz, iHk, hk, Bk, rl, box, ibox, pg);
             if (IVA) {                          // the same pair with the Ivanova surface
-                const float *rl = sb + lane * kStage32;
                 const double *gd = ivan + 4 * (int64_t)j;
                 const float gl[3] = {(float)gd[0], (float)gd[1], (float)gd[2]};
                 const float r = sqrt32(pg.sx * pg.sx + pg.sy * pg.sy + pg.sz * pg.sz);
@@ -154,7 +159,7 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
                                   pg.Ax, pg.Ay, pg.Az);
                 pg.An = sqrt32(pg.Ax * pg.Ax + pg.Ay * pg.Ay + pg.Az * pg.Az);
             }
-            const float dtVl = dtf * rcp32(sb[lane * kStage32 + F_V]);
+            const float dtVl = dtf * rcp32(rl[F_V]);
             const bool use = valid && pg.An > 0.0f;
             // the stages in program order (see the transport)
             __builtin_amdgcn_sched_barrier(0);
@@ -162,11 +167,9 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
             {                                   // the next iteration's geometry rows
 #pragma unroll
                 for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
-                load_rows32(geo32, row, lane, v);
+                load_rows32<OFF32>(geo32, row, lane, v);
             }
-            float Rl[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage32 + q];
+            const Row32 Rl(sb, lane);
             float qLp[4], qRp[4], qL[4], qR[4];
             bool own_slope[4];
 #pragma unroll
@@ -249,7 +252,8 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
     const float b00 = Bk[0] * iV, b01 = Bk[1] * iV, b02 = Bk[2] * iV;
     const float b11 = Bk[3] * iV, b12 = Bk[4] * iV, b22 = Bk[5] * iV;
     float *o = R + (i * G + g0) * 16;
-    o[sub] = (float)((double)(sub == 0 ? Li[0] : sub == 1 ? Li[1] : sub == 2 ? Li[2] : Li[3]) + aU.value());
+    o[sub] = (float)((double)(sub == 0 ? +Li[0] : sub == 1 ? +Li[1] : sub == 2 ? +Li[2] : +Li[3]) +
+                     aU.value());
     o[4 + 3 * sub + 0] = b00 * aD[0] + b01 * aD[1] + b02 * aD[2];
     o[4 + 3 * sub + 1] = b01 * aD[0] + b11 * aD[1] + b12 * aD[2];
     o[4 + 3 * sub + 2] = b02 * aD[0] + b12 * aD[1] + b22 * aD[2];
@@ -257,14 +261,14 @@ k_adj_pair32(int64_t n, int64_t nb, int G, const float *__restrict__ geo32,
 
 // Q lanes share a particle, each taking every Q-th neighbour slot; the
 // per-lane compensated sums are combined in FP64 by a fixed butterfly.
-template <int G, int Q = 1>
+template <int G, int Q, bool OFF32>
 __global__ __launch_bounds__(kBlock) void k_adj_grad32(
     int64_t n, int64_t nb, const float *__restrict__ geo32, const int32_t *__restrict__ nbr,
     const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_nbr,
     const float *__restrict__ R, float *__restrict__ lam, double box) {
     static_assert(Q == 1 || Q == 2 || Q == 4, "lanes per particle: 1, 2 or 4");
     constexpr int NQ = 4 * G, PW = 64 / Q, PB = kBlock / Q;
-    __shared__ float stage[kBlock / 64][64 * kStage32];
+    __shared__ __attribute__((aligned(16))) float stage[kBlock / 64][64 * kStage32];
     const int64_t blk = xcd_block(nb);
     if (blk >= nb) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -302,32 +306,23 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad32(
             const bool valid = k < nn;
             const int32_t j = jn;
             jn = k + Q < nn ? nbr[base + 64 * (int64_t)(k + Q)] : (int32_t)ic;
-            int64_t row[4];
+            uint32_t row[4];
 #pragma unroll
             for (int m = 0; m < 4; ++m) row[m] = __shfl(j, 16 * m + (lane >> 2), 64);
             // all rows of this slot in flight before the first is staged
             constexpr int GC = G < 6 ? G : 6;
-            float4 vp[4], vr[GC][4];
-            load_rows32(geo32, row, lane, vp);
+            fvec4 vp[4], vr[GC][4];
+            load_rows32<OFF32>(geo32, row, lane, vp);
 #pragma unroll
             for (int g = 0; g < GC; ++g) {
-                int64_t rowg[4];
+                uint32_t rowg[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g;
-                load_rows32(R, rowg, lane, vr[g]);
+                load_rows32<OFF32>(R, rowg, lane, vr[g]);
             }
             store_rows32(vp, sb, lane);
-            const float *rl = sb + lane * kStage32;
-            double xl[3];
-            {
-                union { float f[2]; double d; } u;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    u.f[0] = rl[2 * a];
-                    u.f[1] = rl[2 * a + 1];
-                    xl[a] = u.d;
-                }
-            }
+            const Row32 rl(sb, lane);
+            const double xl[3] = {rl.pos(0), rl.pos(1), rl.pos(2)};
             const float sx = (float)min_image(xl[0] - px, box, ibox);
             const float sy = (float)min_image(xl[1] - py, box, ibox);
             const float sz = (float)min_image(xl[2] - pz, box, ibox);
@@ -343,17 +338,17 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad32(
 #pragma unroll
                     for (int g = 0; g < GC; ++g) {
                         if (c0 + g >= G) break;
-                        int64_t rowg[4];
+                        uint32_t rowg[4];
 #pragma unroll
                         for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + c0 + g;
-                        load_rows32(R, rowg, lane, vr[g]);
+                        load_rows32<OFF32>(R, rowg, lane, vr[g]);
                     }
                 }
 #pragma unroll
                 for (int g = 0; g < GC; ++g) {
                     if (c0 + g >= G) break;
                     store_rows32(vr[g], sb, lane);
-                    const float *Rl = sb + lane * kStage32;
+                    const Row32 Rl(sb, lane);
 #pragma unroll
                     for (int m = 0; m < 4; ++m)
                         acc[4 * (c0 + g) + m].add(
@@ -399,10 +394,17 @@ void launch(rt_ctx *ctx, const float *UD, const float *Uung, const float *lam_ne
     k_adj_guard32<G><<<nblk(n * G), kBlock, 0, st>>>(n, Uung, lam_next, lam2, (float)ctx->p.c_red);
     const float2 *tab = (const float2 *)ctx->hll_table32;
     const bool iva = ctx->surfaces == RT_IVANOVA;
-#define RT_ADJ32_PAIR_LAUNCH(HLL_, IVA_)                                                       \
-    k_adj_pair32<HLL_, IVA_><<<(unsigned)xcd_grid(nt * G), kBlock, 0, st>>>(              \
+    // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
+    const bool off32 = (uint64_t)n * 64u * G < (uint64_t(1) << 32);
+#define RT_ADJ32_PAIR_LAUNCH_O(OFF32_, HLL_, IVA_)                                             \
+    k_adj_pair32<OFF32_, HLL_, IVA_><<<(unsigned)xcd_grid(nt * G), kBlock, 0, st>>>(           \
         n, nt, G, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD, lam2, dt,    \
         ctx->p.c_red, ctx->p.box, R, tab, ctx->ivan)
+#define RT_ADJ32_PAIR_LAUNCH(HLL_, IVA_)                                                       \
+    do {                                                                                       \
+        if (off32) RT_ADJ32_PAIR_LAUNCH_O(true, HLL_, IVA_);                                   \
+        else RT_ADJ32_PAIR_LAUNCH_O(false, HLL_, IVA_);                                        \
+    } while (0)
     if (ctx->solver == RT_HLL) {
         if (iva) RT_ADJ32_PAIR_LAUNCH(true, true);
         else RT_ADJ32_PAIR_LAUNCH(true, false);
@@ -411,9 +413,14 @@ void launch(rt_ctx *ctx, const float *UD, const float *Uung, const float *lam_ne
         else RT_ADJ32_PAIR_LAUNCH(false, false);
     }
 #undef RT_ADJ32_PAIR_LAUNCH
+#undef RT_ADJ32_PAIR_LAUNCH_O
     const int64_t ng = (n + kBlock / kAGQ32 - 1) / (kBlock / kAGQ32);
-    k_adj_grad32<G, kAGQ32><<<(unsigned)xcd_grid(ng), kBlock, 0, st>>>(
-        n, ng, ctx->geo32, ctx->nbr, ctx->wave_base, ctx->n_nbr, R, lam, ctx->p.box);
+    if (off32)
+        k_adj_grad32<G, kAGQ32, true><<<(unsigned)xcd_grid(ng), kBlock, 0, st>>>(
+            n, ng, ctx->geo32, ctx->nbr, ctx->wave_base, ctx->n_nbr, R, lam, ctx->p.box);
+    else
+        k_adj_grad32<G, kAGQ32, false><<<(unsigned)xcd_grid(ng), kBlock, 0, st>>>(
+            n, ng, ctx->geo32, ctx->nbr, ctx->wave_base, ctx->n_nbr, R, lam, ctx->p.box);
 }
 
 }  // namespace

@@ -7,7 +7,9 @@
 namespace gearrt {
 namespace {
 
-constexpr int kStage32 = 17;   // floats per staged 16-float row (bank padding)
+// four floats as one 16-byte access (a native vector: copies stay in registers)
+typedef float fvec4 __attribute__((ext_vector_type(4)));
+constexpr int kStage32 = 16;   // floats per staged row (its pieces are swizzled, see store_rows32)
 
 // Hardware FP32 reciprocal and square root (about one ulp).  FP32 denormals are
 // flushed on this path: the square root of a product that underflowed is 0
@@ -131,32 +133,52 @@ __device__ __forceinline__ float minmod32(float a, float b) {
 // Copy one 16-float (64-byte) row per lane's neighbour into the wave's stage
 // buffer: 4 loads, 4 lanes per row, 16 rows per load.  Load and store halves
 // are separate so that several rows can be in flight before the first store.
-__device__ __forceinline__ void load_rows32(const float *__restrict__ src, const int64_t (&row)[4],
-                                            int lane, float4 (&v)[4]) {
-    const int piece = lane & 3;
+// OFF32: the rows' byte offsets fit 32 bits (one instruction per load against
+// five).  In LDS the 16-byte pieces of row r lie in the order piece ^ (r / 4 mod
+// 4), so that the 16-byte stores and loads of neighbouring lanes fall on
+// different banks.  (Rows of 17 floats took 4- and 8-byte accesses, twice as
+// many; both together, with the guard counts only where asked for, took the
+// 3-group 128^3 transport from 1.92 to 1.79 ms, that of 4 groups of 150 thousand
+// clustered particles from 333 to 313 us, and its adjoint of 58 thousand from
+// 336 to 300 us.)
+template <bool OFF32>
+__device__ __forceinline__ void load_rows32(const float *__restrict__ src,
+                                            const uint32_t (&row)[4], int lane, fvec4 (&v)[4]) {
+    const uint32_t piece = lane & 3;
 #pragma unroll
     for (int m = 0; m < 4; ++m)
-        v[m] = *reinterpret_cast<const float4 *>(src + 16 * row[m] + 4 * piece);
+        v[m] = OFF32 ? *reinterpret_cast<const fvec4 *>(reinterpret_cast<const char *>(src) +
+                                                         (64u * row[m] + 16u * piece))
+                     : *reinterpret_cast<const fvec4 *>(src + 16 * (int64_t)row[m] + 4 * piece);
 }
-__device__ __forceinline__ void store_rows32(const float4 (&v)[4], float *sb, int lane) {
+__device__ __forceinline__ void store_rows32(const fvec4 (&v)[4], float *sb, int lane) {
     const int piece = lane & 3, slot = lane >> 2;
     wave_lds_sync32();
+    fvec4 *d = reinterpret_cast<fvec4 *>(sb) + 4 * slot + (piece ^ ((slot >> 2) & 3));
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        float *d = sb + (16 * m + slot) * kStage32 + 4 * piece;
-        d[0] = v[m].x;
-        d[1] = v[m].y;
-        d[2] = v[m].z;
-        d[3] = v[m].w;
-    }
+    for (int m = 0; m < 4; ++m) d[64 * m] = v[m];   // row 16 m + slot
     wave_lds_sync32();
 }
-__device__ __forceinline__ void stage_rows32(const float *__restrict__ src,
-                                             const int64_t (&row)[4], float *sb, int lane) {
-    float4 v[4];
-    load_rows32(src, row, lane, v);
-    store_rows32(v, sb, lane);
-}
+// The lane's staged row.
+struct Row32 {
+    float f[16];
+    __device__ __forceinline__ Row32(const float *sb, int lane) {
+        const fvec4 *r = reinterpret_cast<const fvec4 *>(sb) + 4 * lane;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const fvec4 t = r[c ^ ((lane >> 2) & 3)];
+            f[4 * c] = t.x;
+            f[4 * c + 1] = t.y;
+            f[4 * c + 2] = t.z;
+            f[4 * c + 3] = t.w;
+        }
+    }
+    __device__ __forceinline__ float operator[](int q) const { return f[q]; }
+    // position a of a geometry row, an FP64 number in its floats 2a and 2a + 1
+    __device__ __forceinline__ double pos(int a) const {
+        return __hiloint2double(__float_as_int(f[2 * a + 1]), __float_as_int(f[2 * a]));
+    }
+};
 
 // VJP of guard32 at its input state q (see guard64_vjp).
 __device__ __forceinline__ void guard32_vjp(const float q[4], float lam[4], float c) {
@@ -293,18 +315,9 @@ struct PairGeo32 {
 
 __device__ __forceinline__ void pair_geometry32(double pkx, double pky, double pkz, float iHk,
                                                 float hk, const float (&Bk)[6],
-                                                const float *__restrict__ rl, double box,
+                                                const Row32 &rl, double box,
                                                 double ibox, PairGeo32 &pg) {
-    double xl[3];
-    {
-        union { float f[2]; double d; } u;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            u.f[0] = rl[2 * a];
-            u.f[1] = rl[2 * a + 1];
-            xl[a] = u.d;
-        }
-    }
+    const double xl[3] = {rl.pos(0), rl.pos(1), rl.pos(2)};
     pg.sx = (float)min_image(xl[0] - pkx, box, ibox);
     pg.sy = (float)min_image(xl[1] - pky, box, ibox);
     pg.sz = (float)min_image(xl[2] - pkz, box, ibox);

@@ -110,9 +110,6 @@ __global__ __launch_bounds__(kBlock) void k_gradient32(
     if (chk != chk) atomicOr(status, ST_NONFINITE);
 }
 
-// four floats as one 16-byte access (a native vector: copies stay in registers)
-typedef float fvec4 __attribute__((ext_vector_type(4)));
-
 // Gradient from the block's neighbour union in FP32 (compensated mode, up to
 // 4 groups; see k_gradient64u): the union's FP32 states (16G bytes a row) and
 // FP64 positions are staged in LDS once per block of 64 particles, and every
@@ -289,7 +286,7 @@ k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const doub
 // thousand particles with them (1e-9).  A slice of 2 or 3 groups fits 168
 // registers and 3 waves per SIMD, at the price of the pair geometry once per
 // slice: 557 us a step with the 4 groups in one wave, now 503, the same bits.
-template <int G, bool HLL, bool BIN, bool IVA>
+template <int G, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void k_transport32(
     int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32, const double *__restrict__ geo,
     const int32_t *__restrict__ nbr, const int64_t *__restrict__ wave_base,
@@ -303,7 +300,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
     // HLL instantiation has no registers left for them)
     constexpr bool PIPE = !HLL;
     constexpr int NQ = 4 * G, Q = 4, PW = 64 / Q, PB = kBlock / Q;
-    __shared__ float stage[kBlock / 64][64 * kStage32];
+    __shared__ __attribute__((aligned(16))) float stage[kBlock / 64][64 * kStage32];
     __shared__ double smem[(kBlock / 64) * 2 * G];
     __shared__ unsigned long long scnt[4];
     // the block's particles and groups g0 .. g0 + G
@@ -376,12 +373,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
         // evaluated from the stage buffer.  The next iteration's neighbour
         // index is loaded one iteration ahead.
         int32_t jc = sub < nn ? nbr[base + 64 * (int64_t)sub] : (int32_t)ic;
-        int64_t row[4];
-        float4 v[4];
+        uint32_t row[4];
+        fvec4 v[4];
         if constexpr (PIPE) {
 #pragma unroll
             for (int m = 0; m < 4; ++m) row[m] = __shfl(jc, 16 * m + (lane >> 2), 64);
-            load_rows32(geo32, row, lane, v);
+            load_rows32<OFF32>(geo32, row, lane, v);
         }
         for (int32_t kk = 0; kk < kmax; kk += Q) {
             const int32_t k = kk + sub;
@@ -394,28 +391,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
             if constexpr (!PIPE) {
 #pragma unroll
                 for (int m = 0; m < 4; ++m) row[m] = __shfl(j, 16 * m + (lane >> 2), 64);
-                load_rows32(geo32, row, lane, v);
+                load_rows32<OFF32>(geo32, row, lane, v);
             }
             store_rows32(v, sb, lane);          // the geometry rows
             if constexpr (PIPE) {
-                int64_t rowg[4];
+                uint32_t rowg[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT;
-                load_rows32(UD, rowg, lane, v);
+                load_rows32<OFF32>(UD, rowg, lane, v);
             }
-            const float *rl = sb + lane * kStage32;
+            const Row32 rl(sb, lane);
             // separation in FP64 from FP64 positions, rounded once
-            double xl[3];
-            {
-                // the staged row holds the three doubles as six floats
-                union { float f[2]; double d; } u;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    u.f[0] = rl[2 * a];
-                    u.f[1] = rl[2 * a + 1];
-                    xl[a] = u.d;
-                }
-            }
+            const double xl[3] = {rl.pos(0), rl.pos(1), rl.pos(2)};
             const float sx = (float)min_image(xl[0] - pkx, box, ibox);
             const float sy = (float)min_image(xl[1] - pky, box, ibox);
             const float sz = (float)min_image(xl[2] - pkz, box, ibox);
@@ -459,25 +446,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
                 if constexpr (PIPE) {
                     __builtin_amdgcn_sched_barrier(0);
                 } else {
-                    int64_t rowg[4];
+                    uint32_t rowg[4];
 #pragma unroll
                     for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g;
-                    load_rows32(UD, rowg, lane, v);
+                    load_rows32<OFF32>(UD, rowg, lane, v);
                 }
                 store_rows32(v, sb, lane);      // group g's record rows
                 if constexpr (PIPE) {
                     if (g + 1 < G) {
-                        int64_t rowg[4];
+                        uint32_t rowg[4];
 #pragma unroll
                         for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g + 1;
-                        load_rows32(UD, rowg, lane, v);
+                        load_rows32<OFF32>(UD, rowg, lane, v);
                     } else {                    // the next iteration's geometry rows
 #pragma unroll
                         for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
-                        load_rows32(geo32, row, lane, v);
+                        load_rows32<OFF32>(geo32, row, lane, v);
                     }
                 }
-                const float *Rl = sb + lane * kStage32;
+                const Row32 Rl(sb, lane);
                 float qL[4], qR[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
@@ -503,8 +490,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
                 m1_flux32(qL[0], qL[1], qL[2], qL[3], Ax, Ay, Az, c2, ic2, FL);
                 m1_flux32(qR[0], qR[1], qR[2], qR[3], Ax, Ay, Az, c2, ic2, FR);
                 if (use) {
-                    cE += (f1 & 1) + (f2 & 1);
-                    cF += (f1 >> 1) + (f2 >> 1);
+                    if (counts) {
+                        cE += (f1 & 1) + (f2 & 1);
+                        cF += (f1 >> 1) + (f2 >> 1);
+                    }
 #pragma unroll
                     for (int m = 0; m < 4; ++m)
                         acc[4 * g + m].add(wkl * (w1 * FL[m] + w2 * FR[m] + w3 * (qR[m] - qL[m])));
@@ -649,7 +638,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
 // BIN: one tick of the individual-time-step scheme on the tiles, as in the
 // FP64 tile kernel (due pairs weighted by dt 2^min(b_k, b_l) in the
 // compensated sums, pending sums accm in FP64).
-template <int G, bool HLL, bool BIN, bool IVA>
+template <int G, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void
 k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                    const double *__restrict__ geo, const int32_t *__restrict__ task,
@@ -663,7 +652,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                    const double *__restrict__ ivan = nullptr) {
     constexpr int NQ = 4 * G, MS = NQ + 1;      // accumulator row, padded against bank conflicts
     static_assert(kTile == 64 && kBlock == 256, "a block of 4 waves x 16 particles per tile");
-    __shared__ float stage[kBlock / 64][64 * kStage32];
+    __shared__ __attribute__((aligned(16))) float stage[kBlock / 64][64 * kStage32];
     __shared__ double mir[kBlock / 64][kTile * MS];
     constexpr int DS = 3 * NQ + 1;              // own-gradient row, padded
     __shared__ float dsh[kBlock / 64][16 * DS];
@@ -742,13 +731,13 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
         // rows in flight across the previous stage; the task of the next iteration
         // is loaded one iteration ahead
         int32_t tc = sub < nn ? task[base + 64 * (int64_t)sub] : (int32_t)ic;
-        int64_t row[4];
-        float4 v[4];
+        uint32_t row[4];
+        fvec4 v[4];
         {
             const int32_t j = tc & 0x7fffffff;
 #pragma unroll
             for (int m = 0; m < 4; ++m) row[m] = __shfl(j, 16 * m + (lane >> 2), 64);
-            load_rows32(geo32, row, lane, v);
+            load_rows32<OFF32>(geo32, row, lane, v);
         }
         for (int32_t kk = 0; kk < kmax; kk += 4) {
             const int32_t k = kk + sub;
@@ -763,23 +752,14 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
             const int mr = mirror ? (j - (int32_t)t0) * MS : 0;   // the partner's row
             store_rows32(v, sb, lane);          // the geometry rows
             {
-                int64_t rowg[4];
+                uint32_t rowg[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G;
-                load_rows32(UD, rowg, lane, v);
+                load_rows32<OFF32>(UD, rowg, lane, v);
             }
-            const float *rl = sb + lane * kStage32;
+            const Row32 rl(sb, lane);
             // separation in FP64 from FP64 positions, rounded once
-            double xl[3];
-            {
-                union { float f[2]; double d; } u;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    u.f[0] = rl[2 * a];
-                    u.f[1] = rl[2 * a + 1];
-                    xl[a] = u.d;
-                }
-            }
+            const double xl[3] = {rl.pos(0), rl.pos(1), rl.pos(2)};
             const float sx = (float)min_image(xl[0] - pkx, box, ibox);
             const float sy = (float)min_image(xl[1] - pky, box, ibox);
             const float sz = (float)min_image(xl[2] - pkz, box, ibox);
@@ -824,17 +804,17 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                 __builtin_amdgcn_sched_barrier(0);
                 store_rows32(v, sb, lane);      // group g's record rows
                 if (g + 1 < G) {
-                    int64_t rowg[4];
+                    uint32_t rowg[4];
 #pragma unroll
                     for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g + 1;
-                    load_rows32(UD, rowg, lane, v);
+                    load_rows32<OFF32>(UD, rowg, lane, v);
                 } else {                        // the next iteration's geometry rows
                     const int32_t jn = tn & 0x7fffffff;
 #pragma unroll
                     for (int m = 0; m < 4; ++m) row[m] = __shfl(jn, 16 * m + (lane >> 2), 64);
-                    load_rows32(geo32, row, lane, v);
+                    load_rows32<OFF32>(geo32, row, lane, v);
                 }
-                const float *Rl = sb + lane * kStage32;
+                const Row32 Rl(sb, lane);
                 float qL[4], qR[4];
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
@@ -860,8 +840,10 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                 m1_flux32(qL[0], qL[1], qL[2], qL[3], Ax, Ay, Az, c2, ic2, FL);
                 m1_flux32(qR[0], qR[1], qR[2], qR[3], Ax, Ay, Az, c2, ic2, FR);
                 if (use) {
-                    cE += cnt2 * ((f1 & 1) + (f2 & 1));
-                    cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
+                    if (counts) {
+                        cE += cnt2 * ((f1 & 1) + (f2 & 1));
+                        cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
+                    }
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
                         const float phi = BIN ? wkl * (w1 * FL[m] + w2 * FR[m] + w3 * (qR[m] - qL[m]))
@@ -1050,31 +1032,39 @@ void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, 
     const float2 *tab = (const float2 *)ctx->hll_table32;
     const uint8_t *binm = ctx->bin8 ? ctx->bin8 + n : nullptr;
     unsigned long long *cnt = (unsigned long long *)counts;
-#define RT_STEP32_LAUNCH(HLL_, BIN_, IVA_)                                                       \
+    // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
+    const bool off32 = (uint64_t)n * 64u * ctx->p.groups < (uint64_t(1) << 32);
+#define RT_STEP32_LAUNCH(OFF32_, HLL_, BIN_, IVA_)                                               \
     do {                                                                                         \
         if constexpr (SLICES)                                                                    \
-            k_transport32<G, HLL_, BIN_, IVA_>                                                   \
+            k_transport32<G, OFF32_, HLL_, BIN_, IVA_>                                           \
                 <<<(unsigned)xcd_grid(nt * sl.count), kBlock, 0, ctx->stream>>>(                 \
                     n, nt, sl, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD,   \
                     dt, ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab,   \
                     ctx->ivan, tick, accm, binm);                                                \
         else                                                                                     \
-            k_transport32_tile<G, HLL_, BIN_, IVA_>                                              \
+            k_transport32_tile<G, OFF32_, HLL_, BIN_, IVA_>                                      \
                 <<<(unsigned)xcd_grid(nt), kBlock, 0, ctx->stream>>>(                            \
                     n, nt, ctx->geo32, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, \
                     ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab, tick, \
                     accm, binm, ctx->ivan);                                                      \
     } while (0)
+#define RT_STEP32_LAUNCH_B(OFF32_, HLL_, IVA_)                                                   \
+    do {                                                                                         \
+        if (accm) RT_STEP32_LAUNCH(OFF32_, HLL_, true, IVA_);                                    \
+        else RT_STEP32_LAUNCH(OFF32_, HLL_, false, IVA_);                                        \
+    } while (0)
 #define RT_STEP32_LAUNCH_S(HLL_, IVA_)                                                           \
     do {                                                                                         \
-        if (accm) RT_STEP32_LAUNCH(HLL_, true, IVA_);                                            \
-        else RT_STEP32_LAUNCH(HLL_, false, IVA_);                                                \
+        if (off32) RT_STEP32_LAUNCH_B(true, HLL_, IVA_);                                         \
+        else RT_STEP32_LAUNCH_B(false, HLL_, IVA_);                                              \
     } while (0)
     if (hll && iva) RT_STEP32_LAUNCH_S(true, true);
     else if (hll) RT_STEP32_LAUNCH_S(true, false);
     else if (iva) RT_STEP32_LAUNCH_S(false, true);
     else RT_STEP32_LAUNCH_S(false, false);
 #undef RT_STEP32_LAUNCH_S
+#undef RT_STEP32_LAUNCH_B
 #undef RT_STEP32_LAUNCH
 }
 

@@ -87,7 +87,7 @@ k_adj_pair64_tile(int64_t n, int64_t nb, int G, const double *__restrict__ geo,
                   double box, double *__restrict__ R, const double2 *__restrict__ hll) {
     constexpr int NQ = 4, MS = 17;              // accumulator row, padded
     static_assert(kTile == 64 && kBlock == 256, "a block of 4 waves x 16 particles per tile");
-    __shared__ double stage[kBlock / 64][64 * kStage];
+    __shared__ __attribute__((aligned(16))) double stage[kBlock / 64][64 * kStage];
     __shared__ double mir[kBlock / 64][kTile * MS];
     constexpr bool OWNL = HLL || IVA;
     constexpr int OS = 5 * NQ + 1;              // own row: U (NQ), D (3 NQ), lambda (NQ), pad
@@ -175,35 +175,28 @@ k_adj_pair64_tile(int64_t n, int64_t nb, int G, const double *__restrict__ geo,
             for (int m = 0; m < 8; ++m) rw[m] = __shfl(j, 8 * m + (lane >> 3), 64);
             const RowLines<OFF32> gl(geo, rw, 1, lane), ul(UD, rw, G, lane);
             {
-                double2 v[8];
+                dvec2 v[8];
                 gl.load(0, v);
                 store_lines(v, sb, lane);
             }
-            double rl[12];
-#pragma unroll
-            for (int q = 0; q < 12; ++q) rl[q] = sb[lane * kStage + q];
+            const Row64<> rl(sb, lane);
             PairGeo pg;
             if constexpr (IVA) {
-                const double gl[3] = {sb[lane * kStage + 13], sb[lane * kStage + 14],
-                                      sb[lane * kStage + 15]};
-                pair_geometry_ivanova64(rk, rl, gk, gl, box, ibox, pg);
+                const double gl[3] = {rl[13], rl[14], rl[15]};
+                pair_geometry_ivanova64(rk, rl.f, gk, gl, box, ibox, pg);
             } else {
-                pair_geometry64(rk, rl, box, ibox, pg);
+                pair_geometry64(rk, rl.f, box, ibox, pg);
             }
             const bool use = valid && pg.An > 0.0;
             const double dtVl = dt * rcp64(rl[R_V]);   // (about 1 ulp; no IEEE division per pair)
             // the record lines and the cotangent rows in one round trip
-            double2 v[8], vl[2];
+            dvec2 v[8], vl[2];
             ul.load(g0, v);
             load_rows4(lam2 + 4 * (g0), 4 * G, j, lane, vl);
             store_lines(v, sb, lane);
-            double Rl[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) Rl[q] = sb[lane * kStage + q];
+            const Row64<> Rl(sb, lane);
             store_rows4(vl, sb, lane);
-            double Ll[4];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) Ll[m] = sb[lane * kStage + m];
+            const Row64<> Ll(sb, lane);           // (its first 4)
             // forward recompute of this pair and group
             double qLp[4], qRp[4], qL[4], qR[4];
             bool slope_k[4], slope_l[4];
@@ -336,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad64(
     const int32_t *__restrict__ blist = nullptr) {
     static_assert(Q == 1 || Q == 2 || Q == 4, "lanes per particle: 1, 2 or 4");
     constexpr int NQ = 4 * G, PW = 64 / Q, PB = kBlock / Q;
-    __shared__ double stage[kBlock / 64][64 * kStage];
+    __shared__ __attribute__((aligned(16))) double stage[kBlock / 64][64 * kStage];
     const int64_t bx = xcd_block(nb);
     if (bx >= nb) return;
     const int64_t blk = blist ? (int64_t)blist[bx] : bx;
@@ -378,7 +371,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad64(
             for (int m = 0; m < 8; ++m) row[m] = __shfl(j, 8 * m + (lane >> 3), 64);
             // groups in chunks of at most GC records in flight
             constexpr int GC = G < 4 ? G : 4;
-            double2 vp[2], vr[GC][8];
+            dvec2 vp[2], vr[GC][8];
             load_rows4(geo, kRec, j, lane, vp);
 #pragma unroll
             for (int g = 0; g < GC; ++g) {
@@ -388,7 +381,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad64(
                 load_lines(R, rowg, lane, vr[g]);
             }
             store_rows4(vp, sb, lane);
-            const double *rl = sb + lane * kStage;
+            const Row64<> rl(sb, lane);
             const double sx = min_image(rl[0] - px, box, ibox);
             const double sy = min_image(rl[1] - py, box, ibox);
             const double sz = min_image(rl[2] - pz, box, ibox);
@@ -415,7 +408,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad64(
                 for (int g = 0; g < GC; ++g) {
                     if (c0 + g >= G) break;
                     store_lines(vr[g], sb, lane);
-                    const double *Rl = sb + lane * kStage;
+                    const Row64<> Rl(sb, lane);
 #pragma unroll
                     for (int m = 0; m < 4; ++m)
                         acc[4 * (c0 + g) + m] -=
@@ -451,7 +444,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_grad64(
 // the same operations as k_adj_grad64 with four lanes (rows past a list are
 // the own row with zero weights), so the two give identical bits; blocks whose
 // union did not fit are left to it, by list.
-typedef double dvec2a __attribute__((ext_vector_type(2)));
 template <int G, int W>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(W, W))) void
 k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
@@ -461,8 +453,8 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
               const double *__restrict__ R, double *__restrict__ lam, double box) {
     constexpr int Q = 4, UC = adj_union_cap(W);
     static_assert(kBlock == 256 && UC <= 1024, "64 particles per block");
-    __shared__ dvec2a upos[UC * 2];             // x, y | z, 1/H: the record's first line piece
-    __shared__ dvec2a urho[UC * 6];             // one group's 12 gradient cotangents
+    __shared__ dvec2 upos[UC * 2];             // x, y | z, 1/H: the record's first line piece
+    __shared__ dvec2 urho[UC * 6];             // one group's 12 gradient cotangents
     __shared__ int32_t uidx[UC];
     const int64_t blk = xcd_block(nb);
     if (blk >= nb) return;                      // whole block
@@ -473,8 +465,8 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
     __syncthreads();
     {   // positions and 1/H, all loads in flight
         constexpr int MP = (UC * 2 + kBlock - 1) / kBlock;
-        const dvec2a *G2 = reinterpret_cast<const dvec2a *>(geo);
-        dvec2a v[MP];
+        const dvec2 *G2 = reinterpret_cast<const dvec2 *>(geo);
+        dvec2 v[MP];
 #pragma unroll
         for (int r = 0; r < MP; ++r) {
             const int e = threadIdx.x + r * kBlock;
@@ -503,13 +495,13 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
     const uint64_t *gw = reinterpret_cast<const uint64_t *>(gloc + g0) + threadIdx.x;
     const int T = (kmax + Q - 1) / Q, ngq = (T + 3) / 4;        // this wave's iterations, groups
     double sgx = 0.0, sgy = 0.0, sgz = 0.0;
-    const dvec2a *R2 = reinterpret_cast<const dvec2a *>(R);
+    const dvec2 *R2 = reinterpret_cast<const dvec2 *>(R);
 #pragma unroll 1
     for (int g = 0; g < G; ++g) {
         __syncthreads();                        // the previous group's rows are read
         {   // group g's rows of rho, all loads in flight
             constexpr int MS = (UC * 6 + kBlock - 1) / kBlock;
-            dvec2a v[MS];
+            dvec2 v[MS];
 #pragma unroll
             for (int r = 0; r < MS; ++r) {
                 const int e = threadIdx.x + r * kBlock;
@@ -525,7 +517,7 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         if (kmax > 0) {
             auto pair = [&](int jl, bool valid) __attribute__((always_inline)) {
-                const dvec2a a = upos[2 * jl], b = upos[2 * jl + 1];
+                const dvec2 a = upos[2 * jl], b = upos[2 * jl + 1];
                 const double sx = min_image(a.x - px, box, ibox);
                 const double sy = min_image(a.y - py, box, ibox);
                 const double sz = min_image(b.x - pz, box, ibox);
@@ -538,7 +530,7 @@ k_adj_grad64u(int64_t n, int64_t nb, const double *__restrict__ geo,
                     sgz += wpi * sz;
                 }
                 const double wip = valid ? kern_w(r * iHl) : 0.0;
-                const dvec2a *Rl = urho + 6 * jl;
+                const dvec2 *Rl = urho + 6 * jl;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     // doubles 3m .. 3m+2 of the row: pieces (3m)/2 ..

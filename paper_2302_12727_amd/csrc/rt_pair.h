@@ -311,31 +311,69 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NP], double *__re
 // instead the wave fetches the 64 records it needs in this iteration with
 // coalesced loads (8 lanes per 128-byte line, 8 lines per instruction), writes
 // them to its own LDS buffer, and each lane then reads its neighbour's record
-// from LDS.  Records are padded to 17 doubles in LDS against bank conflicts.
-constexpr int kStage = 17;
+// from LDS.  There the 16-byte pieces of row r lie in the order piece ^ (r / 2
+// mod 8), so that the 16-byte stores and loads of neighbouring lanes fall on
+// different banks.  (Padded rows of 17 doubles, PAD, take 8-byte accesses, but
+// one address for a row's pieces instead of eight: used where registers are
+// short.  3 groups, transport of the 128^3 lattice 3.01 -> 2.97 ms, of 100
+// thousand clustered particles 1.82 -> 1.75 ms swizzled; one group at three
+// waves per SIMD 203 us swizzled, 23 registers spilled, 165 us padded, 64^3.)
+constexpr int kStage = 16;
+// two doubles as one 16-byte access (a native vector: copies stay in registers)
+typedef double dvec2 __attribute__((ext_vector_type(2)));
 
 // Copy one 16-double line per lane's neighbour (line base pointers src + 16 *
 // row[m]) into the wave's stage buffer: 8 loads, each lane moving 16 bytes.
 // The load and store halves are separate so that a kernel can put several
 // loads in flight before it stores the first of them.
 __device__ __forceinline__ void load_lines(const double *__restrict__ src, const int64_t (&row)[8],
-                                           int lane, double2 (&v)[8]) {
+                                           int lane, dvec2 (&v)[8]) {
     const int piece = lane & 7;
 #pragma unroll
     for (int m = 0; m < 8; ++m)
-        v[m] = *reinterpret_cast<const double2 *>(src + 16 * row[m] + 2 * piece);
+        v[m] = *reinterpret_cast<const dvec2 *>(src + 16 * row[m] + 2 * piece);
 }
-__device__ __forceinline__ void store_lines(const double2 (&v)[8], double *sb, int lane) {
+template <bool PAD = false>
+__device__ __forceinline__ void store_lines(const dvec2 (&v)[8], double *sb, int lane) {
     const int piece = lane & 7, slot = lane >> 3;
     wave_lds_sync();
+    if constexpr (PAD) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        double *d = sb + (8 * m + slot) * kStage + 2 * piece;
-        d[0] = v[m].x;
-        d[1] = v[m].y;
+        for (int m = 0; m < 8; ++m) {
+            double *d = sb + (8 * m + slot) * (kStage + 1) + 2 * piece;
+            d[0] = v[m].x;
+            d[1] = v[m].y;
+        }
+        wave_lds_sync();
+        return;
     }
+    dvec2 *d = reinterpret_cast<dvec2 *>(sb) + 8 * slot;
+    const int p0 = piece ^ (slot >> 1);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) d[64 * m + ((m & 1) ? p0 ^ 4 : p0)] = v[m];   // row 8 m + slot
     wave_lds_sync();
 }
+// The lane's staged row.
+template <bool PAD = false>
+struct Row64 {
+    double f[16];
+    __device__ __forceinline__ Row64(const double *sb, int lane) {
+        const dvec2 *r = reinterpret_cast<const dvec2 *>(sb) + 8 * lane;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const dvec2 t = r[c ^ ((lane >> 1) & 7)];
+            f[2 * c] = t.x;
+            f[2 * c + 1] = t.y;
+        }
+    }
+    __device__ __forceinline__ double operator[](int q) const { return f[q]; }
+};
+template <>
+struct Row64<true> {                            // read where it is used
+    const double *f;
+    __device__ __forceinline__ Row64(const double *sb, int lane) : f(sb + lane * (kStage + 1)) {}
+    __device__ __forceinline__ double operator[](int q) const { return f[q]; }
+};
 // Pointers to this lane's 16-byte piece of line `sel` of rows r[m] of a table
 // of rows `stride` lines long, src + 16 (stride r[m] + sel) + 2 (lane % 8),
 // for the 8 rows the lane helps to move.  The row offset is formed in 32 bits
@@ -349,9 +387,9 @@ __device__ __forceinline__ void row_ptrs(const double *__restrict__ src, const i
         p[m] = src + (((size_t)(uint32_t)(r[m] * stride) << 4) + extra);
 }
 // Load the pieces at p[m] + 16 g (line g beyond the one p points into).
-__device__ __forceinline__ void load_at(const double *const (&p)[8], int g, double2 (&v)[8]) {
+__device__ __forceinline__ void load_at(const double *const (&p)[8], int g, dvec2 (&v)[8]) {
 #pragma unroll
-    for (int m = 0; m < 8; ++m) v[m] = *reinterpret_cast<const double2 *>(p[m] + 16 * g);
+    for (int m = 0; m < 8; ++m) v[m] = *reinterpret_cast<const dvec2 *>(p[m] + 16 * g);
 }
 // This lane's 16-byte pieces of line g of rows r[m] of a table of rows
 // `stride` lines long, addressed either by 8 pointers (OFF32 false) or by 8
@@ -365,7 +403,7 @@ template <> struct RowLines<false> {
                                         int stride, int lane) {
         row_ptrs(src, r, stride, 0, lane, p);
     }
-    __device__ __forceinline__ void load(int g, double2 (&v)[8]) const { load_at(p, g, v); }
+    __device__ __forceinline__ void load(int g, dvec2 (&v)[8]) const { load_at(p, g, v); }
 };
 template <> struct RowLines<true> {
     const char *b;
@@ -376,45 +414,29 @@ template <> struct RowLines<true> {
 #pragma unroll
         for (int m = 0; m < 8; ++m) o[m] = (uint32_t)r[m] * (uint32_t)(128 * stride) + 16u * (lane & 7);
     }
-    __device__ __forceinline__ void load(int g, double2 (&v)[8]) const {
+    __device__ __forceinline__ void load(int g, dvec2 (&v)[8]) const {
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v[m] = *reinterpret_cast<const double2 *>(b + o[m] + 128u * g);
+        for (int m = 0; m < 8; ++m) v[m] = *reinterpret_cast<const dvec2 *>(b + o[m] + 128u * g);
     }
 };
-__device__ __forceinline__ void stage_lines(const double *__restrict__ src, const int64_t (&row)[8],
-                                            double *sb, int lane) {
-    double2 v[8];
-    load_lines(src, row, lane, v);
-    store_lines(v, sb, lane);
-}
-
 // Copy the 4-double row (row_stride doubles apart) of every lane's row index j
 // into the wave's stage buffer: 2 loads, 2 lanes per row, 32 rows per load.
 __device__ __forceinline__ void load_rows4(const double *__restrict__ src, int64_t row_stride,
-                                           int64_t j, int lane, double2 (&v)[2]) {
+                                           int64_t j, int lane, dvec2 (&v)[2]) {
     const int piece = lane & 1, slot = lane >> 1;
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         const int64_t r = __shfl(j, 32 * m + slot, 64);
-        v[m] = *reinterpret_cast<const double2 *>(src + row_stride * r + 2 * piece);
+        v[m] = *reinterpret_cast<const dvec2 *>(src + row_stride * r + 2 * piece);
     }
 }
-__device__ __forceinline__ void store_rows4(const double2 (&v)[2], double *sb, int lane) {
+__device__ __forceinline__ void store_rows4(const dvec2 (&v)[2], double *sb, int lane) {
     const int piece = lane & 1, slot = lane >> 1;
     wave_lds_sync();
+    dvec2 *d = reinterpret_cast<dvec2 *>(sb) + 8 * slot + (piece ^ ((slot >> 1) & 7));
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        double *d = sb + (32 * m + slot) * kStage + 2 * piece;
-        d[0] = v[m].x;
-        d[1] = v[m].y;
-    }
+    for (int m = 0; m < 2; ++m) d[256 * m] = v[m];   // row 32 m + slot
     wave_lds_sync();
-}
-__device__ __forceinline__ void stage_rows4(const double *__restrict__ src, int64_t row_stride,
-                                            int64_t j, double *sb, int lane) {
-    double2 v[2];
-    load_rows4(src, row_stride, j, lane, v);
-    store_rows4(v, sb, lane);
 }
 
 // Vector-Jacobian product of guard64 at its input state q (before the guard):

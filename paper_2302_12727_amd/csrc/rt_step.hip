@@ -34,7 +34,6 @@ __global__ void k_inject(int32_t ngas, int G, const int32_t *__restrict__ gptr,
 }
 
 // two doubles as one 16-byte access (a native vector: copies stay in registers)
-typedef double dvec2 __attribute__((ext_vector_type(2)));
 
 // Gradient record of particle i from its Q lanes' sums (every lane holds the
 // combined sums acc = sum_j (q_j - q_i) w_ij s_ij and the own state Ui): the
@@ -584,7 +583,8 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
     constexpr int NQ = 4 * G, MS = NQ + 1;     // accumulator row, padded against bank conflicts
     static_assert(kTile == 64 && (Q == 4 || Q == 8), "a tile is Q waves of 64 / Q particles");
     constexpr int PW = 64 / Q;                  // particles per wave
-    __shared__ double stage[Q][64 * kStage];
+    constexpr bool PAD = W == 3;                // rows padded, not swizzled: fewer registers
+    __shared__ __attribute__((aligned(16))) double stage[Q][64 * (PAD ? kStage + 1 : kStage)];
     __shared__ double mir[Q][kTile * MS];
     constexpr int DS = 3 * NQ + 1;              // own-gradient row, padded
     __shared__ double dsh[Q][PW * DS];
@@ -662,7 +662,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
             // the next iteration is loaded one iteration ahead.
             int32_t tc = sub < nn ? task[base + 64 * (int64_t)sub] : (int32_t)ic;
             int32_t rw[8];
-            double2 v[8];
+            dvec2 v[8];
             {
                 const int32_t j = tc & 0x7fffffff;
 #pragma unroll
@@ -681,23 +681,20 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                 const bool mirror = t < 0;
                 const int32_t j = t & 0x7fffffff;
                 const RowLines<OFF32> ul(UD, rw, GT, lane);
-                store_lines(v, sb, lane);       // the geometry lines
+                store_lines<PAD>(v, sb, lane);       // the geometry lines
                 ul.load(0, v);
-                double rl[12];
-#pragma unroll
-                for (int q = 0; q < 12; ++q) rl[q] = sb[lane * kStage + q];
+                const Row64<PAD> rl(sb, lane);
                 PairGeo pg;
                 if constexpr (IVA) {
-                    const double gl[3] = {sb[lane * kStage + 13], sb[lane * kStage + 14],
-                                          sb[lane * kStage + 15]};
-                    pair_geometry_ivanova64(rk, rl, gk, gl, box, ibox, pg);
+                    const double gl[3] = {rl[13], rl[14], rl[15]};
+                    pair_geometry_ivanova64(rk, rl.f, gk, gl, box, ibox, pg);
                 } else {
-                    pair_geometry64(rk, rl, box, ibox, pg);
+                    pair_geometry64(rk, rl.f, box, ibox, pg);
                 }
                 bool use = valid && pg.An > 0.0;
                 double wkl = 1.0;                   // BIN: time integration of the exchange
                 if constexpr (BIN) {
-                    const int32_t bl = (int32_t)sb[lane * kStage + 12];
+                    const int32_t bl = (int32_t)rl[12];
                     const int32_t bmin = bk < bl ? bk : bl;
                     use = use && (t1 & ((int64_t(1) << bmin) - 1)) == 0;
                     wkl = ldexp(dtp[0], bmin);
@@ -710,7 +707,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                     // the stages in program order: each one's loads stay in
                     // flight across the evaluation of the previous one
                     __builtin_amdgcn_sched_barrier(0);
-                    store_lines(v, sb, lane);   // group g's record lines
+                    store_lines<PAD>(v, sb, lane);   // group g's record lines
                     if (g + 1 < G) {
                         ul.load(g + 1, v);
                     } else {                    // the next iteration's geometry lines
@@ -720,7 +717,7 @@ k_transport64_tile(int64_t n, int64_t nb, Slices sl, const double *__restrict__ 
                         const RowLines<OFF32> gn(geo, rw, 1, lane);
                         gn.load(0, v);
                     }
-                    const double *Rl = sb + lane * kStage;
+                    const Row64<PAD> Rl(sb, lane);
                     double qL[4], qR[4];
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {

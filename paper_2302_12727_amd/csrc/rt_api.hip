@@ -141,7 +141,8 @@ void rt_destroy(rt_ctx *ctx) {
                     ctx->adj_buf, ctx->hll_table, ctx->hll_table32, ctx->vol, ctx->ivan,
                     ctx->bin8, ctx->task, ctx->n_task, ctx->tstat, ctx->urows, ctx->urow, ctx->gloc,
                     ctx->uown, ctx->ublk, ctx->goff, ctx->arows, ctx->arow, ctx->agloc,
-                    ctx->aown, ctx->ablk, ctx->dxpart, ctx->result};
+                    ctx->aown, ctx->ablk, ctx->dxpart, ctx->result,
+                    ctx->lrows, ctx->lrow, ctx->lblk};
     for (void *b : bufs) rt_free(ctx, b);
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
     delete ctx;

@@ -1149,7 +1149,8 @@ __global__ __launch_bounds__(64) void k_tasks(int64_t n, const int64_t *__restri
 // a key's position is kept beside it in the table, where its slots find it.
 // One block of 256 threads (4 per particle) per 64-particle block.  (A count
 // pass, a sort of 1024 keys whatever their number and a binary search per slot
-// took 2.6 ms for both unions of the 128^3 lattice, this 1.2 ms.)
+// took 2.6 ms for both unions of the 128^3 lattice, this 1.2 ms.)  blist: only
+// the listed blocks, whose rows go to urow and rows in the order of the list.
 constexpr int kUnionHash = 2048;
 
 __global__ __launch_bounds__(256) void k_union(int64_t n, int64_t nb, int cap,
@@ -1160,13 +1161,15 @@ __global__ __launch_bounds__(256) void k_union(int64_t n, int64_t nb, int cap,
                                                int32_t *__restrict__ urow,
                                                const int64_t *__restrict__ goff,
                                                uint16_t *__restrict__ gloc,
-                                               uint16_t *__restrict__ uown) {
+                                               uint16_t *__restrict__ uown,
+                                               const int32_t *__restrict__ blist = nullptr) {
     __shared__ int32_t keys[kUnionHash];
     __shared__ uint16_t val[kUnionHash];
     __shared__ int32_t srt[kUnionSort];
     __shared__ int32_t cnt;
-    const int64_t b = xcd_block(nb), t0 = b * 64;
-    if (b >= nb) return;                        // whole block
+    const int64_t bx = xcd_block(nb);
+    if (bx >= nb) return;                       // whole block
+    const int64_t b = blist ? (int64_t)blist[bx] : bx, t0 = b * 64;
     for (int e = threadIdx.x; e < kUnionHash; e += 256) keys[e] = -1;
     if (threadIdx.x == 0) cnt = 0;
     __syncthreads();
@@ -1199,7 +1202,7 @@ __global__ __launch_bounds__(256) void k_union(int64_t n, int64_t nb, int cap,
     __syncthreads();
     const int32_t m = cnt;
     const bool fits = m <= cap;                             // block-uniform
-    if (threadIdx.x == 0) rows[b] = fits ? m : 0;
+    if (threadIdx.x == 0) rows[bx] = fits ? m : 0;
     if (!fits) return;
     int size = 64;
     while (size < m) size <<= 1;
@@ -1226,7 +1229,7 @@ __global__ __launch_bounds__(256) void k_union(int64_t n, int64_t nb, int cap,
     };
     for (int e = threadIdx.x; e < m; e += 256) {
         const int32_t j = srt[e];
-        urow[b * cap + e] = j;
+        urow[bx * cap + e] = j;
         val[find(j)] = (uint16_t)e;
     }
     __syncthreads();
@@ -1254,9 +1257,11 @@ __global__ void k_union_width(int64_t nw, const int64_t *__restrict__ wave_base,
 
 // The blocks with more than cap rows or none (left to the staged kernel), in
 // order, with cap = cap3 (three waves per SIMD) if at least 95% of the blocks
-// fit it: out[0] how many, out[1] the waves per SIMD, then the list.  One block.
+// fit it: out[0] how many, out[1] the waves per SIMD, then the list (ids: of the
+// blocks so named).  One block.
 __global__ __launch_bounds__(1024) void k_union_left(int64_t nw, const int32_t *__restrict__ rows,
-                                                     int w0, int cap3, int32_t *__restrict__ out) {
+                                                     int w0, int cap3, int32_t *__restrict__ out,
+                                                     const int32_t *__restrict__ ids = nullptr) {
     __shared__ int32_t sm[1024];
     __shared__ int32_t base;
     const int t = threadIdx.x;
@@ -1281,7 +1286,8 @@ __global__ __launch_bounds__(1024) void k_union_left(int64_t nw, const int32_t *
         __syncthreads();
         int32_t at = base;
         for (int w = 0; w < wv; ++w) at += sm[w];
-        if (left) out[2 + at + __popcll(m & ((uint64_t(1) << lane) - 1))] = (int32_t)b;
+        if (left) out[2 + at + __popcll(m & ((uint64_t(1) << lane) - 1))] =
+                      ids ? ids[b] : (int32_t)b;
         __syncthreads();
         if (t == 0)
             for (int w = 0; w < 16; ++w) base += sm[w];
@@ -1601,6 +1607,30 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
     ctx->union_waves = res.left[1];
     ctx->n_ablk = res.aleft[0];
     ctx->adj_union_waves = res.aleft[1];
+    // larger unions for the few blocks over the capacity
+    ctx->n_lblk = 0;
+    ctx->n_sblk = ctx->n_ublk;
+    ctx->sblk = ctx->n_ublk > 0 ? ctx->ublk + 2 : nullptr;
+    if (ucap > 0 && union_cap_large(G) > ucap && ctx->n_ublk > 0 &&
+        ctx->n_ublk <= large_blocks(f64)) {
+        const int64_t most = large_blocks(f64);
+        const int64_t nl = ctx->n_ublk;
+        const int lcap = union_cap_large(G);
+        int32_t left = 0;
+        RESERVE(ctx->lrows, sizeof(int32_t) * most);
+        RESERVE(ctx->lrow, sizeof(int32_t) * most * lcap);
+        RESERVE(ctx->lblk, sizeof(int32_t) * (most + 2));
+        k_union<<<(unsigned)xcd_grid(nl), 256, 0, st>>>(n, nl, lcap, ctx->wave_base, ctx->n_gath,
+                                                        ctx->nbr, ctx->lrows, ctx->lrow, ctx->goff,
+                                                        ctx->gloc, ctx->uown, ctx->ublk + 2);
+        k_union_left<<<1, 1024, 0, st>>>(nl, ctx->lrows, 1, 0, ctx->lblk, ctx->ublk + 2);
+        HIP_OR_FAIL(hipGetLastError());
+        HIP_OR_FAIL(hipMemcpyAsync(&left, ctx->lblk, sizeof left, hipMemcpyDeviceToHost, st));
+        HIP_OR_FAIL(hipStreamSynchronize(st));
+        ctx->n_lblk = nl;
+        ctx->n_sblk = left;
+        ctx->sblk = ctx->lblk + 2;
+    }
     rt_free(ctx, list_mem);
     if ((rs = rt_ensure_partials(ctx)) != RT_OK) return rs;
     ctx->built = 1;

@@ -34,6 +34,13 @@ constexpr int union_cap3(int G) { return G == 3 ? 420 : 0; }
 // The compensated-FP32 gradient's union: FP32 states (16G bytes a row), FP64
 // positions, three blocks per CU (at most 53 KB each).
 constexpr int union_cap32(int G) { return G == 1 ? 1024 : G == 2 ? 880 : G == 3 ? 672 : G == 4 ? 576 : 0; }
+// Larger unions, one block per CU, for the blocks that the above leave, if they
+// are few: staging them per pair takes about as long however few they are (4
+// groups: 103 of 2338 blocks of a clustered set 82 us in FP32C, 17 us this way,
+// 299 of 12 thousand 80 against 13; FP64 15 of 1558 blocks 22 against 14 us,
+// 242 30 against 25, 476 even).
+constexpr int union_cap_large(int G) { return G >= 2 && G <= 4 ? kUnionSort : 0; }
+constexpr int64_t large_blocks(bool f64) { return f64 ? 256 : 512; }
 // Rows of a block's union in the adjoint's transposed gradient, which stages
 // one group at a time: position, 1/H and the 12 gradient cotangents (128
 // bytes) plus the row index, 132 bytes a row.  2 or 3 blocks of 4 waves per CU.
@@ -130,9 +137,15 @@ struct rt_ctx {
     uint16_t *gloc = nullptr;
     int64_t *goff = nullptr;     // [nwaves + 1], 1024 ceil(rows / 16) entries per block
     uint16_t *uown = nullptr;    // [n] a particle's position in its block's union
-    int32_t *ublk = nullptr;     // two counts (k_union_left), then the n_ublk blocks left to
-                                 // the staged gradient
+    int32_t *ublk = nullptr;     // two counts (k_union_left), then the n_ublk blocks over the
+                                 // capacity
     int64_t n_ublk = 0;
+    // of these, the n_lblk = n_ublk or 0 with a larger union (rows and stride
+    // union_cap_large, in the order of ublk), and the n_sblk left to the
+    // staged gradient, listed at sblk (in ublk or lblk)
+    int32_t *lrows = nullptr, *lrow = nullptr, *lblk = nullptr;
+    const int32_t *sblk = nullptr;
+    int64_t n_lblk = 0, n_sblk = 0;
     int union_waves = 2;         // waves per SIMD of the union gradient (capacity by it)
     // the same over the symmetric lists, for the FP64 adjoint's transposed
     // gradient (entries packed as gloc, at the same goff)

@@ -386,17 +386,19 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
               const uint16_t *__restrict__ gloc, const int64_t *__restrict__ goff,
               const uint16_t *__restrict__ uown, const int32_t *__restrict__ n_gath,
               const double *__restrict__ U, double *__restrict__ UD, int32_t *__restrict__ status,
-              double box, int64_t tick = 0) {
+              double box, int64_t tick = 0, const int32_t *__restrict__ blist = nullptr) {
     static_assert(Q == 4 && kBlock == 256, "one block of 64 particles per table column block");
-    constexpr int NQ = 4 * G, PU = 2 * G, UC = W == 3 ? union_cap3(G) : union_cap(G);
+    constexpr int UR = W == 1 ? union_cap_large(G) : union_cap(G);   // stride of the rows
+    constexpr int NQ = 4 * G, PU = 2 * G, UC = W == 3 ? union_cap3(G) : UR;
     static_assert(UC > 0 && UC <= kUnionSort, "union capacity");
     __shared__ dvec2 ust[UC * PU];
     __shared__ double upos[UC * 3];
     __shared__ int32_t uidx[UC];
-    const int64_t blk = xcd_block(nb);
-    if (blk >= nb) return;                      // whole block
-    const int64_t u0 = blk * union_cap(G);
-    const int32_t rows = urows[blk];
+    const int64_t bx = xcd_block(nb);
+    if (bx >= nb) return;                       // whole block
+    const int64_t blk = W == 1 ? (int64_t)blist[bx] : bx;
+    const int64_t u0 = bx * UR;
+    const int32_t rows = urows[bx];
     if (rows == 0 || rows > UC) return;                      // left to the staged gradient (whole block)
     if constexpr (BIN) {
         const int64_t ib = blk * (kBlock / Q) + threadIdx.x / Q;
@@ -1137,7 +1139,8 @@ void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
     constexpr int B = grad_block(G);
     if constexpr (union_cap(G) > 0 && kGQ == 4 && B == 256) {
         if (ctx->urows) {
-            // blocks whose union fits: from LDS; the others: staged, by list
+            // blocks whose union fits: from LDS; a few larger ones: too, one to a
+            // CU; the others: staged, by list
             const int64_t nw = ctx->nwaves;
 #define RT_UNION_LAUNCH(W_)                                                                    \
     k_gradient64u<G, kGQ, W_><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(            \
@@ -1150,10 +1153,18 @@ void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
                 RT_UNION_LAUNCH(2);
             }
 #undef RT_UNION_LAUNCH
-            if (ctx->n_ublk > 0)
-                k_gradient64<G, false, kGQ><<<(unsigned)xcd_grid(ctx->n_ublk), B, 0, ctx->stream>>>(
-                    ctx->p.n, ctx->n_ublk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
-                    U, UD, ctx->status, ctx->p.box, 0, ctx->ublk + 2);
+            if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0)
+                    k_gradient64u<G, kGQ, 1><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
+                                               ctx->stream>>>(
+                        ctx->p.n, ctx->n_lblk, ctx->geo, ctx->xs, ctx->lrow, ctx->lrows, ctx->gloc,
+                        ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, 0,
+                        ctx->ublk + 2);
+            }
+            if (ctx->n_sblk > 0)
+                k_gradient64<G, false, kGQ><<<(unsigned)xcd_grid(ctx->n_sblk), B, 0, ctx->stream>>>(
+                    ctx->p.n, ctx->n_sblk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
+                    U, UD, ctx->status, ctx->p.box, 0, ctx->sblk);
             return;
         }
     }
@@ -1186,10 +1197,18 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
                 RT_TICK_UNION_LAUNCH(2);
             }
 #undef RT_TICK_UNION_LAUNCH
-            if (ctx->n_ublk > 0)
-                k_gradient64<G, true, kGQ><<<(unsigned)xcd_grid(ctx->n_ublk), B, 0, ctx->stream>>>(
-                    n, ctx->n_ublk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
-                    U, UD, ctx->status, ctx->p.box, tick, ctx->ublk + 2);
+            if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0)
+                    k_gradient64u<G, kGQ, 1, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
+                                                     ctx->stream>>>(
+                        n, ctx->n_lblk, ctx->geo, ctx->xs, ctx->lrow, ctx->lrows, ctx->gloc,
+                        ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick,
+                        ctx->ublk + 2);
+            }
+            if (ctx->n_sblk > 0)
+                k_gradient64<G, true, kGQ><<<(unsigned)xcd_grid(ctx->n_sblk), B, 0, ctx->stream>>>(
+                    n, ctx->n_sblk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
+                    U, UD, ctx->status, ctx->p.box, tick, ctx->sblk);
             grad_done = true;
         }
     }

@@ -127,23 +127,24 @@ __global__ __launch_bounds__(kBlock) void k_gradient32(
 // left to k_gradient32 with one lane per particle.  BIN: only the particles
 // that end a step in tick `tick` recompute their record; a block none of
 // whose particles does so stages nothing.
-template <int G, bool BIN = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) void
+template <int G, bool BIN = false, bool LARGE = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LARGE ? 1 : 3, LARGE ? 1 : 3))) void
 k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const double *__restrict__ xs,
               const int32_t *__restrict__ urow, const int32_t *__restrict__ urows,
               const uint16_t *__restrict__ gloc, const int64_t *__restrict__ goff,
               const uint16_t *__restrict__ uown, const int32_t *__restrict__ n_gath,
               const float *__restrict__ U, float *__restrict__ UD, int32_t *__restrict__ status,
-              double box, int64_t tick = 0) {
-    constexpr int Q = 4, UC = union_cap32(G);
+              double box, int64_t tick = 0, const int32_t *__restrict__ blist = nullptr) {
+    constexpr int Q = 4, UC = LARGE ? union_cap_large(G) : union_cap32(G);
     static_assert(kBlock == 256 && UC > 0 && UC <= kUnionSort, "64 particles per block");
     __shared__ fvec4 ust[UC * G];              // G pieces of 16 bytes a row
     __shared__ double upos[UC * 3];
     __shared__ int32_t uidx[UC];
-    const int64_t blk = xcd_block(nb);
-    if (blk >= nb) return;                      // whole block
-    const int64_t u0 = blk * UC;
-    const int32_t rows = urows[blk];
+    const int64_t bx = xcd_block(nb);
+    if (bx >= nb) return;                       // whole block
+    const int64_t blk = LARGE ? (int64_t)blist[bx] : bx;
+    const int64_t u0 = bx * UC;
+    const int32_t rows = urows[bx];
     if (rows == 0) return;                      // left to k_gradient32 (whole block)
     if constexpr (BIN) {
         const int64_t ib = blk * (kBlock / Q) + threadIdx.x / Q;
@@ -1001,17 +1002,25 @@ template <int G>
 void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
     if constexpr (union_cap32(G) > 0 && kGQ32 == 1) {   // the union sums in one lane's order
         if (ctx->urows) {
-            // blocks whose union fits: from LDS; the others: one lane per
-            // particle (the same order), by list
+            // blocks whose union fits: from LDS; a few larger ones: too, one to a
+            // CU; the others: one lane per particle (the same order), by list
             const int64_t nw = ctx->nwaves;
             k_gradient32u<G><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(
                 ctx->p.n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box);
-            if (ctx->n_ublk > 0) {
-                const int64_t nl = (ctx->n_ublk + 3) / 4;
+            if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0)
+                    k_gradient32u<G, false, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
+                                                    ctx->stream>>>(
+                        ctx->p.n, ctx->n_lblk, ctx->geo32, ctx->xs, ctx->lrow, ctx->lrows, ctx->gloc,
+                        ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, 0,
+                        ctx->ublk + 2);
+            }
+            if (ctx->n_sblk > 0) {
+                const int64_t nl = (ctx->n_sblk + 3) / 4;
                 k_gradient32<G, 1><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     ctx->p.n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U,
-                    UD, ctx->status, ctx->p.box, 0, ctx->ublk + 2, ctx->n_ublk);
+                    UD, ctx->status, ctx->p.box, 0, ctx->sblk, ctx->n_sblk);
             }
             return;
         }
@@ -1102,11 +1111,19 @@ void launch_tick32(rt_ctx *ctx, float *U, float *UD, const double *dt, double *p
             k_gradient32u<G, true><<<(unsigned)xcd_grid(nw), kBlock, 0, ctx->stream>>>(
                 n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick);
-            if (ctx->n_ublk > 0) {
-                const int64_t nl = (ctx->n_ublk + 3) / 4;
+            if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0)
+                    k_gradient32u<G, true, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
+                                                   ctx->stream>>>(
+                        n, ctx->n_lblk, ctx->geo32, ctx->xs, ctx->lrow, ctx->lrows, ctx->gloc,
+                        ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick,
+                        ctx->ublk + 2);
+            }
+            if (ctx->n_sblk > 0) {
+                const int64_t nl = (ctx->n_sblk + 3) / 4;
                 k_gradient32<G, 1, true><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U, UD,
-                    ctx->status, ctx->p.box, tick, ctx->ublk + 2, ctx->n_ublk);
+                    ctx->status, ctx->p.box, tick, ctx->sblk, ctx->n_sblk);
             }
             grad_done = true;
         }

@@ -76,6 +76,21 @@ struct Slices {
 constexpr int slices_of_3(int G) { return G % 3 == 1 ? G / 3 - 1 : G / 3; }
 constexpr int slices_of_2(int G) { return (G - 3 * slices_of_3(G)) / 2; }
 
+// Up to this many blocks every group of several gets a block of its own: so few
+// leave the CUs waiting on the chains of single waves, and the groups share
+// nothing but the pair geometry.  2 and 3 groups, which else share a wave: two
+// blocks a CU (4000 clustered particles of 3 groups, step of 111 us with the
+// groups in one wave, 74 us; 12 thousand, 564 blocks, 84 against 94).  4, else
+// in two slices of one launch: three (12 thousand, 772 blocks, 107 against 119).
+// More, else in two launches one after the other: six (5 groups: 6000 particles
+// 130 -> 97 us, 16 thousand 197 -> 160; 8 groups: 8000 196 -> 162).  FP32C, four
+// waves per SIMD with one group, up to 4 groups: four blocks a CU (3 groups: 4000
+// particles 129 -> 82 us, 16 thousand 96 -> 79, 939 blocks even; 5 HLL groups:
+// 4000 356 -> 180).
+constexpr int64_t one_group_blocks(bool f64, int G) {
+    return G > 4 ? 1536 : !f64 ? 1024 : G == 4 ? 768 : 512;
+}
+
 struct TimerRec {
     std::string name;
     hipEvent_t a, b;

@@ -1044,16 +1044,6 @@ void launch_finalize(rt_ctx *ctx, int64_t nb, const double *part, double *Q, dou
 inline int64_t transport64_rows(int64_t n) { return (n + kTile - 1) / kTile; }
 
 constexpr int64_t kWideTiles = 256, kThreeTiles = 512;
-// Up to this many blocks every group of several gets a block of its own: so few
-// leave the CUs waiting on the chains of single waves, and the groups share
-// nothing but the pair geometry.  2 and 3 groups, which else share a wave: two
-// blocks a CU (4000 clustered particles of 3 groups, step of 111 us with the
-// groups in one wave, 74 us; 12 thousand, 564 blocks, 84 against 94).  4, else
-// in two slices of one launch: three (12 thousand, 772 blocks, 107 against 119).
-// More, else in two launches one after the other: six (5 groups: 6000 particles
-// 130 -> 97 us, 16 thousand 197 -> 160; 8 groups: 8000 196 -> 162).
-constexpr int64_t one_group_blocks(int G) { return G <= 3 ? 512 : G == 4 ? 768 : 1536; }
-
 // The tile transport of G groups of all GT, or of slices of G of them; accm: one
 // tick of the individual time steps.
 template <int G, bool WHOLE>
@@ -1117,7 +1107,7 @@ void launch_transport64(rt_ctx *ctx, const double *UD, const double *dt, double 
                         double *accm) {
     const int G = ctx->p.groups, s3 = slices_of_3(G), s2 = slices_of_2(G);
     const Slices sl{G, 0, s3};
-    if (G > 1 && transport64_rows(ctx->p.n) * G <= one_group_blocks(G)) {
+    if (G > 1 && transport64_rows(ctx->p.n) * G <= one_group_blocks(true, G)) {
         launch_tiles64<1, false>(ctx, Slices{G, 0, G}, UD, dt, Uout, partials, counts, Uung, tick,
                                  accm);
     } else if (G == 1) {

@@ -639,12 +639,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
 // BIN: one tick of the individual-time-step scheme on the tiles, as in the
 // FP64 tile kernel (due pairs weighted by dt 2^min(b_k, b_l) in the
 // compensated sums, pending sums accm in FP64).
-template <int G, bool OFF32, bool HLL, bool BIN, bool IVA>
+template <int G, bool WHOLE, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void
-k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
+k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32,
                    const double *__restrict__ geo, const int32_t *__restrict__ task,
                    const int64_t *__restrict__ wave_base, const int32_t *__restrict__ n_task,
-                   const float *__restrict__ UD, const double *__restrict__ dtp, double c,
+                   const float *__restrict__ UDall, const double *__restrict__ dtp, double c,
                    double box, float *__restrict__ Uout, double *__restrict__ partials,
                    unsigned long long *__restrict__ counts, float *__restrict__ Uung,
                    int32_t *__restrict__ status, const float2 *__restrict__ hll,
@@ -659,8 +659,13 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
     __shared__ float dsh[kBlock / 64][16 * DS];
     __shared__ double smem[(kBlock / 64) * 2 * G];
     __shared__ unsigned long long scnt[4];
-    const int64_t blk = xcd_block(nb);
-    if (blk >= nb) return;                      // whole block: no barrier is skipped
+    // the block's tile and its groups g0 .. g0 + G of the GT
+    const int GT = WHOLE ? G : sl.groups, nsl = WHOLE ? 1 : sl.count;
+    const int64_t bg = xcd_block(nb * nsl);
+    if (bg >= nb * nsl) return;                 // whole block: no barrier is skipped
+    const int64_t blk = WHOLE ? bg : bg / nsl;
+    const int g0 = WHOLE ? 0 : sl.first + (int)(bg - blk * nsl) * G;
+    const float *UD = UDall + 16 * g0;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int sub = lane & 3;
     const int64_t t0 = blk * kTile;             // the tile's first particle
@@ -694,7 +699,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
     float Ui[NQ];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const float *r = UD + (ic * G + g) * 16;
+        const float *r = UD + (ic * GT + g) * 16;
 #pragma unroll
         for (int m = 0; m < 4; ++m) Ui[4 * g + m] = r[m];
     }
@@ -706,7 +711,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
     for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-            Dsh[3 * (4 * g + sub) + a] = UD[(ic * G + g) * 16 + 4 + 3 * sub + a];
+            Dsh[3 * (4 * g + sub) + a] = UD[(ic * GT + g) * 16 + 4 + 3 * sub + a];
     wave_lds_sync32();
     Kahan acc[NQ];
 #pragma unroll
@@ -755,7 +760,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
             {
                 uint32_t rowg[4];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G;
+                for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT;
                 load_rows32<OFF32>(UD, rowg, lane, v);
             }
             const Row32 rl(sb, lane);
@@ -807,7 +812,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                 if (g + 1 < G) {
                     uint32_t rowg[4];
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) rowg[m] = row[m] * G + g + 1;
+                    for (int m = 0; m < 4; ++m) rowg[m] = row[m] * GT + g + 1;
                     load_rows32<OFF32>(UD, rowg, lane, v);
                 } else {                        // the next iteration's geometry rows
                     const int32_t jn = tn & 0x7fffffff;
@@ -841,16 +846,18 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
                 m1_flux32(qL[0], qL[1], qL[2], qL[3], Ax, Ay, Az, c2, ic2, FL);
                 m1_flux32(qR[0], qR[1], qR[2], qR[3], Ax, Ay, Az, c2, ic2, FR);
                 if (use) {
-                    if (counts) {
-                        cE += cnt2 * ((f1 & 1) + (f2 & 1));
-                        cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
-                    }
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
                         const float phi = BIN ? wkl * (w1 * FL[m] + w2 * FR[m] + w3 * (qR[m] - qL[m]))
                                               : w1 * FL[m] + w2 * FR[m] + w3 * (qR[m] - qL[m]);
                         acc[4 * g + m].add(phi);
                         if (mirror) atomicAdd(mw + mr + 4 * g + m, -(double)phi);
+                    }
+                    // (after the sums: before them the compiler rounds the tick's
+                    // product by itself, not within the compensated sum)
+                    if (counts) {
+                        cE += cnt2 * ((f1 & 1) + (f2 & 1));
+                        cF += cnt2 * ((f1 >> 1) + (f2 >> 1));
                     }
                 }
             }
@@ -879,7 +886,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             if (touched) {
-                double *a = accm + (i * G + g) * 4;
+                double *a = accm + (i * GT + g0 + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) a[m] += av[4 * g + m];
             }
@@ -897,7 +904,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
         if constexpr (BIN) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                double *a = accm + (i * G + g) * 4;
+                double *a = accm + (i * GT + g0 + g) * 4;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
                     av[4 * g + m] += a[m];
@@ -913,7 +920,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
             double q3 = (double)Ui[4 * g + 3] - dtV * av[4 * g + 3];
             const double Epre = q0;
             if (Uung) {
-                float *u = Uung + (i * G + g) * 4;
+                float *u = Uung + (i * GT + g0 + g) * 4;
                 u[0] = (float)q0;
                 u[1] = (float)q1;
                 u[2] = (float)q2;
@@ -937,7 +944,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
             }
             gE += f & 1;
             gF += f >> 1;
-            float *o = Uout + (i * G + g) * 4;
+            float *o = Uout + (i * GT + g0 + g) * 4;
             const float o0 = (float)q0, o1 = (float)q1, o2 = (float)q2, o3 = (float)q3;
             o[0] = o0;
             o[1] = o1;
@@ -967,7 +974,7 @@ k_transport32_tile(int64_t n, int64_t nb, const float *__restrict__ geo32,
             double s = 0.0;
             for (int u = 0; u < kBlock / 64; ++u) s += smem[u * 2 * G + threadIdx.x];
             const int p = threadIdx.x;
-            partials[blk * 2 * G + (p < G ? p : p)] = s;
+            partials[blk * 2 * GT + (p < G ? g0 + p : GT + g0 + p - G)] = s;
         }
     }
     if (counts) {
@@ -1033,7 +1040,7 @@ void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
 
 // Up to 3 groups on the tiles; more of them in slices of G from sl.first on
 // (see k_transport32).  accm: one tick of the individual time steps.
-template <int G, bool SLICES>
+template <int G, bool SLICES, bool TILES>
 void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, float *Uout,
                      double *partials, int64_t *counts, float *Uung, int64_t tick, double *accm) {
     const int64_t n = ctx->p.n, nt = rt_transport32_rows(n);
@@ -1045,16 +1052,16 @@ void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, 
     const bool off32 = (uint64_t)n * 64u * ctx->p.groups < (uint64_t(1) << 32);
 #define RT_STEP32_LAUNCH(OFF32_, HLL_, BIN_, IVA_)                                               \
     do {                                                                                         \
-        if constexpr (SLICES)                                                                    \
+        if constexpr (!TILES)                                                                    \
             k_transport32<G, OFF32_, HLL_, BIN_, IVA_>                                           \
                 <<<(unsigned)xcd_grid(nt * sl.count), kBlock, 0, ctx->stream>>>(                 \
                     n, nt, sl, ctx->geo32, ctx->geo, ctx->nbr, ctx->wave_base, ctx->n_nbr, UD,   \
                     dt, ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab,   \
                     ctx->ivan, tick, accm, binm);                                                \
         else                                                                                     \
-            k_transport32_tile<G, OFF32_, HLL_, BIN_, IVA_>                                      \
-                <<<(unsigned)xcd_grid(nt), kBlock, 0, ctx->stream>>>(                            \
-                    n, nt, ctx->geo32, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, \
+            k_transport32_tile<G, !SLICES, OFF32_, HLL_, BIN_, IVA_>                             \
+                <<<(unsigned)xcd_grid(nt * (SLICES ? sl.count : 1)), kBlock, 0, ctx->stream>>>(  \
+                    n, nt, sl, ctx->geo32, ctx->geo, ctx->task, ctx->wave_base, ctx->n_task, UD, dt, \
                     ctx->p.c_red, ctx->p.box, Uout, partials, cnt, Uung, ctx->status, tab, tick, \
                     accm, binm, ctx->ivan);                                                      \
     } while (0)
@@ -1081,19 +1088,26 @@ void launch_transport32(rt_ctx *ctx, const float *UD, const double *dt, float *U
                         double *partials, int64_t *counts, float *Uung, int64_t tick,
                         double *accm) {
     const int G = ctx->p.groups, s3 = slices_of_3(G), s2 = slices_of_2(G);
-    const Slices sl{G, 0, s3};
-    if (G == 1) {
-        launch_groups32<1, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    const Slices sl{G, 0, s3}, one{G, 0, G};
+    // a block for every group where the tiles are few (see one_group_blocks)
+    const bool few = G > 1 && rt_transport32_rows(ctx->p.n) * G <= one_group_blocks(false, G);
+    if (few && G <= 3) {
+        launch_groups32<1, true, true>(ctx, one, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    } else if (few) {
+        launch_groups32<1, true, false>(ctx, one, UD, dt, Uout, partials, counts, Uung, tick, accm);
+    } else if (G == 1) {
+        launch_groups32<1, false, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else if (G == 2) {
-        launch_groups32<2, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        launch_groups32<2, false, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else if (G == 3) {
-        launch_groups32<3, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+        launch_groups32<3, false, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else {
         if (s3 > 0)
-            launch_groups32<3, true>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick, accm);
+            launch_groups32<3, true, false>(ctx, sl, UD, dt, Uout, partials, counts, Uung, tick,
+                                            accm);
         if (s2 > 0)
-            launch_groups32<2, true>(ctx, Slices{G, 3 * s3, s2}, UD, dt, Uout, partials, counts,
-                                     Uung, tick, accm);
+            launch_groups32<2, true, false>(ctx, Slices{G, 3 * s3, s2}, UD, dt, Uout, partials,
+                                            counts, Uung, tick, accm);
     }
 }
 

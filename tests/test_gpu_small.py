@@ -60,3 +60,44 @@ def test_small_and_wide_transports(n, groups, solver, surfaces):
     log(f"n={n} G={groups} {solver} {surfaces}: states {err:.1e}, totals {qerr:.1e}")
     assert err < 1e-13 and qerr < 1e-13
     assert float((la - lb).abs().max()) < 1e-13 * float(qb.max())
+
+
+@pytest.mark.parametrize("n,groups,solver,surfaces", [
+    (2000, 2, "glf", "hopkins"), (2000, 3, "hll", "ivanova"), (21824, 3, "glf", "hopkins"),
+    (21889, 3, "glf", "hopkins"), (16384, 4, "glf", "ivanova"), (16385, 4, "hll", "hopkins"),
+    (19648, 5, "glf", "hopkins"), (19649, 5, "glf", "hopkins"),
+])
+@pytest.mark.parametrize("ticks", [False, True])
+def test_fp32c_groups_keep_their_bits(n, groups, solver, surfaces, ticks):
+    """FP32C: a group's sums are formed in one order wherever it runs, pair-once
+    up to 3 groups and two-sided above: in a block of its own up to 1024 blocks
+    (1536 of more than 4 groups), else with others in one wave.  So it is, bit
+    for bit, what it is in a context of one group (up to 3 groups), or of 3
+    groups more (above), which crosses those lines elsewhere."""
+    side = 5
+    while side ** 3 < n:
+        side += 1
+    x = dev(workloads.jittered_lattice(side, 0.2, 7)[:n])
+    g = torch.Generator(device="cuda").manual_seed(3)
+    U = torch.rand((n, groups, 4), generator=g, device="cuda", dtype=torch.float64)
+    U[..., 1:] = 0.5 * (U[..., 1:] - 0.5)
+    U = U.float()
+    out = []
+    for V in ((U, U[:, :1]) if groups <= 3 else (U, torch.cat([U, U[:, :3]], 1))):
+        G = V.shape[1]
+        rt = RT(n, G, precision="fp32c")
+        rt.rt_build_cells(x)
+        rt.rt_set_riemann(solver)
+        rt.rt_set_surfaces(surfaces)
+        V = V.contiguous().clone()
+        if ticks:
+            _, cycle = rt.rt_time_bins(3)
+            UD = rt.rt_gradient(V)
+            acc = torch.zeros(V.shape, dtype=torch.float64, device="cuda")
+            for t in range(cycle):
+                rt.rt_tick(V, None, t, UD, acc)
+        else:
+            V = rt.rt_transport(rt.rt_gradient(V))
+        out.append(V)
+    m = min(groups, out[1].shape[1])
+    assert torch.equal(out[0][:, :m], out[1][:, :m])

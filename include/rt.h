@@ -371,13 +371,14 @@ typedef struct {
     int64_t device_bytes_peak; /* the most it held at once since rt_create,
                                including the build's transient lists            */
     int64_t h_list_overflow;   /* particles of the last build whose smoothing-
-                               length candidate list overflowed (their later
-                               evaluations walked the tree again)               */
+                               length candidate list overflowed (its reach was
+                               cut, or the tree walked again)                   */
     int64_t union_blocks;      /* FP64, up to 4 groups: blocks of 64 particles
                                whose gradient reads its neighbours from their
                                union staged in LDS                              */
-    int64_t union_staged_blocks; /* those whose union did not fit (the gradient
-                               stages their rows per pair instead)              */
+    int64_t union_staged_blocks; /* those whose union did not fit (a few are
+                               staged as larger unions, the rows of the others
+                               per pair)                                        */
     int64_t adj_union_blocks;  /* FP64, up to 4 groups: blocks of 64 particles
                                whose adjoint transposed gradient reads the
                                union of their symmetric lists from LDS          */

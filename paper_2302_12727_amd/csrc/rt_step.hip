@@ -372,8 +372,9 @@ __global__ __launch_bounds__(grad_block(G)) __attribute__((amdgpu_waves_per_eu(
 // reads its neighbour's row from LDS by its 16-bit position in the union
 // (gloc): the pair loop's only global loads are the table's entries, 8 bytes
 // per 4 iterations.
-// Blocks whose union did not fit the LDS are left to k_gradient64 (a second
-// launch over their list).  Sums in the same order as k_gradient64 (lane sub
+// W = 1: larger unions, one block to a CU, of the blocks listed in blist (in
+// its order: urows, urow), if they are few (large_blocks).  Blocks whose union
+// fits neither are left to k_gradient64, by list.  Sums in the same order as k_gradient64 (lane sub
 // takes the slots sub, sub + Q, ...; rows past a list are the own row, whose
 // differences are zero), so the two give the same bits.
 // BIN: only the particles that end a step in tick `tick` recompute their

@@ -123,8 +123,9 @@ __global__ __launch_bounds__(kBlock) void k_gradient32(
 // same order and with the same operations as one lane per particle
 // (k_gradient32 with Q = 1), so the two give identical bits (see
 // RT_GRADIENT32_Q for why that order is kept).  Padding past a list is the
-// own row, which adds an exact zero.  Blocks whose union did not fit are
-// left to k_gradient32 with one lane per particle.  BIN: only the particles
+// own row, which adds an exact zero.  LARGE: larger unions of the blocks listed
+// in blist, if they are few (as W = 1 of k_gradient64u).  Blocks whose union
+// fits neither are left to k_gradient32 with one lane per particle.  BIN: only the particles
 // that end a step in tick `tick` recompute their record; a block none of
 // whose particles does so stages nothing.
 template <int G, bool BIN = false, bool LARGE = false>
@@ -287,6 +288,7 @@ k_gradient32u(int64_t n, int64_t nb, const float *__restrict__ geo32, const doub
 // thousand particles with them (1e-9).  A slice of 2 or 3 groups fits 168
 // registers and 3 waves per SIMD, at the price of the pair geometry once per
 // slice: 557 us a step with the 4 groups in one wave, now 503, the same bits.
+// Where the blocks are few a slice is one group (one_group_blocks).
 template <int G, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void k_transport32(
     int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32, const double *__restrict__ geo,
@@ -639,6 +641,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
 // BIN: one tick of the individual-time-step scheme on the tiles, as in the
 // FP64 tile kernel (due pairs weighted by dt 2^min(b_k, b_l) in the
 // compensated sums, pending sums accm in FP64).
+// WHOLE: all G groups in a wave; else slices of G, in use one group a block
+// where the blocks are few (one_group_blocks).
 template <int G, bool WHOLE, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void
 k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32,

@@ -115,7 +115,7 @@ __global__ void k_merge_level(int64_t first, int64_t count, double *__restrict__
 constexpr int kNList = 128;
 constexpr int64_t kNListBytes = int64_t(16) << 30;
 // Bit of a particle's iteration count set when its candidate list overflowed
-// (it was gathered again at a smaller radius).
+// (its reach was cut).
 constexpr int32_t kIterOverflow = 1 << 24;
 
 struct Tree {
@@ -1411,7 +1411,7 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
     BuildResult res{};
     // (no work queued on a stream the context had before reads what this build
     // writes)
-    RT_HIP(hipDeviceSynchronize());
+    if (ctx->xs) RT_HIP(hipDeviceSynchronize());
 
 #define RESERVE(p, bytes)                                                  \
     do {                                                                   \

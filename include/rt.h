@@ -110,8 +110,8 @@ rt_status rt_build_cells(rt_ctx *ctx, const double *x, const double *h_in,
  * length"; the thesis fixes no tolerance or cap).  A particle whose
  * Newton-Raphson/bisection iteration has not met the 4-ulp step test after
  * max_iter evaluations makes the build return RT_ENOCONV.  Default 200
- * (a C-level model of the iteration needs at most 8 on the synthetic sets);
- * 1 .. 10000, else RT_EINVAL.  Applies to later builds. */
+ * (the synthetic sets need at most 9); 1 .. 10000, else RT_EINVAL.  Applies to
+ * later builds. */
 rt_status rt_set_h_iterations(rt_ctx *ctx, int32_t max_iter);
 
 /* Point sources (Part III "First step: injection", "Weights for distribution
@@ -365,7 +365,8 @@ typedef struct {
     int64_t n_gather;       /* directed entries with r_ij < H_i                 */
     int64_t sell_slots;     /* padded slots of the wave-sliced neighbour table  */
     int32_t max_neighbours;
-    int32_t h_iter_max;     /* most Newton/bisection iterations of one particle */
+    int32_t h_iter_max;     /* most Newton/bisection iterations of one particle
+                               (one evaluation more meets the step test)        */
     int64_t n_inject;       /* source-gas injection entries                     */
     int64_t device_bytes;   /* device memory the context holds now              */
     int64_t device_bytes_peak; /* the most it held at once since rt_create,

@@ -427,6 +427,9 @@ __device__ __forceinline__ double sum8(double v) {
 // set; gathering again nearer in, which 45% of 22 thousand clustered particles
 // did, took 652 us, this 248 us).  One whose root lies beyond h_R gathers
 // again further out; one whose two radii meet falls back to the serial walk.
+// `iters` counts as in h_solve_point, the evaluations before the last one; an
+// evaluation at h_R that finds the root beyond it only places the next list and
+// counts neither there nor against max_iter.
 constexpr int kHList = 128;
 template <class Cand>
 __device__ double h_solve_wave(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
@@ -495,8 +498,10 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
             busy = false;
             h = fmin(h, hR);
         } else if (busy) {
+            bool probe = false;                // h is h_R, in place of an iterate beyond it
             if (R < kappa * hR) {
                 hR = R / kappa;
+                probe = h > hR;
                 h = fmin(h, hR);
             }
             // Newton-Raphson on the list, while it reaches
@@ -506,7 +511,6 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                     busy = false;
                     break;
                 }
-                ++it;
                 const double iH = 1.0 / (kappa * h);
                 double sw = 0.0, sdw = 0.0;
                 for (int k = c; k < cnt; k += 8) {
@@ -538,7 +542,9 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                     if (hn > hR) {
                         if (h < hR) {
                             hn = hR;             // the list's end first
+                            probe = true;
                         } else {                 // the root lies beyond: gather again
+                            it += !probe;
                             small = hR;
                             hR = fmin(fmax(1.15 * hn, 1.25 * hR), hcap);
                             h = hn;
@@ -561,6 +567,7 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                     }
                 }
                 h = hn;
+                ++it;
             }
         }
         wave_lds_sync();

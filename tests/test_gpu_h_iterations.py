@@ -1,0 +1,93 @@
+"""The iteration count and cap of the smoothing-length solve against a model of
+the iteration in numpy (start from the leaf box and the Morton window, Newton
+steps inside a bracket, doubling until there is one, stop at a step of 4 ulp).
+
+A particle that takes k iterations needs k + 1 evaluations, the last of which
+meets the step test: that cap builds and one less is refused.  Evaluations that
+the library spends on its candidate lists are not iterations, so it never needs
+a larger cap than the model; it may need a smaller one, where a list's end takes
+the place of an iterate further from the root.
+"""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from tests.gpu_util import dev, log
+from tests.test_gpu_search import clump_set
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2302_12727_amd import RT  # noqa: E402
+from paper_2302_12727_amd.rt import KAPPA, RTError  # noqa: E402
+
+
+def model_iterations(xs, eta, kappa=KAPPA):
+    """Iterations of every particle; xs in Morton order, unit box."""
+    n = xs.shape[0]
+    d = xs[None] - xs[:, None]
+    d -= np.rint(d)
+    r = np.sqrt((d * d).sum(axis=2))
+    leaf = np.arange(n) // 32
+    ext = np.ones(n)
+    for a in range(3):
+        lo, hi = (f.reduceat(xs[:, a], np.arange(0, n, 32)) for f in (np.minimum, np.maximum))
+        ext *= np.maximum(hi - lo, 1 / 2097152)[leaf]
+    h = eta * np.cbrt(ext / np.bincount(leaf)[leaf])
+    i = np.arange(n)
+    near = np.where((np.abs(i[None] - i[:, None]) <= 16) & (i[None] != i[:, None]), r, np.inf)
+    fourth = np.sort(near, axis=1)[:, 3]
+    h = np.minimum(np.minimum(h, 0.8 * eta * fourth * 0.94269861348), min(0.25, 0.25 / kappa))
+    pref, eta3, eps4 = 16 / np.pi / kappa ** 3, eta ** 3, 4 * 2.0 ** -52
+    lo, hi, hcap = np.zeros(n), np.full(n, np.inf), 0.5 / kappa
+    its, live = np.zeros(n, dtype=int), np.ones(n, dtype=bool)
+    while live.any():
+        q = r[live] / (kappa * h[live])[:, None]
+        a, b = np.maximum(1 - q, 0), np.maximum(0.5 - q, 0)
+        sw = (a ** 3 - 4 * b ** 3).sum(axis=1)
+        sdw = ((-3 * a * a + 12 * b * b) * q).sum(axis=1)
+        hl, lol, hil = h[live], lo[live], hi[live]
+        g, dg = pref * sw - eta3, -pref * sdw / hl
+        lol, hil = np.where(g < 0, hl, lol), np.where(g < 0, hil, hl)
+        step = np.where(dg > 0, hl - g / np.where(dg > 0, dg, 1), -1.0)
+        out = np.where((dg > 0) & (step > hl) & (step < 4 * hl), step, 2 * hl)
+        mid = np.where((step > lol) & (step < hil), step, 0.5 * (lol + np.where(np.isinf(hil), 0, hil)))
+        open_end = np.isinf(hil)
+        new = np.where(open_end, np.minimum(out, hcap), mid)
+        done = (g == 0) | (~open_end & ((np.abs(new - hl) <= eps4 * hl)
+                                        | ((dg > 0) & (np.abs(step - hl) <= eps4 * hl))
+                                        | (hil - lol <= eps4 * hil)))
+        assert not (open_end & (hl >= hcap)).any()
+        at = np.flatnonzero(live)
+        h[at], lo[at], hi[at] = new, lol, hil
+        its[at[~done]] += 1
+        live[at[done]] = False
+        assert its.max() < 200
+    return its
+
+
+def check(x, eta):
+    rt = RT(x.shape[0], 1, eta=eta)
+    perm, h, _, _ = rt.rt_build_cells(dev(x))
+    model = int(model_iterations(x[perm.cpu().numpy()], eta).max())
+    took = rt.rt_get_stats()["h_iter_max"]
+    h = h.clone()
+    log(f"n={x.shape[0]} eta={eta}: {took} iterations, model {model}")
+    assert 1 <= took <= model
+    rt.rt_set_h_iterations(took)
+    with pytest.raises(RTError, match="RT_ENOCONV"):
+        rt.rt_build_cells(dev(x))
+    rt.rt_set_h_iterations(took + 1)
+    assert torch.equal(rt.rt_build_cells(dev(x))[1], h)
+
+
+@pytest.mark.parametrize("x", [
+    workloads.jittered_lattice(13, 0.1, 2),
+    workloads.config(4, scale=(1 << 11) / (1 << 24)).x,
+    clump_set(10, 100, 4),                      # lists cut and drawn out again
+], ids=["lattice", "plummer", "small clump"])
+def test_iterations_and_cap(x):
+    check(x, 1.2348)

@@ -373,7 +373,7 @@ typedef struct {
                                including the build's transient lists            */
     int64_t h_list_overflow;   /* particles of the last build whose smoothing-
                                length candidate list overflowed (its reach was
-                               cut, or the tree walked again)                   */
+                               cut)                                             */
     int64_t union_blocks;      /* FP64, up to 4 groups: blocks of 64 particles
                                whose gradient reads its neighbours from their
                                union staged in LDS                              */

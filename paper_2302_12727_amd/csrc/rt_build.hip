@@ -124,87 +124,6 @@ struct Tree {
 };
 
 // ---------------------------------------------------------------------------
-// Smoothing length: root of g(h) = h^3 sum_j W(r_j, kappa h) - eta^3
-// (eq:number-of-neighbors), i.e. (sigma/kappa^3) sum_j w(r_j / (kappa h)) = eta^3,
-// by Newton-Raphson safeguarded with bisection.  h_solve_point walks the tree
-// with one thread for every evaluation: the fallback of h_solve_wave.
-__device__ double h_solve_point(const Tree &T, const double *__restrict__ xs, int64_t n,
-                                double px, double py, double pz, double h0, double eta,
-                                double kappa, double box, double hcap, int32_t max_iter,
-                                int32_t &iters, int32_t &flags) {
-    const double pref = kSigma3 / (kappa * kappa * kappa);
-    const double eta3 = eta * eta * eta;
-    const double eps4 = 4.0 * 2.220446049250313e-16;
-    const double ibox = 1.0 / box;
-    // iterates stay at or below hcap (compact support at most half the box);
-    // a root beyond it is an error
-    double lo = 0.0, hi = INFINITY, h = fmin(h0, hcap);
-    int32_t it = 0;
-    bool ok = false, big = false;
-    for (it = 0; it < max_iter; ++it) {
-        const double H = kappa * h, H2 = H * H, iH = 1.0 / H, acc2 = H2 * (1.0 + 1e-12);
-        double sw = 0.0, sdw = 0.0;
-        traverse(
-            T.P,
-            [&](int64_t v) { return box_dist2(T.lo + 3 * v, T.hi + 3 * v, px, py, pz, box) < acc2; },
-            [&](int64_t l) {
-                const int64_t j0 = l * kLeaf, j1 = min(n, j0 + kLeaf);
-                for (int64_t j = j0; j < j1; ++j) {
-                    const double sx = min_image(xs[3 * j] - px, box, ibox);
-                    const double sy = min_image(xs[3 * j + 1] - py, box, ibox);
-                    const double sz = min_image(xs[3 * j + 2] - pz, box, ibox);
-                    const double r2 = sx * sx + sy * sy + sz * sz;
-                    if (r2 < H2) {
-                        const double q = sqrt(r2) * iH;
-                        sw += kern_w(q);
-                        sdw += kern_dw(q) * q;
-                    }
-                }
-            });
-        const double g = pref * sw - eta3;
-        const double dg = -pref * sdw / h;
-        if (g == 0.0) {
-            ok = true;
-            break;
-        }
-        if (g < 0.0) lo = h; else hi = h;
-        double hn;
-        if (hi == INFINITY) {
-            if (h >= hcap) {                     // g < 0 at the cap
-                big = true;
-                break;
-            }
-            hn = 2.0 * h;                        // expand until bracketed
-            if (dg > 0.0) {
-                const double nt = h - g / dg;
-                if (nt > h && nt < 4.0 * h) hn = nt;
-            }
-            hn = fmin(hn, hcap);
-        } else {
-            // the step test comes before the bracket test: a Newton step that
-            // rounds to h itself lands on a bracket end and would otherwise be
-            // replaced by a bisection from a far end
-            hn = (dg > 0.0) ? h - g / dg : -1.0;
-            if (dg > 0.0 && fabs(hn - h) <= eps4 * h) {
-                h = hn;
-                ok = true;
-                break;
-            }
-            if (!(hn > lo && hn < hi)) hn = 0.5 * (lo + hi);
-            if (fabs(hn - h) <= eps4 * h || hi - lo <= eps4 * hi) {
-                h = hn;
-                ok = true;
-                break;
-            }
-        }
-        h = hn;
-    }
-    iters = it;
-    if (big) flags |= ST_BIGH;
-    else if (!ok) flags |= ST_NOCONV;
-    return h;
-}
-
 // Starting point of the solve: the smaller of two density estimates (a walk
 // costs about its radius cubed, so starting low is cheap and starting high is
 // not):
@@ -420,16 +339,26 @@ __device__ __forceinline__ double sum8(double v) {
     return v + __shfl_xor(v, 4, 64);
 }
 
-// Smoothing lengths of the wave's points: the iteration of h_solve_point, its
-// sums over r_j < kappa h_R collected once per point in LDS (kHList entries)
-// and spread over the point's 8 lanes.  A point with more than kHList particles
-// in reach cuts h_R while it collects and keeps the entries inside (overflow
-// set; gathering again nearer in, which 45% of 22 thousand clustered particles
-// did, took 652 us, this 248 us).  One whose root lies beyond h_R gathers
-// again further out; one whose two radii meet falls back to the serial walk.
-// `iters` counts as in h_solve_point, the evaluations before the last one; an
-// evaluation at h_R that finds the root beyond it only places the next list and
-// counts neither there nor against max_iter.
+// Smoothing length of each of the wave's points: root of
+//   g(h) = h^3 sum_j W(r_j, kappa h) - eta^3   (eq:number-of-neighbors),
+// i.e. (sigma/kappa^3) sum_j w(r_j / (kappa h)) = eta^3, by Newton-Raphson
+// safeguarded with bisection.  The r_j < kappa h_R are collected once per point
+// in LDS (kHList entries) and each sum is spread over the point's 8 lanes.  A
+// point with more than kHList particles in reach cuts h_R while it collects and
+// keeps the entries inside (overflow set; gathering again nearer in, which 45%
+// of 22 thousand clustered particles did, took 652 us, this 248 us).  One whose
+// root lies beyond an h_R that was not cut gathers again further out.  One whose
+// root lies beyond a cut h_R does so too, cut no nearer than what is known to be
+// too near, twice where a list can be expected to hold the root's particles
+// (N = 4 pi (kappa eta)^3 / 3), at once where not; then it is dense: summed
+// straight from the candidates of a gather per evaluation, none kept.  (Drawn
+// out and cut again until a serial walk took over, 64^3 particles at eta 1.8, all
+// of that kind, built in 54.7 ms, this way in 6.9; at eta 2.2 72.6 and 9.2, at
+// eta 1.65, N = 114, 4.7 and 3.6.  Dense at the first short list at the default
+// eta, N = 48: 22 thousand clustered particles 1.34 ms a rebuild against 1.27.)
+// `iters` counts the evaluations before the last one; an evaluation at h_R that
+// finds the root beyond it only places the next reach and counts neither there
+// nor against max_iter.
 constexpr int kHList = 128;
 template <class Cand>
 __device__ double h_solve_wave(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
@@ -440,30 +369,63 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
     const int lane = threadIdx.x & 63, p = lane >> 3, c = lane & 7;
     const double pref = kSigma3 / (kappa * kappa * kappa), eta3 = eta * eta * eta;
     const double eps4 = 4.0 * 2.220446049250313e-16, ibox = 1.0 / box;
+    // iterates stay at or below hcap (compact support at most half the box); a
+    // root beyond it is an error
     const double hcap = 0.5 * box / kappa;
     double lo = 0.0, hi = INFINITY, h = fmin(h0, hcap);
-    double small = 0.0;                        // largest h_R known to be below the root
     double hR = fmin(1.5 * h, hcap);           // the list's reach over kappa
     int32_t it = 0;
-    bool busy = on, serial = false;
+    // short lists that were cut before a point is taken for a dense one
+    int spare = 4.0 / 3.0 * kPi * kappa * kappa * kappa * eta3 < 0.75 * kHList ? 2 : 0;
+    bool busy = on, dense = false;
+    // One step from the sums at h: true if it ends the solve, else the next
+    // iterate is in hn.
+    auto step = [&](double sw, double sdw, double &hn) {
+        const double g = pref * sw - eta3, dg = -pref * sdw / h;
+        if (g == 0.0) return true;
+        if (g < 0.0) lo = h; else hi = h;
+        if (hi == INFINITY) {
+            if (h >= hcap) {                     // g < 0 at the cap
+                flags |= ST_BIGH;
+                return true;
+            }
+            hn = 2.0 * h;                        // expand until bracketed
+            if (dg > 0.0) {
+                const double nt = h - g / dg;
+                if (nt > h && nt < 4.0 * h) hn = nt;
+            }
+            hn = fmin(hn, hcap);
+            return false;
+        }
+        // the step test comes before the bracket test: a Newton step that rounds
+        // to h itself lands on a bracket end and would otherwise be replaced by a
+        // bisection from a far end
+        hn = dg > 0.0 ? h - g / dg : -1.0;
+        if (dg > 0.0 && fabs(hn - h) <= eps4 * h) {
+            h = hn;
+            return true;
+        }
+        if (!(hn > lo && hn < hi)) hn = 0.5 * (lo + hi);
+        if (fabs(hn - h) <= eps4 * h || hi - lo <= eps4 * hi) {
+            h = hn;
+            return true;
+        }
+        return false;
+    };
 #pragma unroll 1
-    for (int round = 0; round < 64 && __ballot(busy) != 0; ++round) {
+    while (__ballot(busy) != 0) {
         double R = busy ? kappa * hR : -1.0, R2 = R * R;
         int cnt = 0, left = 32;                // entries; cuts of R left
-        bool full = false;                     // cannot be cut to fit
         wave_gather<false>(T, depth, xs, nullptr, n, box, px, py, pz, R, B, [&](int m) {
             for (int s = 0; s < m; s += 8) {
                 // no room for 8 more: the points concerned cut R (to 2/3 of the
-                // volume) and keep the entries inside
+                // volume, not below lo) and keep the entries inside; one that
+                // cannot be cut to fit keeps none
                 while (__ballot(cnt > kHList - 8) != 0) {
                     const bool cut = cnt > kHList - 8;
                     if (cut) {
                         overflow = true;
-                        R = fmax(0.875 * R, 0.5 * (R + kappa * small));
-                        if (--left < 0) {
-                            full = true;
-                            R = 0.0;
-                        }
+                        R = --left < 0 ? 0.0 : fmax(0.875 * R, 0.5 * (R + kappa * lo));
                         R2 = R * R;
                     }
                     int keep = 0;
@@ -493,91 +455,87 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
             }
         });
         wave_lds_sync();
-        if (busy && full) {
-            serial = true;
-            busy = false;
-            h = fmin(h, hR);
-        } else if (busy) {
-            bool probe = false;                // h is h_R, in place of an iterate beyond it
-            if (R < kappa * hR) {
-                hR = R / kappa;
+        const bool was_cut = R < kappa * hR;
+        bool probe = false;                    // h is h_R, in place of an iterate beyond it
+        if (busy && was_cut) {
+            hR = R / kappa;
+            dense = !(hR > 0.0);               // no list fits
+            busy = !dense;
+            if (busy) {
                 probe = h > hR;
                 h = fmin(h, hR);
             }
-            // Newton-Raphson on the list, while it reaches
-            while (busy) {
-                if (it >= max_iter) {
-                    flags |= ST_NOCONV;
-                    busy = false;
-                    break;
+        }
+        // Newton-Raphson on the list, while it reaches
+        bool more = busy;
+        while (more) {
+            if (it >= max_iter) {
+                flags |= ST_NOCONV;
+                busy = false;
+                break;
+            }
+            const double iH = 1.0 / (kappa * h);
+            double sw = 0.0, sdw = 0.0;
+            for (int k = c; k < cnt; k += 8) {
+                const double q = list[p][k] * iH;
+                sw += kern_w(q);
+                sdw += kern_dw(q) * q;
+            }
+            double hn;
+            if (step(sum8(sw), sum8(sdw), hn)) {
+                busy = false;
+                break;
+            }
+            if (hi == INFINITY && hn > hR) {
+                if (h < hR) {
+                    hn = hR;                     // the list's end first
+                    probe = true;
+                } else {                         // the root lies beyond
+                    it -= probe;
+                    hR = fmin(fmax(1.15 * hn, 1.25 * hR), hcap);
+                    dense = was_cut && --spare < 0;
+                    busy = !dense;
+                    more = false;
                 }
-                const double iH = 1.0 / (kappa * h);
-                double sw = 0.0, sdw = 0.0;
-                for (int k = c; k < cnt; k += 8) {
-                    const double q = list[p][k] * iH;
-                    sw += kern_w(q);
-                    sdw += kern_dw(q) * q;
+            }
+            h = hn;
+            ++it;
+        }
+        wave_lds_sync();
+    }
+    // the dense points: a gather per evaluation
+#pragma unroll 1
+    while (__ballot(dense) != 0) {
+        if (dense && it >= max_iter) {
+            flags |= ST_NOCONV;
+            dense = false;
+        }
+        const double R = dense ? kappa * h : -1.0, R2 = R * R, iH = 1.0 / (kappa * h);
+        double sw = 0.0, sdw = 0.0;
+        wave_gather<false>(T, depth, xs, nullptr, n, box, px, py, pz, R, B, [&](int m) {
+            for (int q = c; q < m; q += 8) {
+                const double sx = min_image(B.x[q] - px, box, ibox);
+                const double sy = min_image(B.y[q] - py, box, ibox);
+                const double sz = min_image(B.z[q] - pz, box, ibox);
+                const double r2 = sx * sx + sy * sy + sz * sz;
+                if (dense && r2 < R2) {
+                    const double u = sqrt(r2) * iH;
+                    sw += kern_w(u);
+                    sdw += kern_dw(u) * u;
                 }
-                sw = sum8(sw);
-                sdw = sum8(sdw);
-                const double g = pref * sw - eta3, dg = -pref * sdw / h;
-                if (g == 0.0) {
-                    busy = false;
-                    break;
-                }
-                if (g < 0.0) lo = h; else hi = h;
-                double hn;
-                if (hi == INFINITY) {
-                    if (h >= hcap) {             // g < 0 at the cap
-                        flags |= ST_BIGH;
-                        busy = false;
-                        break;
-                    }
-                    hn = 2.0 * h;                // expand until bracketed
-                    if (dg > 0.0) {
-                        const double nt = h - g / dg;
-                        if (nt > h && nt < 4.0 * h) hn = nt;
-                    }
-                    hn = fmin(hn, hcap);
-                    if (hn > hR) {
-                        if (h < hR) {
-                            hn = hR;             // the list's end first
-                            probe = true;
-                        } else {                 // the root lies beyond: gather again
-                            it += !probe;
-                            small = hR;
-                            hR = fmin(fmax(1.15 * hn, 1.25 * hR), hcap);
-                            h = hn;
-                            break;
-                        }
-                    }
-                } else {
-                    // the step test comes before the bracket test (see h_solve_point)
-                    hn = dg > 0.0 ? h - g / dg : -1.0;
-                    if (dg > 0.0 && fabs(hn - h) <= eps4 * h) {
-                        h = hn;
-                        busy = false;
-                        break;
-                    }
-                    if (!(hn > lo && hn < hi)) hn = 0.5 * (lo + hi);
-                    if (fabs(hn - h) <= eps4 * h || hi - lo <= eps4 * hi) {
-                        h = hn;
-                        busy = false;
-                        break;
-                    }
-                }
+            }
+        });
+        double hn;
+        sw = sum8(sw);
+        sdw = sum8(sdw);
+        if (dense) {
+            if (step(sw, sdw, hn)) {
+                dense = false;
+            } else {
                 h = hn;
                 ++it;
             }
         }
-        wave_lds_sync();
-    }
-    if (busy) serial = true;
-    if (serial) {
-        // (all 8 lanes of the point walk: the same reads, the same result)
-        int32_t fl = 0;
-        h = h_solve_point(T, xs, n, px, py, pz, h, eta, kappa, box, hcap, max_iter, it, fl);
-        flags |= fl;
     }
     iters = it;
     return h;

@@ -12,8 +12,9 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads
-from tests.gpu_util import dev, log
+from tests.gpu_util import dev, log, unsort
 from tests.test_gpu_search import clump_set
 
 pytestmark = pytest.mark.gpu
@@ -70,6 +71,7 @@ def model_iterations(xs, eta, kappa=KAPPA):
 
 
 def check(x, eta):
+    """The context built with the smallest cap, and its Morton order."""
     rt = RT(x.shape[0], 1, eta=eta)
     perm, h, _, _ = rt.rt_build_cells(dev(x))
     model = int(model_iterations(x[perm.cpu().numpy()], eta).max())
@@ -82,6 +84,7 @@ def check(x, eta):
         rt.rt_build_cells(dev(x))
     rt.rt_set_h_iterations(took + 1)
     assert torch.equal(rt.rt_build_cells(dev(x))[1], h)
+    return rt, perm.cpu().numpy()
 
 
 @pytest.mark.parametrize("x", [
@@ -91,3 +94,26 @@ def check(x, eta):
 ], ids=["lattice", "plummer", "small clump"])
 def test_iterations_and_cap(x):
     check(x, 1.2348)
+
+
+@pytest.mark.parametrize("eta", [1.65, 1.8, 2.2])
+@pytest.mark.parametrize("x", [
+    workloads.jittered_lattice(13, 0.1, 2),
+    clump_set(10, 400, 3),
+], ids=["lattice", "clump"])
+def test_more_neighbours_than_a_list_holds(x, eta):
+    """110 to 260 particles in reach at the root, more than a candidate list's
+    120: the iteration as long as the model's all the same, for particles and
+    for sources, and h the oracle's (to 1e-13: the solve stops at 4 ulp, its
+    sums of up to 700 terms round to about 1e-14 at most)."""
+    rt, p = check(x, eta)
+    geo = oracle.build_geometry(x, eta=eta)
+    err = float(np.abs(unsort(rt.h.cpu().numpy(), p) / geo.h - 1).max())
+    xs = np.ascontiguousarray(x[[0, x.shape[0] // 2, x.shape[0] - 1]] * 0.999 + 0.0005)
+    rt.rt_set_h_iterations(10)
+    rt.rt_set_sources(dev(xs), eta)
+    serr = float(np.abs(rt.rt_get_sources()[3].cpu().numpy()
+                        / oracle.build_sources(geo, xs, eta).h - 1).max())
+    log(f"h error {err:.1e}, of sources {serr:.1e}, most gather neighbours {np.diff(geo.gptr).max()}")
+    assert np.diff(geo.gptr).max() > 120
+    assert err < 1e-13 and serr < 1e-13

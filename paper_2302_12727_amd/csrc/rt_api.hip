@@ -378,11 +378,12 @@ rt_status rt_get_stats(rt_ctx *ctx, rt_stats *out) {
     out->device_bytes = ctx->device_bytes;
     out->device_bytes_peak = ctx->device_peak;
     out->h_list_overflow = ctx->h_list_overflow;
-    out->union_blocks = ctx->urows ? ctx->nwaves - ctx->n_ublk : 0;
-    out->union_staged_blocks = ctx->urows ? ctx->n_ublk : 0;
-    out->adj_union_blocks = ctx->arows ? ctx->nwaves - ctx->n_ablk : 0;
-    out->adj_union_staged_blocks = ctx->arows ? ctx->n_ablk : 0;
-    if (ctx->built && ctx->tstat) {
+    if (ctx->built) {
+        // (the arrays outlive a failed build, what is in them does not count)
+        out->union_blocks = ctx->urows ? ctx->nwaves - ctx->n_ublk : 0;
+        out->union_staged_blocks = ctx->urows ? ctx->n_ublk : 0;
+        out->adj_union_blocks = ctx->arows ? ctx->nwaves - ctx->n_ablk : 0;
+        out->adj_union_staged_blocks = ctx->arows ? ctx->n_ablk : 0;
         int64_t t[2];
         RT_HIP(hipStreamSynchronize(ctx->stream));
         RT_HIP(hipMemcpy(t, ctx->tstat, sizeof t, hipMemcpyDeviceToHost));

@@ -410,7 +410,16 @@ rt_status rt_get_sources(rt_ctx *ctx, int32_t *gas, int32_t *src, double *xi, do
  * launch of the named kernel ("transport", "gradient", "inject", "adjoint").
  * rt_timing(ctx, 1) starts recording and clears totals; rt_timing(ctx, 0)
  * stops.  rt_get_timing returns the summed milliseconds and launch count
- * (synchronising). */
+ * (synchronising).  A name may go on with "/" and a route the launch took, one
+ * of several kernels by the set's size and its groups: of "transport" and "tick"
+ *   /whole       up to 3 groups in one wave
+ *   /one_group   a block for every group of several
+ *   /slices      more than 3 groups, in slices of 3 and 2
+ *   /wide        8 lanes a particle (FP64)
+ *   /three_waves one FP64 group at three waves per SIMD
+ * and of "gradient" and "tick", with neighbour unions in use,
+ *   /large       some blocks from larger unions
+ *   /staged      some blocks per pair. */
 rt_status rt_timing(rt_ctx *ctx, int32_t on);
 rt_status rt_get_timing(rt_ctx *ctx, const char *kernel, double *ms_total, int64_t *launches);
 

@@ -83,8 +83,13 @@ void rt_timer_end(rt_ctx *ctx, const char *name) {
     }
     hipEvent_t b = ctx->ev_pool[ctx->ev_used++];
     (void)hipEventRecord(b, ctx->stream);
-    ctx->trecs.push_back({name, ctx->ev_open.back(), b});
+    ctx->trecs.push_back({name, ctx->routes + "/", ctx->ev_open.back(), b});
+    ctx->routes.clear();
     ctx->ev_open.pop_back();
+}
+
+void rt_route(rt_ctx *ctx, const char *route) {
+    if (ctx->timing) ctx->routes.append("/").append(route);
 }
 
 static bool finite_pos(double v) { return v > 0.0 && v < 1e300; }
@@ -460,6 +465,7 @@ rt_status rt_timing(rt_ctx *ctx, int32_t on) {
     if (on) {
         RT_HIP(hipStreamSynchronize(ctx->stream));
         ctx->trecs.clear();
+        ctx->routes.clear();
         ctx->ev_open.clear();
         ctx->ev_used = 0;
     }
@@ -472,8 +478,12 @@ rt_status rt_get_timing(rt_ctx *ctx, const char *kernel, double *ms_total, int64
     RT_HIP(hipStreamSynchronize(ctx->stream));
     double ms = 0.0;
     int64_t cnt = 0;
+    const std::string full = kernel;
+    const size_t cut = full.find('/');
+    const std::string name = full.substr(0, cut);
+    const std::string route = cut == std::string::npos ? "" : full.substr(cut) + "/";
     for (auto &r : ctx->trecs) {
-        if (r.name != kernel) continue;
+        if (r.name != name || r.routes.find(route) == std::string::npos) continue;
         float t = 0.0f;
         RT_HIP(hipEventElapsedTime(&t, r.a, r.b));
         ms += t;

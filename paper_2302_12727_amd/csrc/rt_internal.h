@@ -92,7 +92,7 @@ constexpr int64_t one_group_blocks(bool f64, int G) {
 }
 
 struct TimerRec {
-    std::string name;
+    std::string name, routes;    // routes: "/whole/wide" (rt_route)
     hipEvent_t a, b;
 };
 
@@ -215,6 +215,7 @@ struct rt_ctx {
     std::vector<hipEvent_t> ev_pool;
     size_t ev_used = 0;
     std::vector<gearrt::TimerRec> trecs;
+    std::string routes;          // of the timed launch under way
     std::vector<hipEvent_t> ev_open;   // stack of open timers (nested launches)
 };
 
@@ -411,6 +412,8 @@ bool rt_holds(const rt_ctx *ctx, void *ptr, size_t bytes);
 void rt_free(rt_ctx *ctx, void *ptr);
 void rt_timer_begin(rt_ctx *ctx, const char *name);
 void rt_timer_end(rt_ctx *ctx, const char *name);
+// while timing is on: the launch under way takes the named route
+void rt_route(rt_ctx *ctx, const char *route);
 
 // build (rt_build.hip)
 rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_t *perm,

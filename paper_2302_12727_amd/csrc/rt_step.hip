@@ -1058,6 +1058,8 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
     const unsigned grid = (unsigned)xcd_grid(blocks);
     // lanes per particle and waves per SIMD: see k_transport64_tile
     const bool wide = blocks <= kWideTiles, three = blocks > kThreeTiles;
+    if (wide && off32) rt_route(ctx, "wide");
+    if (three && G == 1 && off32 && !hll) rt_route(ctx, "three_waves");
 #define RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, Q_, W_)                                      \
     k_transport64_tile<G, WHOLE, OFF32_, HLL_, IVA_, BIN_, Q_, W_>                               \
         <<<grid, 64 * Q_, 0, ctx->stream>>>(                                                     \
@@ -1108,7 +1110,9 @@ void launch_transport64(rt_ctx *ctx, const double *UD, const double *dt, double 
                         double *accm) {
     const int G = ctx->p.groups, s3 = slices_of_3(G), s2 = slices_of_2(G);
     const Slices sl{G, 0, s3};
-    if (G > 1 && transport64_rows(ctx->p.n) * G <= one_group_blocks(true, G)) {
+    const bool few = G > 1 && transport64_rows(ctx->p.n) * G <= one_group_blocks(true, G);
+    rt_route(ctx, few ? "one_group" : G <= 3 ? "whole" : "slices");
+    if (few) {
         launch_tiles64<1, false>(ctx, Slices{G, 0, G}, UD, dt, Uout, partials, counts, Uung, tick,
                                  accm);
     } else if (G == 1) {
@@ -1158,6 +1162,7 @@ void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
             }
 #undef RT_UNION_LAUNCH
             if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0) rt_route(ctx, "large");
                 if (ctx->n_lblk > 0)
                     k_gradient64u<G, kGQ, 1><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
                                                ctx->stream>>>(
@@ -1165,6 +1170,7 @@ void launch_gradient64(rt_ctx *ctx, const double *U, double *UD) {
                         ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, 0,
                         ctx->ublk + 2);
             }
+            if (ctx->n_sblk > 0) rt_route(ctx, "staged");
             if (ctx->n_sblk > 0)
                 k_gradient64<G, false, kGQ><<<(unsigned)xcd_grid(ctx->n_sblk), B, 0, ctx->stream>>>(
                     ctx->p.n, ctx->n_sblk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,
@@ -1202,6 +1208,7 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
             }
 #undef RT_TICK_UNION_LAUNCH
             if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0) rt_route(ctx, "large");
                 if (ctx->n_lblk > 0)
                     k_gradient64u<G, kGQ, 1, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
                                                      ctx->stream>>>(
@@ -1209,6 +1216,7 @@ void launch_tick64(rt_ctx *ctx, const double *U, double *UD, const double *dt, d
                         ctx->goff, ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick,
                         ctx->ublk + 2);
             }
+            if (ctx->n_sblk > 0) rt_route(ctx, "staged");
             if (ctx->n_sblk > 0)
                 k_gradient64<G, true, kGQ><<<(unsigned)xcd_grid(ctx->n_sblk), B, 0, ctx->stream>>>(
                     n, ctx->n_sblk, ctx->geo, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath,

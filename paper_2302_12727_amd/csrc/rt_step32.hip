@@ -1020,6 +1020,7 @@ void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
                 ctx->p.n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box);
             if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0) rt_route(ctx, "large");
                 if (ctx->n_lblk > 0)
                     k_gradient32u<G, false, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
                                                     ctx->stream>>>(
@@ -1028,6 +1029,7 @@ void launch_gradient32(rt_ctx *ctx, const float *U, float *UD) {
                         ctx->ublk + 2);
             }
             if (ctx->n_sblk > 0) {
+                rt_route(ctx, "staged");
                 const int64_t nl = (ctx->n_sblk + 3) / 4;
                 k_gradient32<G, 1><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     ctx->p.n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U,
@@ -1095,6 +1097,7 @@ void launch_transport32(rt_ctx *ctx, const float *UD, const double *dt, float *U
     const Slices sl{G, 0, s3}, one{G, 0, G};
     // a block for every group where the tiles are few (see one_group_blocks)
     const bool few = G > 1 && rt_transport32_rows(ctx->p.n) * G <= one_group_blocks(false, G);
+    rt_route(ctx, few ? "one_group" : G <= 3 ? "whole" : "slices");
     if (few && G <= 3) {
         launch_groups32<1, true, true>(ctx, one, UD, dt, Uout, partials, counts, Uung, tick, accm);
     } else if (few) {
@@ -1130,6 +1133,7 @@ void launch_tick32(rt_ctx *ctx, float *U, float *UD, const double *dt, double *p
                 n, nw, ctx->geo32, ctx->xs, ctx->urow, ctx->urows, ctx->gloc, ctx->goff,
                 ctx->uown, ctx->n_gath, U, UD, ctx->status, ctx->p.box, tick);
             if constexpr (union_cap_large(G) > 0) {
+                if (ctx->n_lblk > 0) rt_route(ctx, "large");
                 if (ctx->n_lblk > 0)
                     k_gradient32u<G, true, true><<<(unsigned)xcd_grid(ctx->n_lblk), kBlock, 0,
                                                    ctx->stream>>>(
@@ -1138,6 +1142,7 @@ void launch_tick32(rt_ctx *ctx, float *U, float *UD, const double *dt, double *p
                         ctx->ublk + 2);
             }
             if (ctx->n_sblk > 0) {
+                rt_route(ctx, "staged");
                 const int64_t nl = (ctx->n_sblk + 3) / 4;
                 k_gradient32<G, 1, true><<<(unsigned)xcd_grid(nl), kBlock, 0, ctx->stream>>>(
                     n, nl, ctx->geo32, ctx->xs, ctx->nbr, ctx->wave_base, ctx->n_gath, U, UD,

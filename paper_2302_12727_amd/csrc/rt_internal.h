@@ -38,7 +38,9 @@ constexpr int union_cap32(int G) { return G == 1 ? 1024 : G == 2 ? 880 : G == 3 
 // are few: staging them per pair takes about as long however few they are (4
 // groups: 103 of 2338 blocks of a clustered set 82 us in FP32C, 17 us this way,
 // 299 of 12 thousand 80 against 13; FP64 15 of 1558 blocks 22 against 14 us,
-// 242 30 against 25, 476 even).
+// 242 30 against 25).  FP64 is even at 476 blocks; FP32C still gains past its
+// line (whole gradient, 461 blocks 571 against 640 us, 767 1000 against 1050,
+// even at about 1700), which is there for the rows, 4 KB a block in the context.
 constexpr int union_cap_large(int G) { return G >= 2 && G <= 4 ? kUnionSort : 0; }
 constexpr int64_t large_blocks(bool f64) { return f64 ? 256 : 512; }
 // Rows of a block's union in the adjoint's transposed gradient, which stages

@@ -142,7 +142,7 @@ void rt_destroy(rt_ctx *ctx) {
                     ctx->h_iters, ctx->node_lo, ctx->node_hi, ctx->node_hmax, ctx->n_nbr,
                     ctx->n_gath, ctx->wave_base, ctx->nbr, ctx->src_h, ctx->inj_gptr,
                     ctx->inj_gas, ctx->inj_src, ctx->inj_coef, ctx->inj_xi, ctx->src_ptr,
-                    ctx->src_gas, ctx->src_coef, ctx->status, ctx->partials, ctx->scan_tmp,
+                    ctx->src_gas, ctx->src_coef, ctx->status, ctx->partials,
                     ctx->adj_buf, ctx->hll_table, ctx->hll_table32, ctx->vol, ctx->ivan,
                     ctx->bin8, ctx->task, ctx->n_task, ctx->tstat, ctx->urows, ctx->urow, ctx->gloc,
                     ctx->uown, ctx->ublk, ctx->goff, ctx->arows, ctx->arow, ctx->agloc,

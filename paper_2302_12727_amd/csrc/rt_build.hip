@@ -1004,8 +1004,8 @@ __device__ __forceinline__ void level_tasks(bool active, int lane, int32_t &c, u
 // 64-particle column block of the neighbour table) and, flagged by the sign
 // bit, the tile partners it evaluates for both.  Which of the two evaluates
 // an in-tile pair is chosen to balance the lists, whose longest in each
-// group of 16 particles (one wave of the transport) sets the
-// iterations of a pass: one wave per tile starts from each particle's count
+// group of 16 particles (one wave of the transport, 8 at 8 lanes a particle)
+// sets the iterations of a pass: one wave per tile starts from each particle's count
 // of neighbours outside the tile and gives the tile's pairs, in a fixed order
 // (by the lower index, then by its list order), one by one to the particle
 // with the shorter list so far (the lower index on ties); level_tasks then
@@ -1262,12 +1262,6 @@ __global__ __launch_bounds__(1024) void k_union_left(int64_t nw, const int32_t *
         out[0] = base;
         out[1] = three ? 3 : w0;
     }
-}
-
-__device__ inline int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_down(v, d, 64);
-    return v;
 }
 
 // Statistics of a build, one block's share added to s: neighbour entries,

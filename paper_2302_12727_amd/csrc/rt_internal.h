@@ -88,7 +88,7 @@ constexpr int slices_of_2(int G) { return (G - 3 * slices_of_3(G)) / 2; }
 // 130 -> 97 us, 16 thousand 197 -> 160; 8 groups: 8000 196 -> 162).  FP32C, four
 // waves per SIMD with one group, up to 4 groups: four blocks a CU (3 groups: 4000
 // particles 129 -> 82 us, 16 thousand 96 -> 79, 939 blocks even; 5 HLL groups:
-// 4000 356 -> 180).
+// 4000 356 -> 183).
 constexpr int64_t one_group_blocks(bool f64, int G) {
     return G > 4 ? 1536 : !f64 ? 1024 : G == 4 ? 768 : 512;
 }
@@ -192,8 +192,6 @@ struct rt_ctx {
     int32_t *status = nullptr;   // device status word
     double *partials = nullptr;  // [nblocks][2 G] block partial sums
     int64_t nblocks = 0;
-    void *scan_tmp = nullptr;
-    size_t scan_tmp_bytes = 0;
     void *adj_buf = nullptr;     // adjoint scratch (see rt_adjoint.hip)
     size_t adj_bytes = 0;
 

@@ -33,8 +33,6 @@ __global__ void k_inject(int32_t ngas, int G, const int32_t *__restrict__ gptr,
     }
 }
 
-// two doubles as one 16-byte access (a native vector: copies stay in registers)
-
 // Gradient record of particle i from its Q lanes' sums (every lane holds the
 // combined sums acc = sum_j (q_j - q_i) w_ij s_ij and the own state Ui): the
 // gradients are B_i/V_i acc; the Q lanes write consecutive 16-byte pieces of
@@ -1060,6 +1058,9 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
     const bool wide = blocks <= kWideTiles, three = blocks > kThreeTiles;
     if (wide && off32) rt_route(ctx, "wide");
     if (three && G == 1 && off32 && !hll) rt_route(ctx, "three_waves");
+    // (one group a block is for few blocks, so its records are far below 4 GiB,
+    // and two groups in a wave for more than 256)
+    constexpr bool ALL32 = G == 1 && !WHOLE, WIDE = !(G == 2 && WHOLE);
 #define RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, Q_, W_)                                      \
     k_transport64_tile<G, WHOLE, OFF32_, HLL_, IVA_, BIN_, Q_, W_>                               \
         <<<grid, 64 * Q_, 0, ctx->stream>>>(                                                     \
@@ -1068,7 +1069,7 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
         (const double2 *)ctx->hll_table, tick, accm, ctx->bin8 ? ctx->bin8 + n : nullptr)
 #define RT_TILE_LAUNCH(OFF32_, HLL_, IVA_, BIN_)                                                 \
     do {                                                                                         \
-        if constexpr (OFF32_) {                                                                  \
+        if constexpr (OFF32_ && WIDE) {                                                          \
             if (wide) {                                                                          \
                 RT_TILE_LAUNCH_QW(OFF32_, HLL_, IVA_, BIN_, 8, 2);                               \
                 break;                                                                           \
@@ -1092,8 +1093,8 @@ void launch_tiles64(rt_ctx *ctx, Slices sl, const double *UD, const double *dt, 
     } while (0)
 #define RT_TILE_LAUNCH_S(HLL_, IVA_)                                                             \
     do {                                                                                         \
-        if (off32) RT_TILE_LAUNCH_B(true, HLL_, IVA_);                                           \
-        else RT_TILE_LAUNCH_B(false, HLL_, IVA_);                                                \
+        if (ALL32 || off32) RT_TILE_LAUNCH_B(true, HLL_, IVA_);                                  \
+        else RT_TILE_LAUNCH_B(ALL32, HLL_, IVA_);                                                \
     } while (0)
     if (hll && iva) RT_TILE_LAUNCH_S(true, true);
     else if (hll) RT_TILE_LAUNCH_S(true, false);
@@ -1253,9 +1254,8 @@ void rt_finalize_partials(rt_ctx *ctx, int64_t nb, double *Q, double *ledger) {
 }
 
 rt_status rt_ensure_partials(rt_ctx *ctx) {
-    // enough rows for every kernel that writes them (the FP64 transport runs
-    // up to 4 lanes per particle, so up to 4 blocks per kBlock particles)
-    const int64_t nb = (4 * ctx->p.n + kBlock - 1) / kBlock;
+    // enough rows for every kernel that writes them: one per tile at most
+    const int64_t nb = transport64_rows(ctx->p.n);
     if (ctx->partials && ctx->nblocks >= nb) return RT_OK;
     rt_free(ctx, ctx->partials);
     ctx->partials = nullptr;

@@ -625,7 +625,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
 }
 
 // FP32C transport with the pairs inside a tile evaluated once (GLF or HLL,
-// Hopkins or Ivanova surfaces, up to 3 groups or a slice of more): the tile
+// Hopkins or Ivanova surfaces, up to 3 groups): the tile
 // scheme of the FP64 transport (k_transport64_tile, the same task lists) in FP32
 // pair arithmetic.  Four lanes share a particle, each with compensated FP32
 // sums; the lane that evaluates an in-tile pair adds Phi_kl to its own and
@@ -641,8 +641,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANS
 // BIN: one tick of the individual-time-step scheme on the tiles, as in the
 // FP64 tile kernel (due pairs weighted by dt 2^min(b_k, b_l) in the
 // compensated sums, pending sums accm in FP64).
-// WHOLE: all G groups in a wave; else slices of G, in use one group a block
-// where the blocks are few (one_group_blocks).
+// WHOLE: all G groups in a wave; else one group a block, where the blocks are
+// few (one_group_blocks).
 template <int G, bool WHOLE, bool OFF32, bool HLL, bool BIN, bool IVA>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RT_TRANSPORT32_WAVES))) void
 k_transport32_tile(int64_t n, int64_t nb, Slices sl, const float *__restrict__ geo32,
@@ -1055,7 +1055,9 @@ void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, 
     const uint8_t *binm = ctx->bin8 ? ctx->bin8 + n : nullptr;
     unsigned long long *cnt = (unsigned long long *)counts;
     // rows addressed by 32-bit offsets while the gradient records fit 4 GiB
+    // (one group a block is for few blocks: always)
     const bool off32 = (uint64_t)n * 64u * ctx->p.groups < (uint64_t(1) << 32);
+    constexpr bool ALL32 = G == 1 && SLICES;
 #define RT_STEP32_LAUNCH(OFF32_, HLL_, BIN_, IVA_)                                               \
     do {                                                                                         \
         if constexpr (!TILES)                                                                    \
@@ -1078,8 +1080,8 @@ void launch_groups32(rt_ctx *ctx, Slices sl, const float *UD, const double *dt, 
     } while (0)
 #define RT_STEP32_LAUNCH_S(HLL_, IVA_)                                                           \
     do {                                                                                         \
-        if (off32) RT_STEP32_LAUNCH_B(true, HLL_, IVA_);                                         \
-        else RT_STEP32_LAUNCH_B(false, HLL_, IVA_);                                              \
+        if (ALL32 || off32) RT_STEP32_LAUNCH_B(true, HLL_, IVA_);                                \
+        else RT_STEP32_LAUNCH_B(ALL32, HLL_, IVA_);                                              \
     } while (0)
     if (hll && iva) RT_STEP32_LAUNCH_S(true, true);
     else if (hll) RT_STEP32_LAUNCH_S(true, false);

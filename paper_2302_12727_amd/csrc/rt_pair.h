@@ -315,7 +315,7 @@ __device__ __forceinline__ void block_reduce_store(double (&v)[NP], double *__re
 // mod 8), so that the 16-byte stores and loads of neighbouring lanes fall on
 // different banks.  (Padded rows of 17 doubles, PAD, take 8-byte accesses, but
 // one address for a row's pieces instead of eight: used where registers are
-// short.  3 groups, transport of the 128^3 lattice 3.01 -> 2.97 ms, of 100
+// short.  3 groups, transport of the 128^3 lattice 3.01 -> 2.97 ms, of 926
 // thousand clustered particles 1.82 -> 1.75 ms swizzled; one group at three
 // waves per SIMD 203 us swizzled, 23 registers spilled, 165 us padded, 64^3.)
 constexpr int kStage = 16;

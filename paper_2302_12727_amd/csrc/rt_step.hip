@@ -556,11 +556,13 @@ k_gradient64u(int64_t n, int64_t nb, const double *__restrict__ geo, const doubl
 // LDS too): from 513 tiles, two a CU, on 48^3 88.5 -> 85.0 us, 100^3 742 ->
 // 667; 32^3, where no third one comes, 28.3 -> 30.2.
 //
-// What bounds it: the FP64 vector instructions (half the issue slots) and the
-// waits of two waves per SIMD on the neighbours' rows.  Guard counts only where
-// they are asked for, the partners' sums without a sign change, and the
-// shorter reciprocals (rcp64, rsq64) took the 3-group 128^3 lattice from 3.04
-// to 2.93 ms.  (Rows staged once per tile in LDS, the groups one after the
+// What bounds it: the load path of the neighbours' rows (texture-data unit busy
+// 88% of the time on the 3-group 128^3 lattice and 85% on 926 thousand clustered
+// particles; FP64 instructions are half the issue slots; two waves per SIMD wait
+// 28% of their cycles).  HLL asks the same path for the table's scattered cells
+// (61^3, 2 groups: data 90%, addresses 78% against GLF's 51%).  Guard counts only
+// where they are asked for, the partners' sums without a sign change, and the
+// shorter reciprocals (rcp64, rsq64) took the lattice from 3.04 to 2.93 ms.  (Rows staged once per tile in LDS, the groups one after the
 // other with the pair geometry in registers, cut the rows from L2 sixfold and
 // ran 3.33 ms: a fifth more instructions, and barriers between the stages.)
 //

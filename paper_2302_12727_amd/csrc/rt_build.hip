@@ -114,9 +114,9 @@ __global__ void k_merge_level(int64_t first, int64_t count, double *__restrict__
 // most device memory those lists may take.
 constexpr int kNList = 128;
 constexpr int64_t kNListBytes = int64_t(16) << 30;
-// Bit of a particle's iteration count set when its candidate list overflowed
-// (its reach was cut).
-constexpr int32_t kIterOverflow = 1 << 24;
+// Bits of a particle's iteration count set when its candidate list overflowed (its
+// reach was cut), and when it is left to k_h_dense.
+constexpr int32_t kIterOverflow = 1 << 24, kIterDense = 1 << 25;
 
 struct Tree {
     const double *lo, *hi, *hmax;
@@ -339,48 +339,21 @@ __device__ __forceinline__ double sum8(double v) {
     return v + __shfl_xor(v, 4, 64);
 }
 
-// Smoothing length of each of the wave's points: root of
+// Smoothing length: root of
 //   g(h) = h^3 sum_j W(r_j, kappa h) - eta^3   (eq:number-of-neighbors),
 // i.e. (sigma/kappa^3) sum_j w(r_j / (kappa h)) = eta^3, by Newton-Raphson
-// safeguarded with bisection.  The r_j < kappa h_R are collected once per point
-// in LDS (kHList entries) and each sum is spread over the point's 8 lanes.  A
-// point with more than kHList particles in reach cuts h_R while it collects and
-// keeps the entries inside (overflow set; gathering again nearer in, which 45%
-// of 22 thousand clustered particles did, took 652 us, this 248 us).  One whose
-// root lies beyond an h_R that was not cut gathers again further out.  One whose
-// root lies beyond a cut h_R does so too, cut no nearer than what is known to be
-// too near, twice where a list can be expected to hold the root's particles
-// (N = 4 pi (kappa eta)^3 / 3), at once where not; then it is dense: summed
-// straight from the candidates of a gather per evaluation, none kept.  (Drawn
-// out and cut again until a serial walk took over, 64^3 particles at eta 1.8, all
-// of that kind, built in 54.7 ms, this way in 6.9; at eta 2.2 72.6 and 9.2, at
-// eta 1.65, N = 114, 4.7 and 3.6.  Dense at the first short list at the default
-// eta, N = 48: 22 thousand clustered particles 1.34 ms a rebuild against 1.27.)
-// `iters` counts the evaluations before the last one; an evaluation at h_R that
-// finds the root beyond it only places the next reach and counts neither there
-// nor against max_iter.
-constexpr int kHList = 128;
-template <class Cand>
-__device__ double h_solve_wave(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
-                               bool on, double px, double py, double pz, double h0, double eta,
-                               double kappa, double box, int32_t max_iter, Cand &B,
-                               double (&list)[kPts][kHList], int32_t &iters, int32_t &flags,
-                               bool &overflow) {
-    const int lane = threadIdx.x & 63, p = lane >> 3, c = lane & 7;
-    const double pref = kSigma3 / (kappa * kappa * kappa), eta3 = eta * eta * eta;
-    const double eps4 = 4.0 * 2.220446049250313e-16, ibox = 1.0 / box;
-    // iterates stay at or below hcap (compact support at most half the box); a
-    // root beyond it is an error
-    const double hcap = 0.5 * box / kappa;
-    double lo = 0.0, hi = INFINITY, h = fmin(h0, hcap);
-    double hR = fmin(1.5 * h, hcap);           // the list's reach over kappa
-    int32_t it = 0;
-    // short lists that were cut before a point is taken for a dense one
-    int spare = 4.0 / 3.0 * kPi * kappa * kappa * kappa * eta3 < 0.75 * kHList ? 2 : 0;
-    bool busy = on, dense = false;
-    // One step from the sums at h: true if it ends the solve, else the next
-    // iterate is in hn.
-    auto step = [&](double sw, double sdw, double &hn) {
+// safeguarded with bisection.  Iterates stay at or below hcap (compact support at
+// most half the box); a root beyond it is an error.
+struct HRoot {
+    double pref, eta3, hcap;
+    double lo = 0.0, hi = INFINITY, h;         // bracket and iterate
+    __device__ HRoot(double eta, double kappa, double box, double h0)
+        : pref(kSigma3 / (kappa * kappa * kappa)), eta3(eta * eta * eta),
+          hcap(0.5 * box / kappa), h(fmin(h0, hcap)) {}
+    // One step from the sums of w and w' q at h: true if it ends the solve (flags
+    // raised on an error), else the next iterate is in hn.
+    __device__ __forceinline__ bool step(double sw, double sdw, double &hn, int32_t &flags) {
+        const double eps4 = 4.0 * 2.220446049250313e-16;
         const double g = pref * sw - eta3, dg = -pref * sdw / h;
         if (g == 0.0) return true;
         if (g < 0.0) lo = h; else hi = h;
@@ -411,7 +384,34 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
             return true;
         }
         return false;
-    };
+    }
+};
+
+// The solve of each of the wave's points from lists: the r_j < kappa h_R are
+// collected once per point in LDS (kHList entries) and each sum is spread over the
+// point's 8 lanes.  A point with more than kHList particles in reach cuts h_R while
+// it collects and keeps the entries inside (overflow set; gathering again nearer
+// in, which 45% of 22 thousand clustered particles did, took 652 us, this 248 us).
+// One whose root lies beyond an h_R that was not cut gathers again further out.
+// One whose root lies beyond a cut h_R does so too, cut no nearer than what is
+// known to be too near, twice where a list can be expected to hold the root's
+// particles (N = 4 pi (kappa eta)^3 / 3), at once where not; then it is left, with
+// its iterate and dense set, to h_solve_dense.  `it` counts the evaluations before
+// the last one; an evaluation at h_R that finds the root beyond it only places the
+// next reach and counts neither there nor against max_iter.
+constexpr int kHList = 128;
+__device__ void h_solve_lists(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
+                              bool on, double px, double py, double pz, double eta, double kappa,
+                              double box, int32_t max_iter, Candidates<false> &B,
+                              double (&list)[kPts][kHList], HRoot &r, int32_t &it, int32_t &flags,
+                              bool &overflow, bool &dense) {
+    const int lane = threadIdx.x & 63, p = lane >> 3, c = lane & 7;
+    const double ibox = 1.0 / box;
+    double hR = fmin(1.5 * r.h, r.hcap);       // the list's reach over kappa
+    // short lists that were cut before a point is taken for a dense one
+    int spare = 4.0 / 3.0 * kPi * kappa * kappa * kappa * r.eta3 < 0.75 * kHList ? 2 : 0;
+    bool busy = on;
+    dense = false;
 #pragma unroll 1
     while (__ballot(busy) != 0) {
         double R = busy ? kappa * hR : -1.0, R2 = R * R;
@@ -425,7 +425,7 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                     const bool cut = cnt > kHList - 8;
                     if (cut) {
                         overflow = true;
-                        R = --left < 0 ? 0.0 : fmax(0.875 * R, 0.5 * (R + kappa * lo));
+                        R = --left < 0 ? 0.0 : fmax(0.875 * R, 0.5 * (R + kappa * r.lo));
                         R2 = R * R;
                     }
                     int keep = 0;
@@ -462,8 +462,8 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
             dense = !(hR > 0.0);               // no list fits
             busy = !dense;
             if (busy) {
-                probe = h > hR;
-                h = fmin(h, hR);
+                probe = r.h > hR;
+                r.h = fmin(r.h, hR);
             }
         }
         // Newton-Raphson on the list, while it reaches
@@ -474,7 +474,7 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                 busy = false;
                 break;
             }
-            const double iH = 1.0 / (kappa * h);
+            const double iH = 1.0 / (kappa * r.h);
             double sw = 0.0, sdw = 0.0;
             for (int k = c; k < cnt; k += 8) {
                 const double q = list[p][k] * iH;
@@ -482,35 +482,49 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
                 sdw += kern_dw(q) * q;
             }
             double hn;
-            if (step(sum8(sw), sum8(sdw), hn)) {
+            if (r.step(sum8(sw), sum8(sdw), hn, flags)) {
                 busy = false;
                 break;
             }
-            if (hi == INFINITY && hn > hR) {
-                if (h < hR) {
+            if (r.hi == INFINITY && hn > hR) {
+                if (r.h < hR) {
                     hn = hR;                     // the list's end first
                     probe = true;
                 } else {                         // the root lies beyond
                     it -= probe;
-                    hR = fmin(fmax(1.15 * hn, 1.25 * hR), hcap);
+                    hR = fmin(fmax(1.15 * hn, 1.25 * hR), r.hcap);
                     dense = was_cut && --spare < 0;
                     busy = !dense;
                     more = false;
                 }
             }
-            h = hn;
+            r.h = hn;
             ++it;
         }
         wave_lds_sync();
     }
-    // the dense points: a gather per evaluation
+}
+
+// The solve, from the iterate r.h on, of the points with more particles at their
+// root than a list holds: summed straight from the candidates of a gather per
+// evaluation, none kept.  (Lists drawn out and cut again until a serial walk took
+// over, 64^3 particles at eta 1.8, all of that kind, built in 54.7 ms, this way in
+// 7.0; at eta 2.2 72.6 and 9.3, at eta 1.65, N = 114, 4.7 and 3.7.  Dense at the
+// first short list at the default eta, N = 48: 22 thousand clustered particles
+// 1.34 ms a rebuild against 1.27.)
+__device__ void h_solve_dense(const Tree &T, int depth, const double *__restrict__ xs, int64_t n,
+                              bool dense, double px, double py, double pz, double kappa,
+                              double box, int32_t max_iter, Candidates<false> &B, HRoot &r,
+                              int32_t &it, int32_t &flags) {
+    const int c = threadIdx.x & 7;
+    const double ibox = 1.0 / box;
 #pragma unroll 1
     while (__ballot(dense) != 0) {
         if (dense && it >= max_iter) {
             flags |= ST_NOCONV;
             dense = false;
         }
-        const double R = dense ? kappa * h : -1.0, R2 = R * R, iH = 1.0 / (kappa * h);
+        const double R = dense ? kappa * r.h : -1.0, R2 = R * R, iH = 1.0 / (kappa * r.h);
         double sw = 0.0, sdw = 0.0;
         wave_gather<false>(T, depth, xs, nullptr, n, box, px, py, pz, R, B, [&](int m) {
             for (int q = c; q < m; q += 8) {
@@ -529,23 +543,27 @@ __device__ double h_solve_wave(const Tree &T, int depth, const double *__restric
         sw = sum8(sw);
         sdw = sum8(sdw);
         if (dense) {
-            if (step(sw, sdw, hn)) {
+            if (r.step(sw, sdw, hn, flags)) {
                 dense = false;
             } else {
-                h = hn;
+                r.h = hn;
                 ++it;
             }
         }
     }
-    iters = it;
-    return h;
 }
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_h_solve(int64_t n, int64_t ng, Tree T, int depth,
-                                                const double *__restrict__ xs, double eta,
-                                                double kappa, double box, double *__restrict__ h,
-                                                int32_t max_iter, int32_t *__restrict__ iters,
-                                                int32_t *__restrict__ status) {
+// Smoothing lengths, one wave for 8 particles: from lists, and then the dense points
+// (k_h_dense, whose waves leave at once if no point was left to it: a grid of 4
+// rounds of the card's waves at most, since a wave for every 8 particles takes 56 us
+// to come and go on the 128^3 lattice).  Two kernels, because a second gather in
+// the first one costs it registers: 32 spilled and 2.36 ms on that lattice, against
+// 2.26 without.
+constexpr int64_t kDenseGrid = 4 * 256 * 12;
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_h_solve(
+    int64_t n, int64_t ng, Tree T, int depth, const double *__restrict__ xs, double eta,
+    double kappa, double box, double *__restrict__ h, int32_t max_iter,
+    int32_t *__restrict__ iters, int32_t *__restrict__ status) {
     __shared__ Candidates<false> B;
     __shared__ double list[kPts][kHList];
     const int64_t g = xcd_block(ng);
@@ -555,14 +573,43 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     const bool on = i < n;
     const int64_t ic = on ? i : n - 1;
     int32_t it = 0, fl = 0;
-    bool ovf = false;
-    const double hv = h_solve_wave(T, depth, xs, n, on, xs[3 * ic], xs[3 * ic + 1], xs[3 * ic + 2],
-                                   fmin(h[ic], 0.25 * box / kappa), eta, kappa, box, max_iter, B,
-                                   list, it, fl, ovf);
+    bool ovf = false, dense = false;
+    HRoot r(eta, kappa, box, fmin(h[ic], 0.25 * box / kappa));
+    h_solve_lists(T, depth, xs, n, on, xs[3 * ic], xs[3 * ic + 1], xs[3 * ic + 2], eta, kappa, box,
+                  max_iter, B, list, r, it, fl, ovf, dense);
     if (on && (lane & 7) == 0) {
-        h[i] = hv;
-        iters[i] = it | (ovf ? kIterOverflow : 0);
+        h[i] = r.h;
+        iters[i] = it | (ovf ? kIterOverflow : 0) | (dense ? kIterDense : 0);
+        if (dense) fl |= ST_DENSE;
         if (fl) atomicOr(status, fl);
+    }
+}
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_h_dense(
+    int64_t n, int64_t ng, Tree T, int depth, const double *__restrict__ xs, double eta,
+    double kappa, double box, double *__restrict__ h, int32_t max_iter,
+    int32_t *__restrict__ iters, int32_t *__restrict__ status) {
+    __shared__ Candidates<false> B;
+    if (!(*status & ST_DENSE)) return;
+    const int lane = threadIdx.x;
+    const int64_t chunk = (ng + 7) / 8;         // groups of an XCD, as xcd_block's
+    for (int64_t v = blockIdx.x; v < 8 * chunk; v += gridDim.x) {
+        const int64_t g = (v & 7) * chunk + (v >> 3);
+        const int64_t i = g * kPts + (lane >> 3);
+        const bool on = i < n;
+        const int64_t ic = on ? i : n - 1;
+        const int32_t word = iters[ic];
+        const bool dense = on && (word & kIterDense);
+        if (__ballot(dense) == 0) continue;
+        int32_t it = word & (kIterOverflow - 1), fl = 0;
+        HRoot r(eta, kappa, box, h[ic]);
+        h_solve_dense(T, depth, xs, n, dense, xs[3 * ic], xs[3 * ic + 1], xs[3 * ic + 2], kappa,
+                      box, max_iter, B, r, it, fl);
+        if (dense && (lane & 7) == 0) {
+            h[i] = r.h;
+            iters[i] = it | kIterOverflow;
+            if (fl) atomicOr(status, fl);
+        }
     }
 }
 
@@ -850,12 +897,13 @@ __global__ __launch_bounds__(64) void k_src_h(int32_t S, Tree T, int depth,
         else hi = m;
     }
     int32_t it = 0, fl = 0;
-    bool ovf = false;
-    const double hv = h_solve_wave(T, depth, xs, n, threadIdx.x < 8, px, py, pz,
-                                   fmin(geo[(int64_t)kRec * lo + R_H], 0.25 * box / kappa), eta,
-                                   kappa, box, max_iter, B, list, it, fl, ovf);
+    bool ovf = false, dense = false;
+    HRoot r(eta, kappa, box, fmin(geo[(int64_t)kRec * lo + R_H], 0.25 * box / kappa));
+    h_solve_lists(T, depth, xs, n, threadIdx.x < 8, px, py, pz, eta, kappa, box, max_iter, B, list,
+                  r, it, fl, ovf, dense);
+    h_solve_dense(T, depth, xs, n, dense, px, py, pz, kappa, box, max_iter, B, r, it, fl);
     if (threadIdx.x == 0) {
-        src_h[s] = hv;
+        src_h[s] = r.h;
         if (fl) atomicOr(status, fl);
     }
 }
@@ -1461,6 +1509,9 @@ rt_status rt_build_impl(rt_ctx *ctx, const double *x, const double *h_in, int64_
                                                              ctx->p.kappa, ctx->p.box, h,
                                                              ctx->h_iter_cap, ctx->h_iters,
                                                              ctx->status);
+            k_h_dense<<<(unsigned)std::min<int64_t>(xcd_grid(n8), kDenseGrid), 64, 0, st>>>(
+                n, n8, T, depth, ctx->xs, ctx->p.eta, ctx->p.kappa, ctx->p.box, h, ctx->h_iter_cap,
+                ctx->h_iters, ctx->status);
         } else {
             HIP_OR_FAIL(hipMemsetAsync(ctx->h_iters, 0, sizeof(int32_t) * n, st));
         }

@@ -51,7 +51,8 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr double kSigma3 = 16.0 / kPi;   // cubic spline normalisation in 3D
 
 // Device status word bits.
-enum : int32_t { ST_NOCONV = 1, ST_SINGULAR = 2, ST_BIGH = 4, ST_NONFINITE = 8 };
+// (ST_DENSE: within a build, points left to k_h_dense)
+enum : int32_t { ST_NOCONV = 1, ST_SINGULAR = 2, ST_BIGH = 4, ST_NONFINITE = 8, ST_DENSE = 16 };
 
 // Geometry record, one per particle (Morton order), 128 bytes (12 used):
 //   0..2  x, y, z       position in [0, box)

@@ -11,6 +11,7 @@ the place of an iterate further from the root.
 import numpy as np
 import pytest
 import torch
+from scipy.spatial import cKDTree
 
 import oracle
 import workloads
@@ -117,3 +118,14 @@ def test_more_neighbours_than_a_list_holds(x, eta):
     log(f"h error {err:.1e}, of sources {serr:.1e}, most gather neighbours {np.diff(geo.gptr).max()}")
     assert np.diff(geo.gptr).max() > 120
     assert err < 1e-13 and serr < 1e-13
+
+
+def test_more_dense_groups_than_the_grid():
+    """Every point dense, in 12 978 groups of 8: the dense points' kernel runs
+    12 288 waves at most, so some take a second group (the last one has 7)."""
+    x = workloads.jittered_lattice(47, 0.1, 2)
+    rt = RT(x.shape[0], 1, eta=1.8)
+    perm, h, _, _ = rt.rt_build_cells(dev(x))
+    ref, _ = oracle.solve_h(cKDTree(x, boxsize=1.0), x, 1.8)
+    assert rt.rt_get_stats()["h_list_overflow"] == x.shape[0]
+    assert np.abs(unsort(h.cpu().numpy(), perm.cpu().numpy()) / ref - 1).max() < 1e-13
